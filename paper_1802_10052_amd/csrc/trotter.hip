@@ -25,206 +25,206 @@
 namespace ed {
 namespace {
 
-// 512 threads per 4096-amplitude tile (measured against 256 and 1024), one gate per LDS round:
-// rounds that apply two gates of a layer on adjacent pairs to groups of 16 (kPairRounds) leave
-// half of 512 threads idle and were slower
-constexpr int kGThreads = 512;
-constexpr int kGThreadBits = kGThreads == 256 ? 8 : kGThreads == 512 ? 9 : 10;
 constexpr int kGTileBits = 12;
-constexpr int kGSlots = (1 << kGTileBits) / kGThreads;  // amplitudes per thread
-constexpr int kGSlotBits = kGTileBits - kGThreadBits;
-constexpr bool kPairRounds = false;
+constexpr int kGThreads = 256;                           // 16 amplitudes (4 tile bits) per thread
+constexpr int kGRegBits = 4;
+constexpr int kGSlots = 1 << kGRegBits;
+constexpr int kSmallThreads = 512;                       // tiles of fewer than 12 bits
 constexpr int kGLow = 4;                                 // contiguous low bits of a window tile
 constexpr int kFuse = 4;                                 // consecutive layers per run of passes
-constexpr int kMaxGates = kFuse * (kGTileBits / 2);      // gates of one pass
 constexpr int kTableGates = 192;                         // gates one evolve call holds
-// the gate table: 16 double2 (the matrix) per gate, then 2 ints (q, layer) per gate
-constexpr size_t kGateTableBytes = size_t(kTableGates) * (16 * sizeof(double2) + 2 * sizeof(int));
+// the gate table: 16 double2 (the matrix) per gate, then 2 ints per gate: the gates' codes, and as
+// many slots for the rounds of all passes (a round holds a gate, or is one of a pass's two staging
+// rounds, and a pass holds more rounds than one)
+constexpr int kTableRounds = kTableGates;
+constexpr size_t kGateTableBytes = size_t(kTableGates) * 16 * sizeof(double2) +
+                                   size_t(kTableGates + kTableRounds) * sizeof(int);
 
-// One pass: tile geometry and the gates it applies, sorted by (layer, q), in device memory: gate g
-// of the pass acts on tile-local bits (q, q+1) = (G[2 g], G[2 g] + 1) for the layer G[2 g + 1] of
-// the run, and maps the local pair index l = 2 bit(q+1) + bit(q) (bit q+1 is the left site of the
-// bond) by the 4x4 matrix U[16 g + 4 l + m].
+// One pass: tile geometry and its gates, sorted by round, in device memory. Gate g of the pass maps
+// the local pair index l = 2 bit(q+1) + bit(q) of the tile bits (q, q+1) (bit q+1 is the left site
+// of the bond) by the 4x4 matrix U[16 g + 4 l + m]; its code G[g] is q, or for a 12-bit tile
+// 1 << (q - a) of its round a, times kCross when the matrix couples 00 only with 11 and 01 only with
+// 10. A round r of
+// a 12-bit tile (code R[r]) holds the tile bits a..a+3 of 16 amplitudes in the registers of a
+// thread and applies gates g0..g1-1 to them.
 struct GatePass {
     int first;   // contiguous tile of the tbits low bits
     int c, h0;   // window tile: c low bits, window bits [h0, h0 + tbits - c)
     int tbits;   // tile bits (min(L, 12))
     int ngate;
+    int nround;
     const double2* U;
     const int* G;
+    const int* R;
 };
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+constexpr int kCross = 8;
+__host__ __device__ constexpr int round_code(int a, int g0, int g1) { return a | (g0 << 8) | (g1 << 18); }
+
+// a = u a + c in a's own register (u uniform). Left to itself the compiler accumulates into c and
+// copies every result back: 32 copies per gate beside its 256 multiply-adds.
+__device__ __forceinline__ void fma_into(double& a, double u, double c) {
+    asm("v_fma_f64 %0, %1, %0, %2" : "+v"(a) : "s"(u), "v"(c));
 }
 
-__device__ __forceinline__ int64_t gate_index(const GatePass& gp, int64_t n, int i) {
-    if (gp.first) return (n << gp.tbits) + i;
-    const int w = gp.tbits - gp.c;
-    const int lo_bits = gp.h0 - gp.c;
-    const int64_t nlo = n & ((int64_t(1) << lo_bits) - 1), nhi = n >> lo_bits;
-    const int lowmask = (1 << gp.c) - 1;
-    return (nlo << gp.c) | (nhi << (gp.h0 + w)) | int64_t(i & lowmask) | (int64_t(i >> gp.c) << gp.h0);
-}
-
-// Gate on register bits (kGThreadBits + R, kGThreadBits + R + 1): slots k, k | 1 << R, k | 2 << R,
-// k | 3 << R hold the pair indices l = 0..3 of one group (compile-time slot indices keep v in
-// registers).
-template <int R>
+// One gate on register bits (R, R+1): slots k, k | 1 << R, k | 2 << R, k | 3 << R hold the pair
+// indices l = 0..3 of one group (compile-time slot indices keep v in registers).
+template <int R, bool CROSS>
 __device__ __forceinline__ void reg_gate(double2 (&v)[kGSlots], const double2* __restrict__ U) {
-    static_assert(R + 2 <= kGSlotBits, "gate bits beyond the register slots");
+    static_assert(R + 2 <= kGRegBits, "gate bits beyond the register slots");
 #pragma unroll
     for (int k = 0; k < kGSlots; ++k) {
         if (((k >> R) & 3) != 0) continue;
         const double2 a[4] = {v[k], v[k | (1 << R)], v[k | (2 << R)], v[k | (3 << R)]};
-        double2 o[4];
+        // the diagonal's real part last, into the amplitude's own register
+        double2 acc[4];
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
-            double2 acc = make_double2(0.0, 0.0);
+            const double ui = U[5 * l].y;
+            acc[l] = make_double2(-ui * a[l].y, ui * a[l].x);
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const double2 p = cmul(U[4 * l + m], a[m]);
-                acc.x += p.x;
-                acc.y += p.y;
+                if (m == l || (CROSS && m != 3 - l)) continue;
+                const double2 u = U[4 * l + m];
+                acc[l].x = fma(u.x, a[m].x, fma(-u.y, a[m].y, acc[l].x));
+                acc[l].y = fma(u.x, a[m].y, fma(u.y, a[m].x, acc[l].y));
             }
-            o[l] = acc;
         }
-        v[k] = o[0];
-        v[k | (1 << R)] = o[1];
-        v[k | (2 << R)] = o[2];
-        v[k | (3 << R)] = o[3];
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            fma_into(v[k | (l << R)].x, U[5 * l].x, acc[l].x);
+            fma_into(v[k | (l << R)].y, U[5 * l].x, acc[l].y);
+        }
     }
 }
 
-// A gate of the first layer whose two bits are register bits of an N-amplitude tile.
-__device__ __forceinline__ bool in_regs(int layer, int q, int N) {
-    return layer == 0 && q >= kGThreadBits && (1 << (q + 2)) <= N;
+// LDS position of tile index i (doubles): the low five bits take the XOR of bits 4..8, so that 32
+// neighbouring lanes hit 32 different 8-byte columns whatever four bits the registers hold
+// (without it, a round on bits below 4 puts all lanes on one column).
+__host__ __device__ constexpr int swz(int i) { return i ^ ((i >> 4) & 15) ^ ((i >> 4) & 16); }
+
+// swz is linear over XOR: slot m of a round at bit a sits at swz(slot 0) ^ swz(m << a), the second
+// part the same for all threads (scalar, in bytes)
+__device__ __forceinline__ unsigned slot_bytes(int m, int a) {
+    return unsigned(__builtin_amdgcn_readfirstlane(swz(m << a) * 8));
+}
+__device__ __forceinline__ double* lds_at(double* s, unsigned bytes) {
+    return reinterpret_cast<double*>(reinterpret_cast<char*>(s) + bytes);
 }
 
-// Tile-local index of slot k of thread t: i = t + kGThreads k (the low kGThreadBits bits across
-// threads, the rest across the register slots). Gates of the first layer whose two bits are both
-// register bits are applied in registers while the tile is loaded; the others update groups of
-// four amplitudes in LDS.
-__global__ __launch_bounds__(kGThreads) void gate_pass(double2* __restrict__ psi, GatePass gp,
-                                                       const double2* __restrict__ Utab,
-                                                       const int* __restrict__ G) {
-    __shared__ double2 s[1 << kGTileBits];
+// A pass over 12-bit tiles. What a gate costs is FP64 arithmetic (16 complex multiply-adds per group
+// of four amplitudes), a trip of the tile through LDS, and its share of the pass's trip through
+// HBM. Holding four tile bits in registers lets a round apply the gates of up to three layers on
+// those bits (three on average) for one LDS trip; the trip between two rounds goes component by
+// component, so a tile takes 32 KiB of LDS and four tiles of 256 threads share a CU, one's loads and
+// LDS trips under the others' arithmetic. The first round's registers are filled straight from
+// the state and the last round's go straight back (their bits are above the low four, so 16 lanes
+// cover 256 contiguous bytes).
+// L = 27 TFIM, order 4 (14 passes, 143 gates): 16.4 ms per step, 23.5 ms with one gate per LDS trip;
+// windows of 8 to 12 gates take 0.85-0.93 ms (4.6-5.0 TB/s), the low tiles' 16 to 20 gates
+// 1.6-1.9 ms (FP64-bound). Measured besides: whole amplitudes through 64 KiB of LDS, two tiles per CU
+// (16.8 ms); 512 threads of 8 amplitudes (17.9 ms).
+__global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void gate_pass(double2* __restrict__ psi, GatePass gp, const double2* __restrict__ Utab, const int* __restrict__ G,
+               const int* __restrict__ R) {
+    __shared__ double s[1 << kGTileBits];
+    const int t = threadIdx.x;
+    const int64_t n = blockIdx.x;
+    // global index of tile index i: base + (i & 15) + (i >> 4) << hs, for either geometry
+    int64_t base;
+    int hs;
+    if (gp.first) {
+        base = n << kGTileBits;
+        hs = kGLow;
+    } else {
+        const int lo_bits = gp.h0 - gp.c;
+        const int64_t nlo = n & ((int64_t(1) << lo_bits) - 1), nhi = n >> lo_bits;
+        base = (nlo << gp.c) | (nhi << (gp.h0 + kGTileBits - gp.c));
+        hs = gp.h0;
+    }
+    double2 v[kGSlots];
+    for (int r = 0; r < gp.nround; ++r) {
+        const int code = R[r];
+        const int a = code & 255, g0 = (code >> 8) & 1023, g1 = code >> 18;
+        const int b = (t & ((1 << a) - 1)) | ((t >> a) << (a + kGRegBits));  // slot 0 of this thread
+        if (r == 0) {  // a >= kGLow
+            const double2* p = psi + base + ((int64_t(b >> kGLow) << hs) | (b & ((1 << kGLow) - 1)));
+            const int64_t st = int64_t(1) << (hs + a - kGLow);
+#pragma unroll
+            for (int m = 0; m < kGSlots; ++m) v[m] = p[m * st];
+        }
+        for (int g = g0; g < g1; ++g) {
+            const double2* U = Utab + 16 * g;
+            // one bit per body, tested one after the other (a switch, or tests that the compiler can
+            // prove exclusive, made it copy all slots after every gate)
+            const int code = G[g];
+            if (code & 1) reg_gate<0, false>(v, U);
+            if (code & 2) reg_gate<1, false>(v, U);
+            if (code & 4) reg_gate<2, false>(v, U);
+            if (code & (kCross << 0)) reg_gate<0, true>(v, U);
+            if (code & (kCross << 1)) reg_gate<1, true>(v, U);
+            if (code & (kCross << 2)) reg_gate<2, true>(v, U);
+        }
+        if (r + 1 == gp.nround) {  // a >= kGLow
+            double2* p = psi + base + ((int64_t(b >> kGLow) << hs) | (b & ((1 << kGLow) - 1)));
+            const int64_t st = int64_t(1) << (hs + a - kGLow);
+#pragma unroll
+            for (int m = 0; m < kGSlots; ++m) p[m * st] = v[m];
+        } else {
+            // to the next round's slots; a thread writes only positions that it read itself last, so no
+            // barrier is needed before the first write
+            const int a2 = R[r + 1] & 255;
+            const int b2 = (t & ((1 << a2) - 1)) | ((t >> a2) << (a2 + kGRegBits));
+            const unsigned pb = unsigned(swz(b)) * 8u, pb2 = unsigned(swz(b2)) * 8u;
+#pragma unroll
+            for (int m = 0; m < kGSlots; ++m) *lds_at(s, pb ^ slot_bytes(m, a)) = v[m].x;
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < kGSlots; ++m) v[m].x = *lds_at(s, pb2 ^ slot_bytes(m, a2));
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < kGSlots; ++m) *lds_at(s, pb ^ slot_bytes(m, a)) = v[m].y;
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < kGSlots; ++m) v[m].y = *lds_at(s, pb2 ^ slot_bytes(m, a2));
+        }
+    }
+}
+
+// A chain of fewer than 12 sites is one tile in one workgroup: latency counts, so every gate spreads
+// its groups of four over 512 threads, in list order (by layer).
+__global__ __launch_bounds__(kSmallThreads) void gate_pass_small(double2* __restrict__ psi, GatePass gp,
+                                                                 const double2* __restrict__ Utab,
+                                                                 const int* __restrict__ G) {
+    __shared__ double2 s[1 << (kGTileBits - 1)];
     const int t = threadIdx.x;
     const int N = 1 << gp.tbits;
-    const int64_t n = blockIdx.x;
-    double2 v[kGSlots];
-#pragma unroll
-    for (int k = 0; k < kGSlots; ++k) {
-        const int i = t + kGThreads * k;
-        if (i < N) v[k] = psi[gate_index(gp, n, i)];
-    }
-    // the first layer's gates on register bits (q, q+1 >= 8) first: the four amplitudes are slots
-    // of one thread (they commute with the rest of that layer)
-    // (a switch in the kernel body: written as a chain of ifs, or inside a helper taking the slots
-    // by reference, the slots went to scratch memory)
-    for (int g = 0; g < gp.ngate; ++g) {
-        if (!in_regs(G[2 * g + 1], G[2 * g], N)) continue;
-        const double2* U = Utab + 16 * g;
-        switch (G[2 * g] - kGThreadBits) {
-            case 0: reg_gate<0>(v, U); break;
-            case 1:
-                if constexpr (kGSlotBits >= 3) reg_gate<1>(v, U);
-                break;
-            default:
-                if constexpr (kGSlotBits >= 4) reg_gate<2>(v, U);
-                break;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kGSlots; ++k) {
-        const int i = t + kGThreads * k;
-        if (i < N) s[i] = v[k];
-    }
+    for (int i = t; i < N; i += kSmallThreads) s[i] = psi[i];
     __syncthreads();
-    // LDS gates, in list order: each thread owns whole groups of the amplitudes a gate mixes (the
-    // index with zero bits inserted at q), reads them, writes them back. With kPairRounds, two
-    // gates of one layer on adjacent pairs (q, q+1), (q+2, q+3) share one round on groups of 16.
     for (int g = 0; g < gp.ngate; ++g) {
-        const int q = G[2 * g], layer = G[2 * g + 1];
-        if (in_regs(layer, q, N)) continue;  // done in registers
+        const int q = G[g];
         const double2* U = Utab + 16 * g;
-        const bool two = kPairRounds && g + 1 < gp.ngate && G[2 * g + 3] == layer && G[2 * g + 2] == q + 2 &&
-                         !in_regs(layer, q + 2, N);
-        if (two) {
-            const double2* U2 = Utab + 16 * (g + 1);
-            const int lowm = (1 << q) - 1;
-            for (int j = t; j < (N >> 4); j += kGThreads) {
-                const int b = (j & lowm) | ((j >> q) << (q + 4));
-                double2 a[16];
+        const int lowm = (1 << q) - 1;
+        for (int j = t; j < (N >> 2); j += kSmallThreads) {
+            const int b = (j & lowm) | ((j >> q) << (q + 2));
+            double2 a[4];
 #pragma unroll
-                for (int m = 0; m < 16; ++m) a[m] = s[b | (m << q)];
-                // first gate on the low pair (bits q, q+1) of every group of four
+            for (int m = 0; m < 4; ++m) a[m] = s[b | (m << q)];
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    double2 o[4];
+            for (int l = 0; l < 4; ++l) {
+                double2 acc = make_double2(0.0, 0.0);
 #pragma unroll
-                    for (int l = 0; l < 4; ++l) {
-                        double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            const double2 p = cmul(U[4 * l + m], a[4 * h + m]);
-                            acc.x += p.x;
-                            acc.y += p.y;
-                        }
-                        o[l] = acc;
-                    }
-#pragma unroll
-                    for (int l = 0; l < 4; ++l) a[4 * h + l] = o[l];
+                for (int m = 0; m < 4; ++m) {
+                    const double2 u = U[4 * l + m];
+                    acc.x = fma(u.x, a[m].x, fma(-u.y, a[m].y, acc.x));
+                    acc.y = fma(u.x, a[m].y, fma(u.y, a[m].x, acc.y));
                 }
-                // second gate on the high pair (bits q+2, q+3)
-#pragma unroll
-                for (int lo = 0; lo < 4; ++lo) {
-                    double2 o[4];
-#pragma unroll
-                    for (int l = 0; l < 4; ++l) {
-                        double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            const double2 p = cmul(U2[4 * l + m], a[4 * m + lo]);
-                            acc.x += p.x;
-                            acc.y += p.y;
-                        }
-                        o[l] = acc;
-                    }
-#pragma unroll
-                    for (int l = 0; l < 4; ++l) a[4 * l + lo] = o[l];
-                }
-#pragma unroll
-                for (int m = 0; m < 16; ++m) s[b | (m << q)] = a[m];
-            }
-            ++g;
-        } else {
-            const int lowm = (1 << q) - 1;
-            for (int j = t; j < (N >> 2); j += kGThreads) {
-                const int b = (j & lowm) | ((j >> q) << (q + 2));
-                double2 a[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) a[m] = s[b | (m << q)];
-#pragma unroll
-                for (int l = 0; l < 4; ++l) {
-                    double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const double2 p = cmul(U[4 * l + m], a[m]);
-                        acc.x += p.x;
-                        acc.y += p.y;
-                    }
-                    s[b | (l << q)] = acc;
-                }
+                s[b | (l << q)] = acc;
             }
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int k = 0; k < kGSlots; ++k) {
-        const int i = t + kGThreads * k;
-        if (i < N) psi[gate_index(gp, n, i)] = s[i];
-    }
+    for (int i = t; i < N; i += kSmallThreads) psi[i] = s[i];
 }
 
 struct Geometry {
@@ -256,17 +256,79 @@ void bond_hamiltonian(const ed_model* m, int p, cplx* h) {
         }
 }
 
+// Host copy of a call's gate table and its place in device memory (null: only counting passes).
+struct GateTable {
+    std::vector<double2> U;
+    std::vector<int> G, R;
+    const double2* dev_U = nullptr;
+    const int *dev_G = nullptr, *dev_R = nullptr;
+};
+
+// Rounds of a pass over a 12-bit tile. gates: (layer, q) by layer, then q; a_min: the lowest register
+// bit a round may start at. Each round takes four adjacent tile bits and every gate on them that is
+// free, layer by layer (no unapplied gate of an earlier layer shares a bit with it); the four bits
+// with the most such gates come first. The first and the last round must start at bit kGLow or above
+// (they move the tile from and to memory), so a round without gates is put before or after where
+// that leaves no other choice. order: the gates by round; base: the round's first bit, per gate of
+// order; R: the rounds' codes (appended).
+void plan_rounds(const std::vector<std::pair<int, int>>& gates, int a_min, std::vector<int>* order,
+                 std::vector<int>* base, std::vector<int>* R) {
+    const int n = int(gates.size());
+    const int a_max = kGTileBits - kGRegBits;
+    std::vector<char> done(n, 0);
+    auto take = [&](int a, std::vector<char> d) {
+        std::vector<int> got;
+        for (int g = 0; g < n; ++g) {
+            if (d[g] || gates[g].second < a || gates[g].second + 1 >= a + kGRegBits) continue;
+            bool free = true;
+            for (int e = 0; e < n && free; ++e)
+                free = d[e] || gates[e].first >= gates[g].first || std::abs(gates[e].second - gates[g].second) > 1;
+            if (free) {
+                d[g] = 1;
+                got.push_back(g);
+            }
+        }
+        return got;
+    };
+    bool first_round = true;
+    int last_a = a_max;
+    base->clear();
+    while (int(order->size()) < n) {
+        std::vector<int> best;
+        int best_a = -1;
+        for (int a = a_max; a >= (first_round ? kGLow : a_min); --a) {
+            const std::vector<int> got = take(a, done);
+            if (got.size() > best.size()) {
+                best = got;
+                best_a = a;
+            }
+        }
+        if (best.empty()) {
+            if (!first_round) return;  // no free gate: cannot happen for gates listed by layer
+            best_a = a_max;            // all free gates sit below: a round without gates stages the tile
+        }
+        R->push_back(round_code(best_a, int(order->size()), int(order->size() + best.size())));
+        for (int g : best) {
+            done[g] = 1;
+            order->push_back(g);
+            base->push_back(best_a);
+        }
+        last_a = best_a;
+        first_round = false;
+    }
+    if (last_a < kGLow) R->push_back(round_code(a_max, n, n));
+}
+
 // Passes of a run of consecutive layers (part, time): layer l holds the propagators exp(-i t_l h)
 // of the bonds whose left site k has the layer's parity (1: odd k, H_o; 0: even k, H_e). The first
 // pass is the contiguous tile of the 12 low bits; each later pass is a window of 8 bits above 4
 // contiguous low bits, starting at the lowest bond still pending. A gate (l, p) on bits (p, p+1)
 // is ready once every gate of an earlier layer on bonds p - 1, p, p + 1 has a pass; going through
-// the layers in order, each pass takes the ready gates its tile holds. The matrices go to
-// table and the (q, layer) pairs to meta (host copies); the passes point at dev_table and
-// dev_meta. Returns false when a gate finds no pass or the table is full.
-bool build_run(const ed_model* m, const std::vector<std::pair<int, double>>& run, double dt,
-               std::vector<double2>* table, std::vector<int>* meta, const double2* dev_table,
-               const int* dev_meta, std::vector<GatePass>* out) {
+// the layers in order, each pass takes the ready gates its tile holds. The matrices and codes go to
+// tab; the passes point at its device copy. Returns false when a gate finds no pass or the table is
+// full.
+bool build_run(const ed_model* m, const std::vector<std::pair<int, double>>& run, double dt, GateTable* tab,
+               std::vector<GatePass>* out) {
     const int L = m->L;
     const int F = int(run.size());
     const int T = std::min(L, kGTileBits);
@@ -310,27 +372,46 @@ bool build_run(const ed_model* m, const std::vector<std::pair<int, double>>& run
     }
     for (size_t i = 0; i < geo.size(); ++i) {
         if (gates[i].empty()) continue;
-        if (int(gates[i].size()) > kMaxGates) return false;
-        if (table->size() / 16 + gates[i].size() > size_t(kTableGates)) return false;
+        if (tab->U.size() / 16 + gates[i].size() > size_t(kTableGates)) return false;
         GatePass gp;
         std::memset(&gp, 0, sizeof(GatePass));
         gp.first = geo[i].first;
         gp.c = geo[i].c;
         gp.h0 = geo[i].h0;
         gp.tbits = geo[i].tbits;
-        gp.U = dev_table ? dev_table + table->size() : nullptr;  // null when only counting passes
-        gp.G = dev_meta ? dev_meta + meta->size() : nullptr;
+        gp.U = tab->dev_U ? tab->dev_U + tab->U.size() : nullptr;  // null when only counting passes
+        gp.G = tab->dev_G ? tab->dev_G + tab->G.size() : nullptr;
+        gp.R = tab->dev_R ? tab->dev_R + tab->R.size() : nullptr;
+        std::vector<std::pair<int, int>> local;  // (layer, tile bit q) in order of application
         for (const auto& lp : gates[i]) {
             const int l = lp.first, p = lp.second;
             const int q = geo[i].first ? p : geo[i].c + (p - geo[i].h0);
             if (global_bit(geo[i], q) != p || global_bit(geo[i], q + 1) != p + 1) return false;
+            local.push_back({l, q});
+        }
+        std::vector<int> base(local.size(), 0);  // first register bit of each gate's round
+        if (gp.tbits == kGTileBits) {
+            std::vector<int> order;
+            const size_t r0 = tab->R.size();
+            plan_rounds(local, gp.first ? 0 : kGLow, &order, &base, &tab->R);
+            if (order.size() != local.size() || tab->R.size() > size_t(kTableRounds)) return false;
+            gp.nround = int(tab->R.size() - r0);
+            std::vector<std::pair<int, int>> sorted;
+            for (int g : order) sorted.push_back(local[g]);
+            local = sorted;
+        }
+        for (size_t g = 0; g < local.size(); ++g) {
+            const int l = local[g].first, q = local[g].second, p = global_bit(geo[i], q);
             cplx h[16], A[16], U[16];
             bond_hamiltonian(m, p, h);
             for (int e = 0; e < 16; ++e) A[e] = cplx(0.0, -run[l].second * dt) * h[e];
             expm_complex(4, A, U);
-            for (int e = 0; e < 16; ++e) table->push_back(make_double2(U[e].real(), U[e].imag()));
-            meta->push_back(q);
-            meta->push_back(l);
+            bool cross = true;
+            for (int r = 0; r < 4; ++r)
+                for (int c = 0; c < 4; ++c)
+                    if (c != r && c != 3 - r) cross = cross && U[4 * r + c] == cplx(0.0, 0.0);
+            for (int e = 0; e < 16; ++e) tab->U.push_back(make_double2(U[e].real(), U[e].imag()));
+            tab->G.push_back(gp.tbits < kGTileBits ? q : (1 << (q - base[g])) * (cross ? kCross : 1));
             ++gp.ngate;
         }
         out->push_back(gp);
@@ -341,7 +422,10 @@ bool build_run(const ed_model* m, const std::vector<std::pair<int, double>>& run
 hipError_t run_passes(const std::vector<GatePass>& passes, double2* psi, int L, hipStream_t s) {
     for (const GatePass& gp : passes) {
         const int64_t tiles = int64_t(1) << (L - gp.tbits);
-        hipLaunchKernelGGL(gate_pass, dim3(unsigned(tiles)), dim3(kGThreads), 0, s, psi, gp, gp.U, gp.G);
+        if (gp.tbits == kGTileBits)
+            hipLaunchKernelGGL(gate_pass, dim3(unsigned(tiles)), dim3(kGThreads), 0, s, psi, gp, gp.U, gp.G, gp.R);
+        else  // L < 12: one tile
+            hipLaunchKernelGGL(gate_pass_small, dim3(1), dim3(kSmallThreads), 0, s, psi, gp, gp.U, gp.G);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -359,17 +443,20 @@ std::vector<std::pair<int, double>> step_layers(int order) {
 }
 
 // The passes of one step: the step's layers in runs of kFuse, one set of passes per distinct run
-// (runs), the run of each position (which); the gate matrices go to table and their (q, layer)
-// to meta, the passes point at dev_table and dev_meta.
+// (runs), the run of each position (which), and the table of their gates.
 struct StepPlan {
     std::vector<std::vector<GatePass>> runs;
     std::vector<int> which;
-    std::vector<double2> table;
-    std::vector<int> meta;
+    GateTable table;
 };
 
-ed_status plan_step(const ed_model* m, int order, double dt, const double2* dev_table, const int* dev_meta,
-                    StepPlan* sp) {
+// dev: device memory of the gate table (kGateTableBytes), or null when only counting passes.
+ed_status plan_step(const ed_model* m, int order, double dt, char* dev, StepPlan* sp) {
+    if (dev) {
+        sp->table.dev_U = reinterpret_cast<double2*>(dev);
+        sp->table.dev_G = reinterpret_cast<int*>(dev + size_t(kTableGates) * 16 * sizeof(double2));
+        sp->table.dev_R = sp->table.dev_G + kTableGates;
+    }
     const std::vector<std::pair<int, double>> seq = step_layers(order);
     std::vector<std::vector<std::pair<int, double>>> keys;
     for (size_t i0 = 0; i0 < seq.size(); i0 += kFuse) {
@@ -379,7 +466,7 @@ ed_status plan_step(const ed_model* m, int order, double dt, const double2* dev_
             if (keys[j] == run) found = int(j);
         if (found < 0) {
             std::vector<GatePass> passes;
-            if (!build_run(m, run, dt, &sp->table, &sp->meta, dev_table, dev_meta, &passes))
+            if (!build_run(m, run, dt, &sp->table, &passes))
                 return fail(ED_ERR_UNSUPPORTED, "internal error: no Trotter pass plan for L = " + std::to_string(m->L));
             keys.push_back(run);
             sp->runs.push_back(passes);
@@ -429,14 +516,15 @@ extern "C" ed_status ed_trotter_evolve(const ed_model* model, ed_c64* psi, doubl
     const size_t table_off = core_scratch_bytes() + vec_bytes;  // after what carve hands out
     if (table_off + kGateTableBytes > ws_bytes) return fail(ED_ERR_WORKSPACE, "workspace too small for the gate table");
     char* const tab = static_cast<char*>(ws) + table_off;
-    double2* const dev_table = reinterpret_cast<double2*>(tab);
-    int* const dev_meta = reinterpret_cast<int*>(tab + size_t(kTableGates) * 16 * sizeof(double2));
     StepPlan sp;
-    ED_TRY(plan_step(model, order, dt, dev_table, dev_meta, &sp));
-    if (!sp.table.empty()) {
-        ED_HIP_TRY(hipMemcpyAsync(dev_table, sp.table.data(), sp.table.size() * sizeof(double2),
-                                  hipMemcpyHostToDevice, s));
-        ED_HIP_TRY(hipMemcpyAsync(dev_meta, sp.meta.data(), sp.meta.size() * sizeof(int), hipMemcpyHostToDevice, s));
+    ED_TRY(plan_step(model, order, dt, tab, &sp));
+    if (!sp.table.U.empty()) {
+        auto upload = [&](const void* dst, const void* src, size_t bytes) {
+            return bytes ? hipMemcpyAsync(const_cast<void*>(dst), src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
+        };
+        ED_HIP_TRY(upload(sp.table.dev_U, sp.table.U.data(), sp.table.U.size() * sizeof(double2)));
+        ED_HIP_TRY(upload(sp.table.dev_G, sp.table.G.data(), sp.table.G.size() * sizeof(int)));
+        ED_HIP_TRY(upload(sp.table.dev_R, sp.table.R.data(), sp.table.R.size() * sizeof(int)));
         ED_HIP_TRY(hipStreamSynchronize(s));  // the host tables are locals
     }
     auto record = [&](int step) -> ed_status {
@@ -470,7 +558,7 @@ extern "C" ed_status ed_trotter_passes(const ed_model* model, int order, int* pa
     if (order != 2 && order != 4) return fail(ED_ERR_ARG, "order must be 2 or 4");
     if (model->lr || model->lv_L > 0) return fail(ED_ERR_UNSUPPORTED, "the Trotter layers take site and bond rules only");
     StepPlan sp;
-    ED_TRY(plan_step(model, order, 0.0, nullptr, nullptr, &sp));
+    ED_TRY(plan_step(model, order, 0.0, nullptr, &sp));
     int n = 0;
     for (int r : sp.which) n += int(sp.runs[r].size());
     *passes = n;

@@ -149,3 +149,30 @@ def test_trotter_device_observables():
     _, od = P.trotter_evolve(m, b, 0.05, 4, order=4, energy=True, device_obs=True)
     for k in ("sz", "energy", "norm"):
         assert np.array_equal(oh[k], od[k].cpu().numpy()), k
+
+
+@pytest.mark.parametrize("L", [12, 14, 15, 18, 21])
+def test_trotter_register_rounds(L):
+    """The rounds of a 12-bit tile (four tile bits in registers, gates of several layers per LDS
+    trip): gates that couple only 00 with 11 and 01 with 10 (an XYZ chain in z fields, whose
+    vanishing entries are skipped) and dense ones (with a tilted field), on one tile, on windows that
+    overlap the low tile, and on windows of their own. Same tolerance as above."""
+    print(f"trotter rounds L={L}", flush=True)
+    rng = np.random.default_rng(L)
+    xyz = dict(bond_ops=[E.SXSX, E.SYSY, E.SZSZ], bond_coef=rng.uniform(-1, 1, (3, L - 1)))
+    for name, desc in (("cross", E.ModelDesc(L, site_ops=[E.SZ], site_coef=rng.uniform(-1, 1, (1, L)), **xyz)),
+                       ("dense", E.ModelDesc(L, site_ops=[E.SX, E.SY], site_coef=rng.uniform(-1, 1, (2, L)), **xyz))):
+        psi0 = E.random_state(L, 3)
+        for order in (2, 4):
+            ref, _ = OT.evolve(desc, psi0, 0.2, 1, order)
+            psi = to_dev(psi0)
+            P.trotter_evolve(P.Model(desc), psi, 0.2, 1, order=order, observe=False)
+            err = np.linalg.norm(psi.cpu().numpy() - ref) / np.linalg.norm(ref)
+            assert err < 1e-12, (L, name, order, err)
+
+
+def test_trotter_table_holds_every_length():
+    """The gate table and its rounds fit for every chain length (the plan of each order is made)."""
+    for L in range(2, 31):
+        m = P.Model(E.tfim(L, 0.5))
+        assert P.trotter_passes(m, 4) >= 3 and P.trotter_passes(m, 2) >= 1, L
