@@ -178,3 +178,31 @@ def test_trajectory_ensemble_vs_liouville_L8():
     _, obs, _ = P.krylov_evolve(m, rho, dt * stride, steps // stride, m_max=30, tol=1e-12, hermitian=False)
     assert mean.shape == obs["sz"].shape
     assert np.all(np.abs(mean - obs["sz"]) < 4 * se + 1e-3), np.abs(mean - obs["sz"]).max()
+
+
+@pytest.mark.parametrize("L", [3, 4, 5, 7, 8, 9, 10, 11])
+def test_jump_terms_by_group(L):
+    """Only the jump sandwiches (H = 0): every entry's partners over all groups and cells, on both
+    sides of the sizes where the kernel changes (L = 4 and L = 10), for a lowering, a dephasing and a
+    dense complex jump on every site, against the same sums by index arithmetic. Each entry adds
+    at most 4 terms per site and the decay: 1e-14 of the largest entry covers the rounding."""
+    rng = np.random.default_rng(L)
+    J = [E.SMINUS, E.SZ, rng.standard_normal((2, 2)) + 1j * rng.standard_normal((2, 2))]
+    rates = rng.uniform(0.1, 1.0, (3, L))
+    zero = E.ModelDesc(L, site_ops=np.zeros((0, 2, 2)), site_coef=np.zeros((0, L)), bond_ops=[np.zeros((4, 4))],
+                       bond_coef=np.zeros((1, L - 1)))
+    D = 1 << L
+    x = E.random_state(2 * L, 5, normalise=False)
+    got = P.apply_H(P.Liouville(zero, J, rates), torch.from_numpy(x).to(DEV)).cpu().numpy()
+    ref = np.zeros(D * D, np.complex128)
+    for z, A in enumerate(J):
+        JJ = A.conj().T @ A
+        for k in range(L):
+            g = rates[z, k]
+            row = x.reshape(1 << k, 2, -1)
+            ref += -0.5j * g * np.einsum("ab,ibj->iaj", JJ, row).reshape(-1)
+            col = x.reshape(D << k, 2, -1)
+            ref += -0.5j * g * np.einsum("ab,ibj->iaj", JJ.conj(), col).reshape(-1)
+            both = x.reshape(1 << k, 2, 1 << (L - 1), 2, -1)
+            ref += 1j * g * np.einsum("ab,cd,ibjdk->iajck", A, A.conj(), both).reshape(-1)
+    assert np.max(np.abs(got - ref)) < 1e-14 * np.max(np.abs(ref)) * 4 * L
