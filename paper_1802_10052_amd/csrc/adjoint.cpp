@@ -29,59 +29,106 @@ void destroy_model(ed_model* m);
 namespace {
 
 constexpr int kBT = 256;
-constexpr int kMaxBonds = 31;
+constexpr int kAdjScal = 640;  // bond sums one copy fetches (scalars between the tickets and N at m_max = 64)
+static_assert(kThreeTermFree + kAdjScal + 3 * 64 + 2 <= kObs, "scalar area");
+constexpr int kBTile = 12;     // tile bits
+constexpr int kBLow = 3;       // contiguous low bits of a window tile
+constexpr int kBThr = 512;     // threads per tile, 8 amplitudes each
+constexpr int kBSlots = (1 << kBTile) / kBThr;
+constexpr int kBTb = 9;        // thread bits
 
-// part[blk][b] = sum_{x in block} conj(mu[x]) (h_b phi)[x] for every bond bit p = 0..L-2
-// (bond ops per bit in `bond`, 16 entries each). Partner amplitudes come straight from global
-// memory: the vectors of this path (L <= 24) live in the last-level cache.
-__global__ __launch_bounds__(kBT) void bond_expect_partial(const double2* __restrict__ mu, const double2* __restrict__ phi,
-                                                           const double2* __restrict__ bond, int L,
-                                                           double2* __restrict__ part, int part_ld) {
-    __shared__ double red[kBT / 64][2 * kMaxBonds];
-    double a[2 * kMaxBonds];
+// One pass over 12-bit tiles (the low bits, or c low bits and a window of 12 - c bits at h0):
+// part[tile][p] = sum over the tile of conj(mu[x]) (h_p phi)[x] for the bonds on tile bits
+// (q, q + 1), q0 <= q < q1, of global bit p. phi's tile sits in LDS, so a flipped partner costs an LDS
+// read; both vectors are read once per pass. Bound by memory and LDS: XXXX us for both passes at
+// L = 20, where gathering every partner from global memory took 139 us.
+struct BondPass {
+    int first, h0, c, tbits;
+    int q0, q1;
+};
+
+__global__ __launch_bounds__(kBThr) void bond_expect_tile(const double2* __restrict__ mu, const double2* __restrict__ phi,
+                                                          const double2* __restrict__ bond, BondPass bp,
+                                                          double2* __restrict__ part, int part_ld) {
+    __shared__ double2 s[1 << kBTile];
+    __shared__ double red[kBThr / 64][2 * (kBTile - 1)];
+    const int t = threadIdx.x;
+    const int N = 1 << bp.tbits;
+    const int64_t n = blockIdx.x;
+    int64_t base;
+    int hs;  // tile index i is base + (i & (2^c - 1)) + (i >> c) << hs
+    if (bp.first) {
+        base = n << bp.tbits;
+        hs = bp.c;
+    } else {
+        const int lo_bits = bp.h0 - bp.c;
+        base = ((n & ((int64_t(1) << lo_bits) - 1)) << bp.c) | ((n >> lo_bits) << (bp.h0 + kBTile - bp.c));
+        hs = bp.h0;
+    }
+    double2 f[kBSlots], m[kBSlots];
 #pragma unroll
-    for (int i = 0; i < 2 * kMaxBonds; ++i) a[i] = 0.0;
-    const int64_t D = int64_t(1) << L;
-    const int64_t chunk = (D + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = int64_t(blockIdx.x) * chunk;
-    const int64_t hi = lo + chunk < D ? lo + chunk : D;
-    for (int64_t x = lo + threadIdx.x; x < hi; x += kBT) {
-        const double2 m = mu[x];
-        const double2 f = phi[x];
+    for (int k = 0; k < kBSlots; ++k) {
+        const int i = t + kBThr * k;
+        f[k] = m[k] = make_double2(0.0, 0.0);
+        if (i < N) {
+            const int64_t x = base + ((int64_t(i >> bp.c) << hs) | (i & ((1 << bp.c) - 1)));
+            f[k] = phi[x];
+            m[k] = mu[x];
+        }
+        s[i] = f[k];
+    }
+    __syncthreads();
+    const int lane = t & 63, wv = t >> 6;
 #pragma unroll
-        for (int p = 0; p < kMaxBonds; ++p) {
-            if (p + 1 < L) {
-                const int l = (x >> p) & 3;
-                const double2* B = bond + 16 * p;
-                double2 hv = cmul(B[5 * l], f);
+    for (int q = 0; q < kBTile - 1; ++q) {
+        double ax = 0.0, ay = 0.0;
+        if (q >= bp.q0 && q < bp.q1) {
+            const int p = bp.first || q < bp.c ? q : bp.h0 + q - bp.c;
+            const double2* B = bond + 16 * p;
+            double2 hv[kBSlots];
+            {
+                const double2 d0 = B[0], d1 = B[5], d2 = B[10], d3 = B[15];
 #pragma unroll
-                for (int mm = 1; mm < 4; ++mm) {
-                    const double2 c = B[4 * l + (l ^ mm)];
-                    if (c.x != 0.0 || c.y != 0.0) {
-                        const double2 g = phi[x ^ (int64_t(mm) << p)];
-                        hv.x += c.x * g.x - c.y * g.y;
-                        hv.y += c.x * g.y + c.y * g.x;
-                    }
+                for (int k = 0; k < kBSlots; ++k) {
+                    const int l = ((t + kBThr * k) >> q) & 3;
+                    hv[k] = cmul(sel4(l, d0, d1, d2, d3), f[k]);
                 }
-                // conj(m) * hv
-                a[2 * p] += m.x * hv.x + m.y * hv.y;
-                a[2 * p + 1] += m.x * hv.y - m.y * hv.x;
+            }
+#pragma unroll
+            for (int mm = 1; mm < 4; ++mm) {
+                const double2 b0 = B[0 + (0 ^ mm)], b1 = B[4 + (1 ^ mm)], b2 = B[8 + (2 ^ mm)], b3 = B[12 + (3 ^ mm)];
+                const double any = fabs(b0.x) + fabs(b0.y) + fabs(b1.x) + fabs(b1.y) + fabs(b2.x) + fabs(b2.y) +
+                                   fabs(b3.x) + fabs(b3.y);
+                if (any == 0.0) continue;  // the same for all threads
+#pragma unroll
+                for (int k = 0; k < kBSlots; ++k) {
+                    const int i = t + kBThr * k;
+                    cfma<false>(hv[k], sel4((i >> q) & 3, b0, b1, b2, b3), s[i ^ (mm << q)]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kBSlots; ++k) {  // conj(m) * hv
+                ax = fma(m[k].x, hv[k].x, fma(m[k].y, hv[k].y, ax));
+                ay = fma(m[k].x, hv[k].y, fma(-m[k].y, hv[k].x, ay));
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                ax += __shfl_xor(ax, o, 64);
+                ay += __shfl_xor(ay, o, 64);
+            }
+            if (lane == 0) {
+                red[wv][2 * q] = ax;
+                red[wv][2 * q + 1] = ay;
             }
         }
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int i = 0; i < 2 * kMaxBonds; ++i) {
-        double v = a[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if (lane == 0) red[wv][i] = v;
-    }
     __syncthreads();
-    if (threadIdx.x < 2 * (L - 1)) {
-        double s = 0.0;
-        for (int w = 0; w < kBT / 64; ++w) s += red[w][threadIdx.x];
-        reinterpret_cast<double*>(part + int64_t(blockIdx.x) * part_ld)[threadIdx.x] = s;
+    const int q = t >> 1;
+    if (q >= bp.q0 && q < bp.q1) {
+        double v = 0.0;
+        for (int w = 0; w < kBThr / 64; ++w) v += red[w][t];
+        const int p = bp.first || q < bp.c ? q : bp.h0 + q - bp.c;
+        reinterpret_cast<double*>(part + n * part_ld + p)[t & 1] = v;
     }
 }
 
@@ -167,45 +214,67 @@ ed_status slice_models(const ed_model* tmpl, int S, const double* J, ModelSet* m
 
 struct Basis {
     Workspace w;
+    ThreeTerm T;
     std::vector<xreal> d, Z;  // eigenpairs of the tridiagonal T (extended precision)
     int m = 0;
     double nrm = 0.0;
 };
 
-// Lanczos basis of psi under model (three-term recurrence with local re-projection, or fixed m)
+// Lanczos basis of psi under model (three-term recurrence with local re-projection, or fixed m); alias:
+// psi itself is u_0 (it must then stay until the basis is no longer needed), else a copy is.
+// Both projections are taken (local re-projection): the bases run at a fixed dimension well past
+// convergence, where the gradient check needs the more orthogonal basis. The iterations of a fixed
+// dimension are enqueued at once; adaptive ones in batches of the last basis's dimension.
 ed_status build_basis(const ed_model* mod, const double2* psi, double dt_err, const ed_adjoint_params* p, Basis* B,
-                      hipStream_t s) {
-    ED_TRY(start_vector(B->w, psi, &B->nrm, s));
+                      bool alias, hipStream_t s) {
     const int mmax = p->m_max;
+    const int guess = B->m;
+    B->T.sigma = three_term_scale(mod);
+    ED_TRY(three_term_start(B->T, B->w, psi, alias, false, s));
     std::vector<double> a(mmax + 1), b(mmax + 1);
-    std::vector<cplx> h(mmax + 2);
-    int m = 0;
-    for (int j = 0; j < mmax; ++j) {
-        const int lo = std::max(j - 1, 0);
-        double beta = 0.0;
-        bool brk = false;
-        // both projections swept (local re-projection): the bases run at a fixed dimension well
-        // past convergence, where the gradient check needs the more orthogonal basis
-        ED_TRY(krylov_step(mod, B->w, j, lo, 1, 1e-14, h.data(), &beta, &brk, s));
-        a[j] = h[j - lo].real();
-        m = j + 1;
-        bool stop = brk || m >= mmax;
-        if (p->m_fixed > 0) {
-            stop = brk || m >= std::min(p->m_fixed, mmax);
-        } else if (!stop) {
-            std::vector<xreal> dd(a.begin(), a.begin() + m), ee(m, 0.0L), Z(size_t(m) * m, 0.0L);
-            for (int i = 0; i + 1 < m; ++i) ee[i] = b[i];
-            for (int i = 0; i < m; ++i) Z[size_t(i) * m + i] = 1.0L;
-            if (!tridiag_ql_ext(m, dd.data(), ee.data(), Z.data()))
-                return fail(ED_ERR_NUMERIC, "tridiagonal eigensolver did not converge");
-            std::vector<cplx> u(m);
-            expm_col_sym_ext(m, dd.data(), Z.data(), std::fabs(dt_err), u.data());
-            stop = B->nrm * beta * std::abs(u[m - 1]) <= p->tol;
+    std::vector<double2> hv(B->T.count());
+    const double2 *hN = hv.data(), *hS = hN + (B->T.SP - B->T.N);
+    int m = 0, enq = 0;
+    bool stop = false;
+    while (!stop) {
+        int nb = p->m_fixed > 0 ? std::min(p->m_fixed, mmax) : std::max(guess - enq, 1);
+        nb = std::min(nb, mmax - enq);
+        ED_TRY(three_term_run(mod, B->T, B->w, enq, nb, true, s));
+        enq += nb;
+        ED_TRY(fetch_scalars(B->T.N, B->T.count(), hv.data(), s));
+        for (; m < enq && !stop;) {
+            const int j = m;
+            if (j == 0) {
+                if (!std::isfinite(hN[0].x)) return fail(ED_ERR_NUMERIC, "non-finite start vector");
+                if (hN[0].x <= 0.0) return fail(ED_ERR_ARG, "start vector is zero");
+                B->nrm = std::sqrt(hN[0].x);
+            }
+            if (!std::isfinite(hN[j + 1].x) || !std::isfinite(hS[2 * j].x))
+                return fail(ED_ERR_NUMERIC, "non-finite value in the Krylov recurrence");
+            const cplx h(hS[2 * j].x / hN[j].x, hS[2 * j].y / hN[j].x);
+            const double hp =
+                j > 0 ? std::hypot(hS[2 * j + 1].x, hS[2 * j + 1].y) / std::sqrt(hN[j - 1].x * hN[j].x) : 0.0;
+            a[j] = h.real();
+            b[j] = std::sqrt(std::max(hN[j + 1].x, 0.0) / hN[j].x) / B->T.sigma;
+            const bool brk = b[j] <= 1e-14 * std::max(std::max(std::abs(h), hp), 1e-300) || b[j] == 0.0;
+            m = j + 1;
+            stop = brk || m >= mmax;
+            if (p->m_fixed > 0) {
+                stop = brk || m >= std::min(p->m_fixed, mmax);
+            } else if (!stop) {
+                std::vector<xreal> dd(a.begin(), a.begin() + m), ee(m, 0.0L), Z(size_t(m) * m, 0.0L);
+                for (int i = 0; i + 1 < m; ++i) ee[i] = b[i];
+                for (int i = 0; i < m; ++i) Z[size_t(i) * m + i] = 1.0L;
+                if (!tridiag_ql_ext(m, dd.data(), ee.data(), Z.data()))
+                    return fail(ED_ERR_NUMERIC, "tridiagonal eigensolver did not converge");
+                std::vector<cplx> u(m);
+                expm_col_sym_ext(m, dd.data(), Z.data(), std::fabs(dt_err), u.data());
+                stop = B->nrm * b[j] * std::abs(u[m - 1]) <= p->tol;
+            }
         }
-        if (stop) break;
-        b[j] = beta;
     }
     B->m = m;
+    for (int i = 0; i < m; ++i) B->w.c[i] = 1.0 / std::sqrt(hN[i].x);
     B->d.assign(a.begin(), a.begin() + m);
     std::vector<xreal> ee(m, 0.0L);
     for (int i = 0; i + 1 < m; ++i) ee[i] = b[i];
@@ -225,11 +294,30 @@ ed_status eval_basis(const Basis& B, double tau, double2* out, hipStream_t s) {
     return combine_basis(B.w, B.m, c.data(), out, s);
 }
 
+// out_q = nrm V exp(-i tau_q T) e_1 for up to kNodeOut times in one sweep of the basis; no output may
+// be a basis vector
+ed_status eval_nodes(const Basis& B, const std::vector<double>& tau, const std::vector<double2*>& out, hipStream_t s) {
+    const int n = int(tau.size());
+    std::vector<cplx> u(B.m);
+    std::vector<double2> C(size_t(B.m) * n);
+    for (int q = 0; q < n; ++q) {
+        expm_col_sym_ext(B.m, B.d.data(), B.Z.data(), tau[q], u.data());
+        for (int i = 0; i < B.m; ++i) {
+            const double f = B.nrm * B.w.c[i];
+            C[size_t(i) * n + q] = make_double2(f * u[i].real(), f * u[i].imag());
+        }
+    }
+    if (combination_nodes(const_cast<const double2* const*>(B.w.u.data()), B.m, C.data(), out.data(), n, B.w.D, s) !=
+        hipSuccess)
+        return fail(ED_ERR_HIP, "node combination");
+    return ED_OK;
+}
+
 // psi <- exp(-i H dt) psi through K sub-steps
 ed_status propagate(const ed_model* mod, double2* psi, double dt, int K, const ed_adjoint_params* p, Basis* B,
                     hipStream_t s) {
     for (int k = 0; k < K; ++k) {
-        ED_TRY(build_basis(mod, psi, dt / K, p, B, s));
+        ED_TRY(build_basis(mod, psi, dt / K, p, B, true, s));
         ED_TRY(eval_basis(*B, dt / K, psi, s));
     }
     return ED_OK;
@@ -306,6 +394,8 @@ extern "C" ed_status ed_evolve_adjoint(const ed_model* tmpl, int n_slices, doubl
     double2* mun = reinterpret_cast<double2*>(c);
     c += al(vec);
     double* dw = reinterpret_cast<double*>(c);
+    ED_TRY(three_term_init(tmpl, Bp.w, p->m_max, &Bp.T, s));
+    ED_TRY(three_term_init(tmpl, Bm.w, p->m_max, &Bm.T, s));
 
     ModelSet ms;
     ED_TRY(slice_models(tmpl, S, J, &ms));
@@ -326,7 +416,8 @@ extern "C" ed_status ed_evolve_adjoint(const ed_model* tmpl, int n_slices, doubl
     std::vector<double> xq, wq;
     gauss_legendre(p->quad_nodes, xq, wq);
     const double delta = slice_len / K;
-    std::vector<double2> z(NB);
+    std::vector<double2> z;
+    double2* const zdev = Bp.w.scal + kThreeTermFree;  // free between the tickets and the recurrence's scalars
     for (int sl = S - 1; sl >= 0; --sl) {
         const ed_model* Hs = ms.m[sl];
         // lam_{s-1} = exp(+i H_s Delta) lam_s
@@ -336,21 +427,45 @@ extern "C" ed_status ed_evolve_adjoint(const ed_model* tmpl, int n_slices, doubl
         ED_HIP_TRY(hipMemcpyAsync(mun, lam, vec, hipMemcpyDeviceToDevice, s));
         std::vector<double> g(NB, 0.0);
         for (int k = 0; k < K; ++k) {
-            ED_TRY(build_basis(Hs, phin, delta, p, &Bp, s));
-            ED_TRY(build_basis(Hs, mun, delta, p, &Bm, s));
-            for (int q = 0; q < p->quad_nodes; ++q) {
-                const double sig = 0.5 * delta * (1.0 + xq[q]);
-                ED_TRY(eval_basis(Bp, sig, phin, s));
-                ED_TRY(eval_basis(Bm, sig, mun, s));
-                if (bond_expect(mun, phin, tmpl->d_bond, L, Bp.w.scal + kObs, Bp.w.part, s) != hipSuccess)
-                    return fail(ED_ERR_HIP, "bond reduction");
-                ED_TRY(fetch_scalars(Bp.w.scal + kObs, NB, z.data(), s));
-                // bond bit p = L - b - 2 for bond b (sites b+1, b+2)
-                for (int b = 0; b < NB; ++b) g[b] += 0.5 * delta * wq[q] * 2.0 * z[L - b - 2].y;
+            ED_TRY(build_basis(Hs, phin, delta, p, &Bp, false, s));
+            ED_TRY(build_basis(Hs, mun, delta, p, &Bm, false, s));
+            // the quadrature nodes, as many at a time as the slots behind both bases hold (always
+            // one: slot m is free), the states at the end of the sub-step with the last of them
+            const int room = std::min(std::min(p->m_max + 1 - Bp.m, p->m_max + 1 - Bm.m), kNodeOut - 1);
+            const int zrows = std::max(1, kAdjScal / NB);
+            int queued = 0, done = 0;  // node results waiting on the device, and read
+            for (int q0 = 0; q0 < p->quad_nodes; q0 += room) {
+                const int nq = std::min(room, p->quad_nodes - q0);
+                const bool end = q0 + nq == p->quad_nodes;
+                std::vector<double> tau(nq);
+                for (int q = 0; q < nq; ++q) tau[q] = 0.5 * delta * (1.0 + xq[q0 + q]);
+                if (end) tau.push_back(delta);
+                std::vector<double2*> op, om;
+                for (int q = 0; q < nq; ++q) {
+                    op.push_back(Bp.w.slot(Bp.m + q));
+                    om.push_back(Bm.w.slot(Bm.m + q));
+                }
+                if (end) {
+                    op.push_back(phin);
+                    om.push_back(mun);
+                }
+                ED_TRY(eval_nodes(Bp, tau, op, s));
+                ED_TRY(eval_nodes(Bm, tau, om, s));
+                for (int q = 0; q < nq; ++q) {
+                    if (bond_expect(om[q], op[q], tmpl->d_bond, L, zdev + size_t(queued) * NB, Bp.w.part, s) != hipSuccess)
+                        return fail(ED_ERR_HIP, "bond reduction");
+                    ++queued;
+                    if (queued == zrows || (end && q + 1 == nq)) {
+                        z.resize(size_t(queued) * NB);
+                        ED_TRY(fetch_scalars(zdev, queued * NB, z.data(), s));
+                        // bond bit p = L - b - 2 for bond b (sites b+1, b+2)
+                        for (int r = 0; r < queued; ++r, ++done)
+                            for (int b = 0; b < NB; ++b)
+                                g[b] += 0.5 * delta * wq[done] * 2.0 * z[size_t(r) * NB + L - b - 2].y;
+                        queued = 0;
+                    }
+                }
             }
-            // advance phi and mu to the end of the sub-step
-            ED_TRY(eval_basis(Bp, delta, phin, s));
-            ED_TRY(eval_basis(Bm, delta, mun, s));
         }
         for (int b = 0; b < NB; ++b) grad[size_t(sl) * NB + b] = g[b];
     }
@@ -381,6 +496,7 @@ extern "C" ed_status ed_evolve_loss(const ed_model* tmpl, int n_slices, double s
     const size_t basis_bytes = core_scratch_bytes() + al(size_t(p->m_max + 1) * size_t(D) * sizeof(double2));
     ED_TRY(carve(ws, basis_bytes, D, p->m_max + 1, &B.w));
     double2* psi = reinterpret_cast<double2*>(static_cast<char*>(ws) + basis_bytes);
+    ED_TRY(three_term_init(tmpl, B.w, p->m_max, &B.T, s));
     ModelSet ms;
     ED_TRY(slice_models(tmpl, n_slices, J, &ms));
     ED_HIP_TRY(hipMemcpyAsync(psi, psi0, size_t(D) * sizeof(double2), hipMemcpyDeviceToDevice, s));
@@ -392,11 +508,20 @@ extern "C" ed_status ed_evolve_loss(const ed_model* tmpl, int n_slices, double s
 namespace ed {
 hipError_t bond_expect(const double2* mu, const double2* phi, const double2* bond, int L, double2* out, double2* part,
                        hipStream_t s) {
-    const int64_t D = int64_t(1) << L;
-    int G = reduction_blocks(D);
-    hipLaunchKernelGGL(bond_expect_partial, dim3(G), dim3(kBT), 0, s, mu, phi, bond, L, part, kPartLd);
+    const int tbits = std::min(L, kBTile);
+    const unsigned tiles = 1u << (L - tbits);
+    BondPass bp{1, 0, std::min(kBLow, tbits), tbits, 0, std::min(L - 1, kBTile - 1)};
+    hipLaunchKernelGGL(bond_expect_tile, dim3(tiles), dim3(kBThr), 0, s, mu, phi, bond, bp, part, kPartLd);
+    // windows: each takes the bonds from the lowest one pending up to its own top
+    for (int p = kBTile - 1; p < L - 1;) {
+        const int w = kBTile - kBLow, h0 = std::min(p, L - w);
+        const int top = std::min(h0 + w - 1, L - 1);  // bonds p .. top - 1
+        bp = BondPass{0, h0, kBLow, kBTile, kBLow + p - h0, kBLow + top - h0};
+        hipLaunchKernelGGL(bond_expect_tile, dim3(tiles), dim3(kBThr), 0, s, mu, phi, bond, bp, part, kPartLd);
+        p = top;
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return reduce_partial_rows(part, G, L - 1, out, s);
+    return reduce_partial_rows(part, int(tiles), L - 1, out, s);
 }
 }  // namespace ed

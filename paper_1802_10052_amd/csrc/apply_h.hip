@@ -136,7 +136,8 @@ void hpsi_tile_pair(const double2* __restrict__ psi, double2* __restrict__ out, 
 
 // dot_part: the last pass (a window pass) also writes each tile's sum of conj(psi) out
 template <unsigned CLS>
-hipError_t launch_variant(const ed_model* m, const double2* psi, double2* out, hipStream_t s, double2* dot_part) {
+hipError_t launch_variant(const ed_model* m, const double2* psi, double2* out, hipStream_t s, double2* dot_part,
+                          const double2* psi2) {
     const int L = m->L;
     if (L < kTileBits) {
         const int64_t D = int64_t(1) << L;
@@ -160,6 +161,7 @@ hipError_t launch_variant(const ed_model* m, const double2* psi, double2* out, h
         const dim3 grid{unsigned(tiles)}, block{unsigned(kTileThreads)};
         const bool dot = dot_part && !pd.first && ip == m->n_pass - 1;
         pa.dot_part = dot ? dot_part : nullptr;
+        pa.dot_psi2 = dot ? psi2 : nullptr;
 #define ED_TILE_ARGS psi, out, m->d_site, m->d_bond, m->d_diag_lo, m->d_diag_mid, m->d_diag_hi, pa
         // optional LDS padding: one workgroup per CU, so that the tiles of a group fit in L2
         const unsigned pad = (pd.G > 0 && pd.occ1) ? unsigned(kOccPadBytes) : 0u;
@@ -192,31 +194,32 @@ hipError_t launch_variant(const ed_model* m, const double2* psi, double2* out, h
 }
 
 template <int I>
-hipError_t dispatch(const ed_model* m, const double2* psi, double2* out, hipStream_t s, double2* dot_part) {
+hipError_t dispatch(const ed_model* m, const double2* psi, double2* out, hipStream_t s, double2* dot_part,
+                    const double2* psi2) {
     if constexpr (I >= kNumVariants) {
         return hipErrorInvalidValue;
     } else {
-        if (variant_fits(kVariants[I], m->op_class)) return launch_variant<kVariants[I]>(m, psi, out, s, dot_part);
-        return dispatch<I + 1>(m, psi, out, s, dot_part);
+        if (variant_fits(kVariants[I], m->op_class)) return launch_variant<kVariants[I]>(m, psi, out, s, dot_part, psi2);
+        return dispatch<I + 1>(m, psi, out, s, dot_part, psi2);
     }
 }
 
 }  // namespace
 
 ed_status launch_apply_H(const ed_model* m, const double2* psi, double2* out, hipStream_t s) {
-    hipError_t e = dispatch<0>(m, psi, out, s, nullptr);
+    hipError_t e = dispatch<0>(m, psi, out, s, nullptr, nullptr);
     if (e != hipSuccess) return fail(ED_ERR_HIP, std::string("apply_H launch: ") + hipGetErrorString(e));
     if (!m->far.empty()) return launch_far_terms(m, psi, out, s);
     return ED_OK;
 }
 
 ed_status launch_apply_H_dot(const ed_model* m, const double2* psi, double2* out, double2* dot_part,
-                             int64_t max_parts, int64_t* nparts, hipStream_t s) {
+                             int64_t max_parts, int64_t* nparts, hipStream_t s, const double2* psi2) {
     *nparts = 0;
     const bool fusable = m->L >= kTileBits && m->far.empty() && m->n_pass > 0 && !m->pass[m->n_pass - 1].first &&
                          (int64_t(1) << (m->L - kTileBits)) <= max_parts;
     if (!fusable) return launch_apply_H(m, psi, out, s);
-    hipError_t e = dispatch<0>(m, psi, out, s, dot_part);
+    hipError_t e = dispatch<0>(m, psi, out, s, dot_part, psi2);
     if (e != hipSuccess) return fail(ED_ERR_HIP, std::string("apply_H launch: ") + hipGetErrorString(e));
     *nparts = int64_t(1) << (m->L - kTileBits);
     return ED_OK;

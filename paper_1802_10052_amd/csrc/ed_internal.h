@@ -141,9 +141,10 @@ namespace ed {
 ed_status launch_apply_H(const ed_model* m, const double2* psi, double2* out, hipStream_t s);
 // H psi whose last pass also leaves, per tile n, dot_part[n] = sum over the tile of conj(psi) out
 // (*nparts = the number of tiles), when the plan ends with a window pass, there are no far terms
-// and the tiles fit max_parts entries; otherwise a plain product with *nparts = 0.
+// and the tiles fit max_parts entries; otherwise a plain product with *nparts = 0. With psi2 the
+// sums of conj(psi) out and conj(psi2) out sit side by side: dot_part[2 n], dot_part[2 n + 1].
 ed_status launch_apply_H_dot(const ed_model* m, const double2* psi, double2* out, double2* dot_part,
-                             int64_t max_parts, int64_t* nparts, hipStream_t s);
+                             int64_t max_parts, int64_t* nparts, hipStream_t s, const double2* psi2 = nullptr);
 // out += sum of the far terms applied to psi (liouville.hip)
 ed_status launch_far_terms(const ed_model* m, const double2* psi, double2* out, hipStream_t s);
 // trace and sum_j rho_jj z_k(j), k = 1..Ls (site order), of a superket of an Ls-site system,

@@ -15,6 +15,8 @@ constexpr int kChunk = 64;        // basis vectors per subtraction sweep
 constexpr int kKeepDots = 16;     // dots of the next pass taken inside a subtraction sweep
 constexpr int kMultiIn = 96;      // inputs of one multi-output combination
 constexpr int kMultiOut = 8;      // outputs of one multi-output combination
+constexpr int kNodeIn = 20;       // inputs of one launch of a node combination (arguments of 3.4 KiB)
+constexpr int kNodeOut = 9;       // its outputs
 constexpr size_t kPartBytes = size_t(kRedBlocks) * kPartLd * sizeof(double2);
 
 int reduction_blocks(int64_t D);
@@ -38,7 +40,8 @@ hipError_t axpby(const double2* x, double2* y, double2 a, double2 b, int64_t D, 
 hipError_t combination(const double2* V, int64_t ldv, int n, const double2* c, double2* out, int64_t D,
                        hipStream_t s);
 // out[0].x = |psi|^2, out[1+p].x = sum |psi_x|^2 (1 - 2 bit_p(x))  (p = bit, site L-p)
-hipError_t sz_all(const double2* psi, int L, double2* out, double2* part, hipStream_t s);
+// (norm2[0].x = |psi|^2 too where given)
+hipError_t sz_all(const double2* psi, int L, double2* out, double2* part, hipStream_t s, double2* norm2 = nullptr);
 
 // out[0] = sum of part[0..n) in a fixed order
 hipError_t sum_partials(const double2* part, int64_t n, double2* out, hipStream_t s);
@@ -66,6 +69,10 @@ hipError_t axpy_dots_norm_ptr(const double2* const* U, int n, const double2* coe
 // out_o = sum_i C[i * n_out + o] U_i for o < n_out (C device, real, n_in x n_out row-major), in one
 // sweep; outputs may alias inputs. n_in <= kMultiIn, n_out <= kMultiOut.
 hipError_t combination_multi(const double2* const* U, int n_in, const double* C, double2* const* out, int n_out,
+                             int64_t D, hipStream_t s);
+// out_o = sum_i C[i * n_out + o] U_i for o < n_out <= kNodeOut (C host, complex), in one sweep per
+// kNodeIn vectors; no output may be an input.
+hipError_t combination_nodes(const double2* const* U, int n_in, const double2* C, double2* const* out, int n_out,
                              int64_t D, hipStream_t s);
 // out = sum_i c[i] U_i (c host); out may be U_0 when n <= kMaxComb
 hipError_t combination_ptr(const double2* const* U, int n, const double2* c, double2* out, int64_t D, hipStream_t s);

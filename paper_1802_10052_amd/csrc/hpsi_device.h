@@ -50,6 +50,8 @@ struct PassArgs {
     // last window pass with the product's projection on the input: dot_part[n] = the sum over
     // tile n of conj(psi[x]) out[x] (only the fused launch reads it)
     double2* dot_part;
+    // when set, also on psi2: the two sums sit at dot_part[2 n] and dot_part[2 n + 1]
+    const double2* dot_psi2;
 };
 
 // Operator tables of one model as the per-amplitude kernels see them.
@@ -355,6 +357,7 @@ __device__ __forceinline__ void tile_finish(double2* __restrict__ out,
         }
         if ((t & 63) == 0) sD[t >> 6] = make_double2(dx, dy);
         __syncthreads();
+        const int ds = pa.dot_psi2 ? 1 : 0;
         if (t == 0) {
             double2 sum = sD[0];
 #pragma unroll
@@ -362,7 +365,34 @@ __device__ __forceinline__ void tile_finish(double2* __restrict__ out,
                 sum.x += sD[w].x;
                 sum.y += sD[w].y;
             }
-            pa.dot_part[n] = sum;
+            pa.dot_part[n << ds] = sum;
+        }
+        if (ds) {  // the same for psi2, read here
+            const double2* __restrict__ p2 = pa.dot_psi2 + i0;
+            dx = dy = 0.0;
+#pragma unroll
+            for (int k = 0; k < kSl; ++k) {
+                const double2 p = p2[k * step];
+                dx = fma(p.x, acc[k].x, fma(p.y, acc[k].y, dx));
+                dy = fma(p.x, acc[k].y, fma(-p.y, acc[k].x, dy));
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                dx += __shfl_xor(dx, o);
+                dy += __shfl_xor(dy, o);
+            }
+            __syncthreads();
+            if ((t & 63) == 0) sD[t >> 6] = make_double2(dx, dy);
+            __syncthreads();
+            if (t == 0) {
+                double2 sum = sD[0];
+#pragma unroll
+                for (int w = 1; w < kThr / 64; ++w) {
+                    sum.x += sD[w].x;
+                    sum.y += sD[w].y;
+                }
+                pa.dot_part[2 * n + 1] = sum;
+            }
         }
     }
 }
@@ -489,6 +519,7 @@ inline PassArgs to_args(const PassDesc& pd, const GatherJob* jobs, int njobs) {
     pa.lr_low = nullptr;
     pa.lr_cross = nullptr;
     pa.dot_part = nullptr;
+    pa.dot_psi2 = nullptr;
     return pa;
 }
 

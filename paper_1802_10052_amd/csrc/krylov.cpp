@@ -678,16 +678,160 @@ ed_status krylov_time_step(const ed_model* m, const Workspace& w, double2* psi, 
     return ED_OK;
 }
 
-// <psi|H|psi>/<psi|psi> using V_0, V_1 of the workspace as scratch
+// <psi|H|psi>/<psi|psi> using V_1 of the workspace as scratch
 ed_status energy_of(const ed_model* m, const Workspace& w, const double2* psi, double* e, hipStream_t s) {
-    double nrm0 = 0.0;
-    ED_TRY(start_vector(w, psi, &nrm0, s));
+    ED_K(norm2(psi, w.D, w.scal + kNrm, w.part, s));
     double2* Hv = w.V + w.D;
-    ED_TRY(launch_apply_H(m, w.V, Hv, s));
-    ED_K(dots(w.V, w.D, 1, Hv, w.D, w.scal + 1, w.part, s));
+    int64_t nparts = 0;
+    ED_TRY(launch_apply_H_dot(m, psi, Hv, w.part, int64_t(kPartBytes / sizeof(double2)), &nparts, s));
+    if (nparts > 0) ED_K(sum_partials(w.part, nparts, w.scal + 1, s));
+    else ED_K(dots(psi, w.D, 1, Hv, w.D, w.scal + 1, w.part, s));
     double2 hv[2];
     ED_TRY(fetch_scalars(w.scal, 2, hv, s));
-    *e = hv[1].x;
+    if (!std::isfinite(hv[kNrm].x)) return fail(ED_ERR_NUMERIC, "non-finite start vector");
+    if (hv[kNrm].x <= 0.0) return fail(ED_ERR_ARG, "start vector is zero");
+    *e = hv[1].x / hv[kNrm].x;
+    return ED_OK;
+}
+
+// |[exp(-i dt T)]_{m,1}| of the m x m tridiagonal (a, b) in FP64 (Taylor on pieces of norm at most
+// one): absolute error around 1e-14, to tell a step that is far from converged.
+double expm_last_estimate(int m, const double* a, const double* b, double dt) {
+    double nrm = 0.0;
+    for (int i = 0; i < m; ++i) {
+        double r = std::fabs(a[i]);
+        if (i > 0) r += std::fabs(b[i - 1]);
+        if (i + 1 < m) r += std::fabs(b[i]);
+        nrm = std::max(nrm, r);
+    }
+    nrm *= std::fabs(dt);
+    if (!(nrm < 64.0)) return 0.0;  // too long a series: no estimate
+    const int pieces = std::max(1, int(std::ceil(nrm)));
+    const double tau = dt / pieces;
+    std::vector<cplx> u(m, 0.0), t(m), n(m);
+    u[0] = 1.0;
+    for (int p = 0; p < pieces; ++p) {
+        t = u;
+        for (int k = 1; k <= 20; ++k) {  // 1/20! = 4e-19
+            for (int i = 0; i < m; ++i) {
+                cplx v = a[i] * t[i];
+                if (i > 0) v += b[i - 1] * t[i - 1];
+                if (i + 1 < m) v += b[i] * t[i + 1];
+                n[i] = cplx(v.imag(), -v.real()) * (tau / k);
+            }
+            t.swap(n);
+            for (int i = 0; i < m; ++i) u[i] += t[i];
+        }
+    }
+    return std::abs(u[m - 1]);
+}
+
+// n_steps Hermitian Krylov steps on the three-term recurrence with device scalars. The iterations of a
+// step are enqueued in batches and judged in order when their scalars arrive, so a step uses the same
+// dimension as one that looks at every product; what a batch computed beyond it is not used. A
+// batch is the previous step's dimension while an iteration is short next to the host round trip
+// (about 15 us): up to 2^22 amplitudes, where an iteration takes 0.1 ms. The observables of a step
+// ride in the same copy as the next step's scalars.
+ed_status evolve_three_term(const ed_model* m, const Workspace& w, double2* psi, double dt, int n_steps,
+                            const ed_krylov_params* p, const ed_observe* obs, int* total_m, int* max_m, double* max_err,
+                            hipStream_t s) {
+    const int L = m->L, mmax = p->m_max;
+    const bool want_obs = obs && (obs->sz || obs->norm);
+    const bool small = three_term_small_fits(m) && mmax <= kMaxComb;
+    const int cap = w.D <= (int64_t(1) << 22) ? mmax : 1;
+    ThreeTerm T;
+    ED_TRY(three_term_init(m, w, mmax, &T, s));
+    double2* const res = w.scal + kObs;
+    std::vector<double2> hv(size_t(T.count()) + L + 1);
+    const double2* const hN = hv.data();
+    const double2* const hS = hN + (T.SP - T.N);
+    const double2* const hO = hN + T.count();
+    bool pending = want_obs;  // observables enqueued and not yet recorded
+    auto fetch = [&](int step) -> ed_status {
+        ED_TRY(fetch_scalars(T.N, T.count() + L + 1, hv.data(), s));
+        if (pending) {
+            const double n2 = hO[0].x;
+            if (obs->norm) obs->norm[step] = std::sqrt(std::max(n2, 0.0));
+            if (obs->sz)
+                for (int k = 1; k <= L; ++k) obs->sz[size_t(step) * L + k - 1] = hO[1 + (L - k)].x / n2;
+            pending = false;
+        }
+        return ED_OK;
+    };
+    if (want_obs) ED_K(sz_all(psi, L, res, w.part, s, T.N));
+    std::vector<double> al(mmax + 1), be(mmax + 1);
+    std::vector<cplx> u(mmax + 1);
+    // before a step's dimension is known, and beyond the last step's: a few iterations per round trip
+    const int more = small ? 3 : w.D <= (int64_t(1) << 16) ? 2 : 1;
+    int guess = small ? 8 : 2 * more;
+    for (int st = 0; st < n_steps; ++st) {
+        ED_TRY(three_term_start(T, w, psi, true, want_obs, s));
+        int enq = 0, mm = 0;
+        double nrm0 = 0.0, err = 0.0;
+        bool stop = false;
+        while (!stop) {
+            int nb = std::max(more, std::min(guess, cap) - enq);
+            if (p->fixed_m > 0 && cap > 1) nb = std::min(p->fixed_m, mmax) - enq;
+            nb = std::min(nb, mmax - enq);
+            ED_TRY(three_term_run(m, T, w, enq, nb, false, s));
+            enq += nb;
+            ED_TRY(fetch(st));
+            for (; mm < enq && !stop;) {
+                const int j = mm;
+                if (j == 0) {
+                    if (!std::isfinite(hN[0].x)) return fail(ED_ERR_NUMERIC, "non-finite start vector");
+                    if (hN[0].x <= 0.0) return fail(ED_ERR_ARG, "start vector is zero");
+                    nrm0 = std::sqrt(hN[0].x);
+                }
+                if (!std::isfinite(hN[j + 1].x) || !std::isfinite(hS[2 * j].x))
+                    return fail(ED_ERR_NUMERIC, "non-finite value in the Krylov recurrence");
+                const double bprev = j > 0 ? be[j - 1] : 0.0;
+                const cplx h(hS[2 * j].x / hN[j].x, hS[2 * j].y / hN[j].x);
+                al[j] = h.real();
+                be[j] = std::sqrt(std::max(hN[j + 1].x, 0.0) / hN[j].x) / T.sigma;
+                const bool brk = be[j] <= 1e-14 * std::max(std::max(std::abs(h), bprev), 1e-300) || be[j] == 0.0;
+                mm = j + 1;
+                if (p->fixed_m > 0) stop = brk || mm >= std::min(p->fixed_m, mmax);
+                else stop = brk || mm >= mmax;
+                if (!stop) {
+                    if (p->fixed_m > 0) continue;
+                    // far from converged: no need of the extended-precision solve
+                    const double est = expm_last_estimate(mm, al.data(), be.data(), dt);
+                    if (est > 1e-11 && nrm0 * be[j] * est > 4.0 * p->tol) continue;
+                }
+                std::vector<xreal> d(mm), e(mm), Z(size_t(mm) * mm, 0.0L);
+                for (int i = 0; i < mm; ++i) {
+                    d[i] = al[i];
+                    e[i] = i + 1 < mm ? be[i] : 0.0;
+                    Z[size_t(i) * mm + i] = 1.0L;
+                }
+                if (!tridiag_ql_ext(mm, d.data(), e.data(), Z.data()))
+                    return fail(ED_ERR_NUMERIC, "tridiagonal eigensolver did not converge");
+                expm_col_sym_ext(mm, d.data(), Z.data(), dt, u.data());
+                err = brk ? 0.0 : nrm0 * be[j] * std::abs(u[mm - 1]);
+                stop = stop || (p->fixed_m <= 0 && err <= p->tol);
+            }
+        }
+        std::vector<double2> c(mm);
+        for (int i = 0; i < mm; ++i) {
+            const double ci = nrm0 / std::sqrt(hN[i].x);
+            c[i] = make_double2(ci * u[i].real(), ci * u[i].imag());
+        }
+        if (small) {
+            ED_TRY(three_term_combine_small(w, L, mm, c.data(), psi, res, s));
+        } else {
+            if (mm > kMaxComb) return fail(ED_ERR_UNSUPPORTED, "in-place combination of more than 64 vectors");
+            ED_K(combination_ptr(const_cast<const double2* const*>(w.u.data()), mm, c.data(), psi, w.D, s));
+            if (want_obs) ED_K(sz_all(psi, L, res, w.part, s, T.N));
+        }
+        pending = want_obs;
+        if (obs && obs->energy) obs->energy[st] = al[0];
+        guess = mm;
+        *total_m += mm;
+        *max_m = std::max(*max_m, mm);
+        *max_err = std::max(*max_err, err);
+    }
+    if (pending) ED_TRY(fetch(n_steps));
     return ED_OK;
 }
 
@@ -733,8 +877,12 @@ extern "C" ed_status ed_krylov_evolve(const ed_model* model, ed_c64* psi, double
         if (obs->norm) obs->norm[step] = nrm;
         return ED_OK;
     };
-    ED_TRY(record(0));
-    for (int st = 0; st < n_steps; ++st) {
+    const bool three_term = p->hermitian && !p->reorth && p->m_max <= kThreeTermMax;
+    if (three_term)
+        ED_TRY(evolve_three_term(model, w, v, dt, n_steps, p, obs, &total_m, &max_m, &max_err, s));
+    else
+        ED_TRY(record(0));
+    for (int st = 0; st < n_steps && !three_term; ++st) {
         int mu = 0;
         double err = 0.0, e_in = 0.0, n_in = 0.0;
         ED_TRY(krylov_time_step(model, w, v, dt, p, &mu, &err, &e_in, &n_in, s));

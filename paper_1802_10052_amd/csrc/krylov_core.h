@@ -114,6 +114,31 @@ ed_status start_vector(const Workspace& w, const double2* psi, double* nrm, hipS
 // out = sum_i xi_i v_i over the first m basis vectors (xi host); out may be u_0.
 ed_status combine_basis(const Workspace& w, int m, const double2* xi, double2* out, hipStream_t s);
 ed_status measure_state(const double2* psi, int L, const Workspace& w, double* sz, double* nrm, hipStream_t s);
+// Three-term recurrence with device scalars (three_term.hip). N[j].x = |u_j|^2, SP[2 j] = <u_j|H u_j>,
+// SP[2 j + 1] = <u_{j-1}|H u_j> (where taken), all in the workspace's scalar area right before the
+// observables at kObs, so that one copy fetches everything. ticket: the sweeps' arrival counters at the
+// front of the scalar area, zero when no sweep runs.
+constexpr int kThreeTermFree = 140;  // scalars at the front that N and SP leave
+constexpr int kThreeTermMax = 256;  // basis dimensions whose scalars fit there
+struct ThreeTerm {
+    int mmax = 0;
+    double sigma = 1.0;
+    double2 *N = nullptr, *SP = nullptr;
+    unsigned* ticket = nullptr;
+    int count() const { return 3 * mmax + 2; }
+};
+ed_status three_term_init(const ed_model* m, const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s);
+double three_term_scale(const ed_model* m);
+// Basis vector 0: psi itself (alias) or a copy in slot 0, and N[0] unless it is known to hold |psi|^2.
+ed_status three_term_start(const ThreeTerm& T, const Workspace& w, const double2* psi, bool alias, bool have_norm,
+                           hipStream_t s);
+// Iterations j0 .. j0 + nj - 1, asynchronous; both: also project on u_{j-1} explicitly.
+ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace& w, int j0, int nj, bool both,
+                         hipStream_t s);
+// Chains of at most 12 sites: psi = sum c_i u_i in place (u_0 = psi) and its observables in res, one launch.
+bool three_term_small_fits(const ed_model* m);
+ed_status three_term_combine_small(const Workspace& w, int L, int n, const double2* c, double2* psi, double2* res,
+                                   hipStream_t s);
 ed_status krylov_time_step(const ed_model* m, const Workspace& w, double2* psi, double dt,
                            const ed_krylov_params* p, int* m_used, double* err_out, double* e_in,
                            double* nrm_in, hipStream_t s);

@@ -66,24 +66,33 @@ __global__ __launch_bounds__(kThreads) void dot_partial(const double2* __restric
     }
 }
 
-// Sum partials in fixed order: out[i] = scale * sum_b part[b][i] (+ out[i] if accumulate).
+// out[i] = sum_b part[b][i] in a fixed order, one workgroup per sum (one workgroup for all of them took
+// its sums one after the other, 20 us on average in a restarted Lanczos run); also[0] = out[0] where
+// given.
 __global__ __launch_bounds__(kThreads) void reduce_partials(const double2* __restrict__ part, int part_ld,
-                                                            int nblk, int n, double2* __restrict__ out,
-                                                            int accumulate) {
+                                                            int nblk, double2* __restrict__ out,
+                                                            double2* __restrict__ also) {
     __shared__ double lds[kWaves * 2];
-    for (int i = 0; i < n; ++i) {
-        double a[2] = {0.0, 0.0};
-        for (int b = threadIdx.x; b < nblk; b += kThreads) {
-            const double2 v = part[int64_t(b) * part_ld + i];
-            a[0] += v.x;
-            a[1] += v.y;
+    const int i = blockIdx.x;
+    double a[2] = {0.0, 0.0};
+    constexpr int U = 8;
+    for (int b0 = threadIdx.x; b0 < nblk; b0 += U * kThreads) {
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + u * kThreads;
+            v[u] = b < nblk ? part[int64_t(b) * part_ld + i] : make_double2(0.0, 0.0);
         }
-        block_sum<2>(a, lds);
-        if (threadIdx.x < 2) {
-            double* o = reinterpret_cast<double*>(out + i);
-            o[threadIdx.x] = accumulate ? o[threadIdx.x] + a[0] : a[0];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[0] += v[u].x;
+            a[1] += v[u].y;
         }
-        __syncthreads();
+    }
+    block_sum<2>(a, lds);
+    if (threadIdx.x < 2) {
+        reinterpret_cast<double*>(out + i)[threadIdx.x] = a[0];
+        if (also && i == 0) reinterpret_cast<double*>(also)[threadIdx.x] = a[0];
     }
 }
 
@@ -408,6 +417,46 @@ __global__ __launch_bounds__(kThreads) void combine_multi_kernel(MultiPtrs P, in
     }
 }
 
+// out_o = sum_i C[i][o] u_i for o < n_out, complex coefficients by value (read as scalars): the states at
+// several times from one basis in one sweep of it (nine from 20 vectors at L = 20: 105 us), where a
+// combination per time reads the basis once each (62 us each). accumulate: a later chunk of vectors adds to the outputs.
+struct NodeArgs {
+    const double2* in[kNodeIn];
+    double2* out[kNodeOut];
+    double2 c[kNodeIn * kNodeOut];
+};
+
+__global__ __launch_bounds__(kThreads) void combine_nodes(NodeArgs P, int n_in, int n_out, int64_t D, int accumulate) {
+    constexpr int H = 4;  // vectors whose loads are issued together
+    const int64_t stride = int64_t(gridDim.x) * kThreads;
+    for (int64_t x = int64_t(blockIdx.x) * kThreads + threadIdx.x; x < D; x += stride) {
+        double2 acc[kNodeOut];
+#pragma unroll
+        for (int o = 0; o < kNodeOut; ++o) {
+            acc[o] = make_double2(0.0, 0.0);
+            if (accumulate && o < n_out) acc[o] = P.out[o][x];
+        }
+        for (int i0 = 0; i0 < n_in; i0 += H) {
+            double2 v[H];
+#pragma unroll
+            for (int h = 0; h < H; ++h) v[h] = P.in[i0 + h < n_in ? i0 + h : i0][x];
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                if (i0 + h >= n_in) break;
+#pragma unroll
+                for (int o = 0; o < kNodeOut; ++o) {
+                    const int e = (i0 + h) * kNodeOut + o;
+                    acc[o].x = fma(P.c[e].x, v[h].x, fma(-P.c[e].y, v[h].y, acc[o].x));
+                    acc[o].y = fma(P.c[e].x, v[h].y, fma(P.c[e].y, v[h].x, acc[o].y));
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < kNodeOut; ++o)
+            if (o < n_out) P.out[o][x] = acc[o];
+    }
+}
+
 // dst[x] = src[x], one amplitude per thread, with streaming (non-temporal) stores: the plain device
 // copy that sets the box's practical HBM streaming rate for the calibration of the benchmarks.
 __global__ __launch_bounds__(kThreads) void stream_copy_kernel(const double2* __restrict__ src,
@@ -442,7 +491,7 @@ hipError_t dots(const double2* V, int64_t ldv, int n, const double2* w, int64_t 
         } else {
             hipLaunchKernelGGL((dot_partial<kDotGroup>), dim3(G), dim3(kThreads), 0, s, V + int64_t(i0) * ldv, ldv, nn, w, D, part, kPartLd);
         }
-        hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, nn, out + i0, 0);
+        hipLaunchKernelGGL(reduce_partials, dim3(nn), dim3(kThreads), 0, s, part, kPartLd, G, out + i0, nullptr);
     }
     return hipGetLastError();
 }
@@ -462,14 +511,14 @@ hipError_t axpy_multi(const double2* V, int64_t ldv, int n, const double2* coef,
 }
 
 hipError_t reduce_partial_rows(const double2* part, int nblk, int n, double2* out, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, nblk, n, out, 0);
+    hipLaunchKernelGGL(reduce_partials, dim3(n), dim3(kThreads), 0, s, part, kPartLd, nblk, out, nullptr);
     return hipGetLastError();
 }
 
 hipError_t norm2(const double2* w, int64_t D, double2* out, double2* part, hipStream_t s) {
     const int G = grid_for(D);
     hipLaunchKernelGGL(norm2_partial, dim3(G), dim3(kThreads), 0, s, w, D, part, kPartLd);
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, 1, out, 0);
+    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, out, nullptr);
     return hipGetLastError();
 }
 
@@ -501,13 +550,13 @@ hipError_t axpby(const double2* x, double2* y, double2 a, double2 b, int64_t D, 
     return hipGetLastError();
 }
 
-hipError_t sz_all(const double2* psi, int L, double2* out, double2* part, hipStream_t s) {
+hipError_t sz_all(const double2* psi, int L, double2* out, double2* part, hipStream_t s, double2* norm2) {
     const int64_t D = int64_t(1) << L;
     const int cb = L < kZBits ? L : kZBits;
     int64_t nchunk = D >> cb;
     int G = int(nchunk < kSzBlocks ? nchunk : kSzBlocks);
     hipLaunchKernelGGL(sz_partial, dim3(G), dim3(kThreads), 0, s, psi, L, part, kPartLd);
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, L + 1, out, 0);
+    hipLaunchKernelGGL(reduce_partials, dim3(L + 1), dim3(kThreads), 0, s, part, kPartLd, G, out, norm2);
     return hipGetLastError();
 }
 
@@ -516,7 +565,7 @@ hipError_t sz_all(const double2* psi, int L, double2* out, double2* part, hipStr
 namespace ed {
 
 hipError_t sum_partials(const double2* part, int64_t n, double2* out, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, 1, int(n), 1, out, 0);
+    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, 1, int(n), out, nullptr);
     return hipGetLastError();
 }
 
@@ -537,7 +586,7 @@ hipError_t dots_ptr(const double2* const* U, int n, const double2* w, int64_t D,
         } else {
             hipLaunchKernelGGL((dot_partial_ptr<kDotGroup>), dim3(G), dim3(kThreads), 0, s, vp, nn, w, D, part, kPartLd);
         }
-        hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, nn, out + i0, 0);
+        hipLaunchKernelGGL(reduce_partials, dim3(nn), dim3(kThreads), 0, s, part, kPartLd, G, out + i0, nullptr);
     }
     return hipGetLastError();
 }
@@ -556,7 +605,7 @@ hipError_t axpy_norm_ptr(const double2* const* U, int n, const double2* coef, co
         if (last) {
             hipLaunchKernelGGL((sub_sweep<true, 0>), dim3(G), dim3(kThreads), 0, s, ca, nn, coef + i0, w, D, part,
                                kPartLd);
-            hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, 1, nrm_out, 0);
+            hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, nrm_out, nullptr);
         } else {
             hipLaunchKernelGGL((sub_sweep<false, 0>), dim3(G), dim3(kThreads), 0, s, ca, nn, coef + i0, w, D, part,
                                kPartLd);
@@ -591,7 +640,7 @@ hipError_t axpy_dots_ptr(const double2* const* U, int n, const double2* coef, co
     hipLaunchKernelGGL((sub_sweep<false, kKeepDots>), dim3(G), dim3(kThreads), 0, s, ca, n, coef, w, D, part,
                        kPartLd);
     const int nk = n < kKeepDots ? n : kKeepDots;
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, nk, dots_out, 0);
+    hipLaunchKernelGGL(reduce_partials, dim3(nk), dim3(kThreads), 0, s, part, kPartLd, G, dots_out, nullptr);
     if (n > kKeepDots) return dots_ptr(U + kKeepDots, n - kKeepDots, w, D, dots_out + kKeepDots, part, s);
     return hipGetLastError();
 }
@@ -611,8 +660,8 @@ hipError_t axpy_dots_norm_ptr(const double2* const* U, int n, const double2* coe
     }
     hipLaunchKernelGGL((sub_sweep<true, kKeepDots>), dim3(G), dim3(kThreads), 0, s, ca, n, coef, w, D, part, kPartLd);
     const int nk = n < kKeepDots ? n : kKeepDots;
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, nk, dots_out, 0);
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part + kKeepDots, kPartLd, G, 1, nrm_out, 0);
+    hipLaunchKernelGGL(reduce_partials, dim3(nk), dim3(kThreads), 0, s, part, kPartLd, G, dots_out, nullptr);
+    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part + kKeepDots, kPartLd, G, nrm_out, nullptr);
     *ndots = nk;
     return hipGetLastError();
 }
@@ -624,6 +673,23 @@ hipError_t combination_multi(const double2* const* U, int n_in, const double* C,
     for (int i = 0; i < kMultiIn; ++i) P.in[i] = i < n_in ? U[i] : nullptr;
     for (int o = 0; o < kMultiOut; ++o) P.out[o] = o < n_out ? out[o] : nullptr;
     hipLaunchKernelGGL(combine_multi_kernel, dim3(grid_for(D)), dim3(kThreads), 0, s, P, n_in, n_out, C, D);
+    return hipGetLastError();
+}
+
+hipError_t combination_nodes(const double2* const* U, int n_in, const double2* C, double2* const* out, int n_out,
+                             int64_t D, hipStream_t s) {
+    if (n_out < 1 || n_out > kNodeOut) return hipErrorInvalidValue;
+    for (int i0 = 0; i0 < n_in; i0 += kNodeIn) {
+        const int nn = n_in - i0 < kNodeIn ? n_in - i0 : kNodeIn;
+        NodeArgs P;
+        for (int i = 0; i < kNodeIn; ++i) {
+            P.in[i] = i < nn ? U[i0 + i] : nullptr;
+            for (int o = 0; o < kNodeOut; ++o)
+                P.c[i * kNodeOut + o] = i < nn && o < n_out ? C[(i0 + i) * n_out + o] : make_double2(0.0, 0.0);
+        }
+        for (int o = 0; o < kNodeOut; ++o) P.out[o] = o < n_out ? out[o] : nullptr;
+        hipLaunchKernelGGL(combine_nodes, dim3(grid_for(D)), dim3(kThreads), 0, s, P, nn, n_out, D, i0 > 0 ? 1 : 0);
+    }
     return hipGetLastError();
 }
 

@@ -336,3 +336,33 @@ def test_lanczos_xxz_random_fields_restart_sizes(L, basis, keep, reorth):
         print(f"  oracle E0={eo!r}", flush=True)
         assert abs(e0 - eo) <= 1e-10 * abs(eo)
         assert overlap_err(psi.cpu().numpy(), po) <= 1e-9
+
+
+@pytest.mark.parametrize("L", [2, 3, 7, 10, 11, 12, 13, 14])
+def test_krylov_batched_iterations(L):
+    """The three-term steps whose iterations run without a round trip each: one workgroup up to
+    L = 12 (partly filled below L = 10), separate launches above, against the oracle's steps. Several
+    steps (so that a batch is the previous step's dimension) with and without observables, an
+    adaptive and a fixed dimension, and a model with long-range terms. Tolerances as for the quench
+    tests above (1e-9)."""
+    r = np.random.default_rng(L)
+    models = {"tfim": E.tfim(L, 0.7), "xxz": E.xxz(L, 1.0, 0.5, E.random_fields(L, 2)),
+              "generic": E.random_model(L, 3 + L), "lr": E.lrqi(L, 0.6, 1.5)}
+    dt, steps = 0.07, 4
+    for name, desc in models.items():
+        H = OH.hamiltonian_sparse(desc)
+        psi0 = E.random_state(L, 5) * 1.7
+        states = [psi0]
+        for _ in range(steps):
+            states.append(OK.krylov_step(lambda v: H @ v, states[-1], dt, m_max=30, tol=1e-12)[0])
+        m = P.Model(desc)
+        for kw in (dict(tol=1e-12), dict(tol=1e-12, observe=False), dict(fixed_m=min(16, 1 << L))):
+            psi = torch.from_numpy(psi0).to(DEV)
+            _, obs, info = P.krylov_evolve(m, psi, dt, steps, m_max=30, **kw)
+            assert np.linalg.norm(psi.cpu().numpy() - states[-1]) < 1e-9, (L, name, kw)
+            if obs is not None:
+                for n, s in enumerate(states):
+                    n2 = np.vdot(s, s).real
+                    assert abs(obs["norm"][n] - np.sqrt(n2)) < 1e-9
+                    assert np.max(np.abs(obs["sz"][n] - OO.sz_all(s, L))) < 1e-9
+                    assert abs(obs["energy"][n] - np.vdot(s, H @ s).real / n2) < 1e-9 * max(1.0, abs(obs["energy"][n]))
