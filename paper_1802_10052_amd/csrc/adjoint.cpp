@@ -40,8 +40,8 @@ constexpr int kBTb = 9;        // thread bits
 // One pass over 12-bit tiles (the low bits, or c low bits and a window of 12 - c bits at h0):
 // part[tile][p] = sum over the tile of conj(mu[x]) (h_p phi)[x] for the bonds on tile bits
 // (q, q + 1), q0 <= q < q1, of global bit p. phi's tile sits in LDS, so a flipped partner costs an LDS
-// read; both vectors are read once per pass. Bound by memory and LDS: XXXX us for both passes at
-// L = 20, where gathering every partner from global memory took 139 us.
+// read; both vectors are read once per pass. Bound by LDS and FP64: 40 us for both passes at L = 20, where
+// gathering every partner from global memory took 139 us.
 struct BondPass {
     int first, h0, c, tbits;
     int q0, q1;

@@ -82,3 +82,29 @@ def test_autograd_function():
     (3.0 * loss).backward()
     _, gr = OA.gradient_eig(tmpl, J, psi0, 0.1, w)
     assert np.max(np.abs(Jt.grad.numpy() - 3.0 * gr)) <= 1e-9 * 3 * np.max(np.abs(gr))
+
+
+@pytest.mark.parametrize("L", [11, 12, 13, 16, 21])
+def test_bond_sums_over_tiles(L):
+    """The gradient's bond sums on one tile, on the low tile and one window, and with two windows,
+    for dense complex bond operators: the identity dLoss/dJ_b summed with weights J_b is the loss's
+    derivative with respect to a common factor of all couplings, here by central differences in that
+    factor (h = 1e-5: truncation and rounding stay below 1e-7 of the largest term)."""
+    rng = np.random.default_rng(L)
+    A = rng.standard_normal((4, 4)) + 1j * rng.standard_normal((4, 4))
+    tmpl = E.ModelDesc(L, site_ops=[E.SX], site_coef=np.full((1, L), 0.4), bond_ops=[0.3 * (A + A.conj().T)],
+                       bond_coef=np.ones((1, L - 1)))
+    J = E.adjoint_couplings(2, L - 1, 5)
+    w = rng.uniform(-1, 1, L)
+    m, p0 = P.Model(tmpl), torch.from_numpy(E.random_state(L, 3)).to(DEV)
+    kw = dict(substeps=2, m_fixed=24, m_max=30)
+    _, g = P.evolve_adjoint(m, J, p0, 0.1, w, quad_nodes=10, **kw)
+    h = 1e-5
+    for s in range(2):
+        for sel in (slice(0, (L - 1) // 2), slice((L - 1) // 2, L - 1)):
+            Jp, Jm = J.copy(), J.copy()
+            Jp[s, sel] *= 1 + h
+            Jm[s, sel] *= 1 - h
+            fd = (P.evolve_loss(m, Jp, p0, 0.1, w, **kw) - P.evolve_loss(m, Jm, p0, 0.1, w, **kw)) / (2 * h)
+            got = float(np.sum(g[s, sel] * J[s, sel]))
+            assert abs(got - fd) <= 1e-6 * max(abs(fd), float(np.max(np.abs(g * J)))), (L, s, sel, got, fd)
