@@ -103,7 +103,8 @@ ed_status ed_model_create(const ed_model_desc* desc, ed_model** out);
 ed_status ed_model_destroy(ed_model* model);
 /* L and D = 2^L of a model. */
 ed_status ed_model_dims(const ed_model* model, int* L, int64_t* D);
-/* Number of streaming passes over the state one ed_apply_H makes (diagnostic). */
+/* Number of streaming passes over the state one ed_apply_H makes (diagnostic; 1 on the direct launch
+ * described below). */
 ed_status ed_model_passes(const ed_model* model, int* passes);
 
 /* Autotuning of H psi. A model holds up to 96 candidate pass plans (which index bits each
@@ -111,6 +112,9 @@ ed_status ed_model_passes(const ed_model* model, int* passes);
  * whether a pass runs one workgroup per CU, two tiles per workgroup, or one tile per 1024-thread
  * workgroup). All candidates compute the same H psi (up to the order of floating-point sums). Candidates have the fewest passes possible for L (plus the plan
  * without neighbour reads), ordered by an estimated cost; the first is selected at creation.
+ * A model of 12 to 19 sites (18 with single-flip bond terms) without long-range rules starts on a
+ * direct product instead, one launch that gathers every partner amplitude through the caches;
+ * ed_model_select_plan and a tuned plan that is faster replace it.
  * ed_model_tune times every candidate on the caller's device buffers psi, out (D amplitudes each,
  * `reps` products per candidate, HIP events on stream), selects the fastest and returns its
  * index and the per-candidate times (host, may be NULL; count from ed_model_plans). Selecting or

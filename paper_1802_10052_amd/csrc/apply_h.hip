@@ -36,6 +36,86 @@ __global__ __launch_bounds__(256) void hpsi_small(const double2* __restrict__ ps
     out[x] = y;
 }
 
+// One thread per amplitude, partners gathered through the caches, the diagonal from the tile passes'
+// tables: one launch of 2^L / 256 workgroups. A product of up to 2^18 amplitudes is bound by launches
+// and by how little of the chip its 2^(L-12) tiles fill; one launch of many small workgroups takes both
+// away, at the price of one 16-byte gather per term, which the caches of a state this small serve.
+// Chunks of four bits have all their gathers in flight before the first is used.
+// DOT: dot_part[b] (stride 2 with psi2) = the sum over workgroup b of conj(psi) out, and of
+// conj(psi2) out beside it.
+template <unsigned CLS, bool DOT>
+__global__ __launch_bounds__(kTileThreads) void hpsi_direct(const double2* __restrict__ psi, double2* __restrict__ out,
+                                                            const double2* __restrict__ site,
+                                                            const double2* __restrict__ bond,
+                                                            const double2* __restrict__ dlo,
+                                                            const double2* __restrict__ dmid,
+                                                            const double2* __restrict__ dhi, int L,
+                                                            double2* __restrict__ dot_part,
+                                                            const double2* __restrict__ psi2) {
+    constexpr bool OFFR = CLS & kOffReal;
+    constexpr int CH = 4;
+    const int x = blockIdx.x * kTileThreads + threadIdx.x;
+    const double2 v = psi[x];
+    const double2 d0 = dlo[x & 255], d1 = dmid[(x >> 7) & 31], d2 = dhi[x >> 11];
+    double2 acc = cmul(make_double2(d0.x + d1.x + d2.x, d0.y + d1.y + d2.y), v);
+    for (int p0 = 0; p0 < L; p0 += CH) {
+        double2 w[4][CH];
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const int p = p0 + k < L ? p0 + k : 0, pb = p0 + k + 1 < L ? p0 + k : 0;
+            if (CLS & kSiteOff) w[0][k] = psi[x ^ (1 << p)];
+            if (CLS & kBondSingle) {
+                w[1][k] = psi[x ^ (1 << pb)];
+                w[2][k] = psi[x ^ (2 << pb)];
+            }
+            if (CLS & kBondDouble) w[3][k] = psi[x ^ (3 << pb)];
+        }
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const int p = p0 + k;
+            if ((CLS & kSiteOff) && p < L) {
+                const double2 c01 = site[4 * p + 1], c10 = site[4 * p + 2];
+                cfma<OFFR>(acc, sel2((x >> p) & 1, c01, c10), w[0][k]);
+            }
+            if ((CLS & (kBondSingle | kBondDouble)) && p + 1 < L) {
+                const double2* B = bond + 16 * p;
+                const int l = (x >> p) & 3;
+#pragma unroll
+                for (int m = 1; m < 4; ++m) {
+                    if (!(CLS & (m == 3 ? kBondDouble : kBondSingle))) continue;
+                    const double2 b0 = B[0 + (0 ^ m)], b1 = B[4 + (1 ^ m)], b2 = B[8 + (2 ^ m)], b3 = B[12 + (3 ^ m)];
+                    cfma<OFFR>(acc, sel4(l, b0, b1, b2, b3), w[m][k]);
+                }
+            }
+        }
+    }
+    out[x] = acc;
+    if constexpr (DOT) {
+        __shared__ double2 sD[2][kTileThreads / 64];
+        const int n = psi2 ? 2 : 1;
+        for (int i = 0; i < n; ++i) {
+            const double2 u = i == 0 ? v : psi2[x];
+            double dx = fma(u.x, acc.x, u.y * acc.y), dy = fma(u.x, acc.y, -u.y * acc.x);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                dx += __shfl_xor(dx, o);
+                dy += __shfl_xor(dy, o);
+            }
+            if ((threadIdx.x & 63) == 0) sD[i][threadIdx.x >> 6] = make_double2(dx, dy);
+        }
+        __syncthreads();
+        if (int(threadIdx.x) < n) {
+            double2 sum = sD[threadIdx.x][0];
+#pragma unroll
+            for (int w = 1; w < kTileThreads / 64; ++w) {
+                sum.x += sD[threadIdx.x][w].x;
+                sum.y += sD[threadIdx.x][w].y;
+            }
+            dot_part[int(blockIdx.x) * n + int(threadIdx.x)] = sum;
+        }
+    }
+}
+
 // Gathered jobs whose partners a wide tile loads ahead, per round (two rounds). A wide tile holds 4
 // amplitudes per thread, so a job costs 16 registers: 4 jobs fit the 128 registers of a
 // 1024-thread workgroup with a real diagonal, 3 with a complex one.
@@ -147,6 +227,16 @@ hipError_t launch_variant(const ed_model* m, const double2* psi, double2* out, h
                            m->d_site, m->d_bond, L, m->lr ? m->d_lr_low : nullptr);
         return hipGetLastError();
     }
+    if (m->direct) {
+        const dim3 grid{unsigned((int64_t(1) << L) / kTileThreads)}, block{unsigned(kTileThreads)};
+        if (dot_part)
+            hipLaunchKernelGGL((hpsi_direct<CLS, true>), grid, block, 0, s, psi, out, m->d_site, m->d_bond, m->d_diag_lo,
+                               m->d_diag_mid, m->d_diag_hi, L, dot_part, psi2);
+        else
+            hipLaunchKernelGGL((hpsi_direct<CLS, false>), grid, block, 0, s, psi, out, m->d_site, m->d_bond,
+                               m->d_diag_lo, m->d_diag_mid, m->d_diag_hi, L, dot_part, psi2);
+        return hipGetLastError();
+    }
     const int64_t tiles = int64_t(1) << (L - kTileBits);
     for (int ip = 0; ip < m->n_pass; ++ip) {
         const PassDesc& pd = m->pass[ip];
@@ -216,7 +306,13 @@ ed_status launch_apply_H(const ed_model* m, const double2* psi, double2* out, hi
 ed_status launch_apply_H_dot(const ed_model* m, const double2* psi, double2* out, double2* dot_part,
                              int64_t max_parts, int64_t* nparts, hipStream_t s, const double2* psi2) {
     *nparts = 0;
-    const bool fusable = m->L >= kTileBits && m->far.empty() && m->n_pass > 0 && !m->pass[m->n_pass - 1].first &&
+    if (m->direct && m->far.empty() && (int64_t(1) << m->L) / kTileThreads <= max_parts) {
+        const hipError_t e = dispatch<0>(m, psi, out, s, dot_part, psi2);
+        if (e != hipSuccess) return fail(ED_ERR_HIP, std::string("apply_H launch: ") + hipGetErrorString(e));
+        *nparts = (int64_t(1) << m->L) / kTileThreads;
+        return ED_OK;
+    }
+    const bool fusable = !m->direct && m->L >= kTileBits && m->far.empty() && m->n_pass > 0 && !m->pass[m->n_pass - 1].first &&
                          (int64_t(1) << (m->L - kTileBits)) <= max_parts;
     if (!fusable) return launch_apply_H(m, psi, out, s);
     hipError_t e = dispatch<0>(m, psi, out, s, dot_part, psi2);

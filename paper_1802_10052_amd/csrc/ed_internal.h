@@ -40,6 +40,12 @@ constexpr int kMaxPasses = 4;
 
 constexpr int kMaxGather = 8;     // index bits above a tile whose partner tiles are read from L2
 constexpr int kMaxPlans = 96;     // candidate pass plans per model (chosen by ed_model_tune)
+// Chains of 12 up to this many sites run H psi in one launch that gathers every partner through the
+// caches, until a plan is selected (one fewer with single-flip bond terms, which gather two partners
+// more per bond). Direct against the tuned passes, us per product on the device: TFIM L = 14 3.8 / 11.3,
+// L = 18 5.6 / 11.4, L = 19 10.3 / 15.9, L = 20 21.4 / 18.9; XXZ L = 19 12.7 / 16.5, L = 20 23.0 /
+// 19.5; dense operators L = 17 11.9 / 31.3, L = 18 19.4 / 33.4, L = 19 36.4 / 36.0.
+constexpr int kDirectMaxL = 19;
 constexpr int kOccPadBytes = 40960;  // extra LDS that leaves room for one tile workgroup per CU
 
 struct PassDesc {
@@ -123,6 +129,7 @@ struct ed_model {
     ed::PassDesc pass[ed::kMaxPasses];
     int n_cand = 0;              // candidate plans and their pass counts
     int plan = 0;
+    bool direct = false;         // the product runs in one gather launch instead of the plan's passes
     int cand_np[ed::kMaxPlans] = {};
     ed::PassDesc cand[ed::kMaxPlans][ed::kMaxPasses];
     // gathered terms of every candidate pass: [plan][pass][job], counts in njobs
@@ -137,6 +144,8 @@ struct ed_model {
 };
 
 namespace ed {
+// Whether a model starts on the one-launch product (model.cpp; see kDirectMaxL).
+bool direct_fits(const ed_model* m);
 // Launch the passes of out = H psi (apply_h.hip), then the far terms if the model has any.
 ed_status launch_apply_H(const ed_model* m, const double2* psi, double2* out, hipStream_t s);
 // H psi whose last pass also leaves, per tile n, dot_part[n] = sum over the tile of conj(psi) out

@@ -403,6 +403,10 @@ ed_status build_device_tables(ed_model* m) {
     return ED_OK;
 }
 
+bool direct_fits(const ed_model* m) {
+    return !m->lr && m->L >= kTileBits && m->L <= kDirectMaxL - ((m->op_class & kBondSingle) ? 1 : 0);
+}
+
 // Fold the rule terms into per-bit operators and classify them.
 ed_status fold_model(const ed_model_desc* desc, ed_model* m) {
     const int L = desc->L;
@@ -493,6 +497,7 @@ ed_status fold_model(const ed_model_desc* desc, ed_model* m) {
         if (!plan_is_valid(L, (cls & (kBondSingle | kBondDouble)) != 0, m->cand[c], m->cand_np[c]))
             return fail(ED_ERR_UNSUPPORTED, "internal error: invalid H psi pass plan " + std::to_string(c) + " for L = " +
                                                 std::to_string(L));
+    m->direct = direct_fits(m);
     m->jobs.assign(size_t(kMaxPlans) * kMaxPasses * kMaxJobs, GatherJob{});
     for (int c = 0; c < m->n_cand; ++c)
         for (int i = 0; i < m->cand_np[c]; ++i)
@@ -831,7 +836,7 @@ ed_status ed_model_dims(const ed_model* model, int* L, int64_t* D) {
 
 ed_status ed_model_passes(const ed_model* model, int* passes) {
     if (!model || !passes) return ed::fail(ED_ERR_ARG, "null argument");
-    *passes = model->n_pass;
+    *passes = model->direct ? 1 : model->n_pass;
     return ED_OK;
 }
 
@@ -845,6 +850,7 @@ ed_status ed_model_plans(const ed_model* model, int* count, int* selected) {
 ed_status ed_model_select_plan(ed_model* model, int index) {
     if (!model) return ed::fail(ED_ERR_ARG, "model is null");
     if (index < 0 || index >= model->n_cand) return ed::fail(ED_ERR_ARG, "plan index out of range");
+    model->direct = false;
     model->plan = index;
     model->n_pass = model->cand_np[index];
     for (int i = 0; i < model->n_pass; ++i) model->pass[i] = model->cand[index][i];
@@ -950,17 +956,29 @@ ed_status ed_model_tune(ed_model* model, const ed_c64* psi, ed_c64* out, int rep
     int arg = 0;
     float best_ms = 0.0f;
     ed_status st = ED_OK;
-    for (int c = 0; c < model->n_cand && st == ED_OK; ++c) {
-        ed_model_select_plan(model, c);
-        st = ed_apply_H(model, psi, out, stream);  // warm-up
-        if (st != ED_OK) break;
+    auto time_product = [&](float* ms) -> ed_status {
+        ED_TRY(ed_apply_H(model, psi, out, stream));  // warm-up
         (void)hipEventRecord(e0, s);
-        for (int r = 0; r < reps && st == ED_OK; ++r) st = ed_apply_H(model, psi, out, stream);
+        for (int r = 0; r < reps; ++r) ED_TRY(ed_apply_H(model, psi, out, stream));
         (void)hipEventRecord(e1, s);
         (void)hipEventSynchronize(e1);
+        *ms = 0.0f;
+        (void)hipEventElapsedTime(ms, e0, e1);
+        *ms /= float(reps);
+        return ED_OK;
+    };
+    // the direct launch, where this model starts on it: kept unless a plan is faster
+    const bool direct = ed::direct_fits(model);
+    float direct_ms = 0.0f;
+    if (direct) {
+        model->direct = true;
+        st = time_product(&direct_ms);
+    }
+    for (int c = 0; c < model->n_cand && st == ED_OK; ++c) {
+        ed_model_select_plan(model, c);
         float ms = 0.0f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        ms /= float(reps);
+        st = time_product(&ms);
+        if (st != ED_OK) break;
         if (times_ms) times_ms[c] = ms;
         if (c == 0 || ms < best_ms) {
             best_ms = ms;
@@ -971,6 +989,7 @@ ed_status ed_model_tune(ed_model* model, const ed_c64* psi, ed_c64* out, int rep
     (void)hipEventDestroy(e1);
     ED_TRY(st);
     ed_model_select_plan(model, arg);
+    model->direct = direct && direct_ms <= best_ms;
     ed::remember_plan(model);
     if (best) *best = arg;
     return ED_OK;

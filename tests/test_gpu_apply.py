@@ -157,3 +157,25 @@ def test_tuned_plan_cache_selects_at_creation(tmp_path):
     assert P.Model(E.tfim(L + 2, 0.5)).plan_key != key
     P.plan_cache_clear()
     P.plan_cache_load(P._lib.DEFAULT_PLANS) if os.path.exists(P._lib.DEFAULT_PLANS) else None
+
+
+@pytest.mark.parametrize("L", [12, 13, 15, 17, 18, 19, 20])
+def test_direct_product_equals_the_plans(L):
+    """The one-launch product of short chains against a selected streaming plan (and, through it, the
+    oracle tests above): every model class, on both sides of the sizes where it is used. Both add the
+    same terms in another order: 1e-13 relative, as for the product itself."""
+    for kind, desc in models(L).items():
+        m = P.Model(desc)
+        psi = to_dev(E.random_state(L, 4))
+        a = P.apply_H(m, psi)
+        single = any(np.any(np.abs(np.asarray(b).reshape(4, 4)[[0, 0, 1, 1, 2, 2, 3, 3], [1, 2, 0, 3, 0, 3, 1, 2]]) > 0)
+                     for b in np.asarray(desc.bond_ops).reshape(-1, 4, 4))
+        assert (m.passes == 1) == (L <= 19 - single), (kind, m.passes)
+        m.select_plan(m.plans[1])
+        assert m.passes == (1 if L == 12 else 2)
+        b = P.apply_H(m, psi)
+        assert torch.linalg.vector_norm(a - b) < 1e-13 * torch.linalg.vector_norm(b), kind
+    m = P.Model(E.tfim(L, 0.5))
+    best, _ = m.tune(psi, reps=2)
+    assert m.plans[1] == best
+    assert torch.linalg.vector_norm(P.apply_H(m, psi) - P.apply_H(P.Model(E.tfim(L, 0.5)), psi)) < 1e-12
