@@ -15,12 +15,13 @@ __all__ = ["Model", "apply_H", "lanczos_ground", "krylov_evolve", "measure", "en
 
 
 def _stream_ptr(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:  # the raw handle: a Stream object costs as much as the launch of a small product
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dptr(t):
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _check_state(t, D, name="psi"):
