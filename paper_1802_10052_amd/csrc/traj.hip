@@ -12,8 +12,7 @@
 // the host by longest processing time first (each trajectory, heaviest first, goes to the
 // workgroup with the least work so far; the work of a trajectory is taken proportional to its
 // state size plus a fixed per-step overhead), keeps the state and Krylov basis in its own slice of
-// the workspace, runs H psi
-// tile by tile through LDS, and does every reduction, the small exponential, the root search,
+// the workspace, runs H psi, and does every reduction, the small exponential, the root search,
 // the Philox draws and the jumps itself, so a trajectory never returns to the host.
 // Plain path: the same algorithm one trajectory at a time from the host, on the library's
 // stream-level kernels (the per-instance baseline).
@@ -40,7 +39,9 @@ void destroy_model(ed_model* m);
 
 namespace {
 
-constexpr int kTT = 256;       // threads per trajectory workgroup
+constexpr int kTT = 256;       // threads per trajectory workgroup of short chains
+constexpr int kWideTT = 1024;  // and where few long chains leave the chip idle
+constexpr int kWideL = 14;
 constexpr int kTMax = 24;      // max Krylov dimension per step (basis holds kTMax + 1 vectors)
 constexpr int kMaxL = 20;
 constexpr int kMaxHalvings = 10;       // exp(-i tau H_m) e_1: at most 2^10 scaled Taylor sums
@@ -121,71 +122,113 @@ struct TrajArgs {
     long long* busy;  // per workgroup: wall-clock ticks from its start to the end of its last trajectory
 };
 
+constexpr int kMaxTT = 1024;
+constexpr int kTrajL = 16;  // longest chain (validated)
 struct Shared {
     double2 H[(kTMax + 1) * (kTMax + 1)];
     double2 u[kTMax + 1], term[kTMax + 1], acc[kTMax + 1], h[kTMax + 1], h2[kTMax + 1], coef[kTMax + 1];
     double cs[kTMax + 1];  // basis vector i of the step is v_i = cs[i] u_i (u_i stored)
-    double red[kTT / 64][2 * (kTMax + 1)];
+    double red[kMaxTT / 64][32];
+    double tot[32];
     double pop[kMaxL + 1];
     double scal[8];
+    // the model's operators, in LDS for the whole trajectory: the diagonal by the bits 0..7, 7..11 and
+    // 11.. of the index, the off-diagonal entries by term and the bits it flips
+    double2 dlo[256], dmid[32], dhi[1 << (kTrajL - 11)];
+    double2 cs1[kTrajL][2];     // site p, row bit
+    double2 cb[3][kTrajL][4];   // bond p flipping m + 1, row of the two bits
 };
 
 // ---------------------------------------------------------------------------- WG reductions
+// Sum of P = 2^LOG per-lane values over the wave with one transposing butterfly (a lane keeps half of
+// its values at each exchange): lane l then holds the total of value l >> (6 - LOG).
+// (A compile-time recursion: as a loop over h and o the values went to scratch memory.)
+template <int H, int O, int P>
+__device__ __forceinline__ void fold_values(double (&r)[P]) {
+    if constexpr (H >= 1) {
+        const bool up = (threadIdx.x & O) != 0;
+#pragma unroll
+        for (int q = 0; q < H; ++q) {
+            const double keep = up ? r[q + H] : r[q];
+            const double send = up ? r[q] : r[q + H];
+            r[q] = keep + __shfl_xor(send, O, 64);
+        }
+        fold_values<H / 2, O / 2, P>(r);
+    }
+}
+
+template <int LOG>
+__device__ __forceinline__ double wave_totals(double (&r)[1 << LOG]) {
+    fold_values<(1 << LOG) / 2, 32, (1 << LOG)>(r);
+#pragma unroll
+    for (int o = (64 >> LOG) / 2; o > 0; o >>= 1) r[0] += __shfl_xor(r[0], o, 64);
+    return r[0];
+}
+
 // Sum NA per-thread doubles over the workgroup; every thread receives all NA totals in out[].
-template <int NA>
+template <int NA, int TT>
 __device__ void wg_sum(double (&a)[NA], Shared& sh, double* out) {
+    static_assert(NA <= 32, "rows of red and tot");
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int LOG = NA == 1 ? 0 : NA <= 8 ? 3 : NA <= 17 ? 4 : 5;  // 17: 16 and one of its own
+    double r[1 << LOG];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        double v = a[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if (lane == 0) sh.red[wv][i] = v;
+    for (int i = 0; i < (1 << LOG); ++i) r[i] = i < NA ? a[i] : 0.0;
+    const double v = wave_totals<LOG>(r);
+    if ((lane & ((64 >> LOG) - 1)) == 0 && (lane >> (6 - LOG)) < NA) sh.red[wv][lane >> (6 - LOG)] = v;
+    if constexpr (NA == 17) {
+        double e[1] = {a[16]};
+        const double w = wave_totals<0>(e);
+        if (lane == 0) sh.red[wv][16] = w;
     }
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
+    if (threadIdx.x < NA) {
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < kTT / 64; ++w) s += sh.red[w][i];
-        out[i] = s;
+        for (int w = 0; w < TT / 64; ++w) s += sh.red[w][threadIdx.x];
+        sh.tot[threadIdx.x] = s;
     }
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NA; ++i) out[i] = sh.tot[i];
 }
 
 // The loops below take 4 elements (or a group of basis vectors) per iteration and issue all of
 // their loads before using any, so every wave keeps several loads in flight; a workgroup's state
-// has N = 2^L >= 256 = kTT elements, a multiple of kTT.
+// has N = 2^L elements.
+template <int TT>
 __device__ double wg_norm2(const double2* x, int64_t N, Shared& sh) {
     double a[1] = {0.0};
     #pragma unroll 1
-    for (int64_t i = threadIdx.x; i < N; i += 4 * kTT) {
+    for (int64_t i = threadIdx.x; i < N; i += 4 * TT) {
         double2 y[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) y[u] = x[i + u * kTT < N ? i + u * kTT : i];
+        for (int u = 0; u < 4; ++u) y[u] = x[i + u * TT < N ? i + u * TT : i];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (i + u * kTT < N) a[0] = fma(y[u].x, y[u].x, fma(y[u].y, y[u].y, a[0]));
+            if (i + u * TT < N) a[0] = fma(y[u].x, y[u].x, fma(y[u].y, y[u].y, a[0]));
     }
     double o[1];
-    wg_sum<1>(a, sh, o);
+    wg_sum<1, TT>(a, sh, o);
     return o[0];
 }
 
+template <int TT>
 __device__ void wg_scale(double2* x, int64_t N, double s) {
     #pragma unroll 1
-    for (int64_t i = threadIdx.x; i < N; i += 4 * kTT) {
+    for (int64_t i = threadIdx.x; i < N; i += 4 * TT) {
         double2 y[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) y[u] = x[i + u * kTT < N ? i + u * kTT : i];
+        for (int u = 0; u < 4; ++u) y[u] = x[i + u * TT < N ? i + u * TT : i];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (i + u * kTT < N) x[i + u * kTT] = make_double2(y[u].x * s, y[u].y * s);
+            if (i + u * TT < N) x[i + u * TT] = make_double2(y[u].x * s, y[u].y * s);
     }
     __syncthreads();
 }
 
 // out[i] (into sh.h) = <V_i|w>, i < n; vectors taken in groups of 8 to bound register use
+template <int TT>
 __device__ void wg_dots(const double2* V, int64_t ld, int n, const double2* w, int64_t N, Shared& sh) {
     constexpr int G = 8;
     for (int i0 = 0; i0 < n; i0 += G) {
@@ -193,7 +236,7 @@ __device__ void wg_dots(const double2* V, int64_t ld, int n, const double2* w, i
 #pragma unroll
         for (int i = 0; i < 2 * G; ++i) a[i] = 0.0;
         #pragma unroll 1
-        for (int64_t x = threadIdx.x; x < N; x += kTT) {
+        for (int64_t x = threadIdx.x; x < N; x += TT) {
             const double2 y = w[x];
             double2 v[G];
 #pragma unroll
@@ -207,43 +250,20 @@ __device__ void wg_dots(const double2* V, int64_t ld, int n, const double2* w, i
             }
         }
         double o[2 * G];
-        wg_sum<2 * G>(a, sh, o);
+        wg_sum<2 * G, TT>(a, sh, o);
         if (threadIdx.x < G && i0 + threadIdx.x < n)
             sh.h[i0 + threadIdx.x] = make_double2(o[2 * threadIdx.x], o[2 * threadIdx.x + 1]);
     }
     __syncthreads();
 }
 
-// w -= sum_i c_i V_i with c in shared memory
-__device__ void wg_sub(const double2* V, int64_t ld, int n, const double2* c, double2* w, int64_t N) {
-    constexpr int G = 8;
-    #pragma unroll 1
-    for (int64_t x = threadIdx.x; x < N; x += kTT) {
-        double2 acc = w[x];
-        for (int i0 = 0; i0 < n; i0 += G) {
-            double2 v[G];
-#pragma unroll
-            for (int i = 0; i < G; ++i) v[i] = V[(i0 + i < n ? i0 + i : i0) * ld + x];
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                if (i0 + i < n) {
-                    const double2 ci = c[i0 + i];
-                    acc.x -= ci.x * v[i].x - ci.y * v[i].y;
-                    acc.y -= ci.x * v[i].y + ci.y * v[i].x;
-                }
-            }
-        }
-        w[x] = acc;
-    }
-    __syncthreads();
-}
-
 // out = scale * sum_i c_i V_i
+template <int TT>
 __device__ void wg_combine(const double2* V, int64_t ld, int n, const double2* c, double scale, double2* out,
                            int64_t N) {
     constexpr int G = 8;
     #pragma unroll 1
-    for (int64_t x = threadIdx.x; x < N; x += kTT) {
+    for (int64_t x = threadIdx.x; x < N; x += TT) {
         double2 acc = make_double2(0.0, 0.0);
         for (int i0 = 0; i0 < n; i0 += G) {
             double2 v[G];
@@ -268,13 +288,14 @@ __device__ void wg_combine(const double2* V, int64_t ld, int n, const double2* c
 // values are still in registers) and |w_new|^2, which it returns; wg_more_dots takes the dots of
 // any further vectors, in an extra pass.
 constexpr int kSubKeep = 8;
+template <int TT>
 __device__ double wg_sub_dots(const double2* V, int64_t ld, int n, double2* w, int64_t N, Shared& sh) {
     constexpr int G = kSubKeep;
     double a[2 * G + 1];
 #pragma unroll
     for (int i = 0; i < 2 * G + 1; ++i) a[i] = 0.0;
     #pragma unroll 1
-    for (int64_t x = threadIdx.x; x < N; x += kTT) {
+    for (int64_t x = threadIdx.x; x < N; x += TT) {
         double2 acc = w[x];
         double2 keep[G];
 #pragma unroll
@@ -311,7 +332,7 @@ __device__ double wg_sub_dots(const double2* V, int64_t ld, int n, double2* w, i
         a[2 * G] = fma(acc.x, acc.x, fma(acc.y, acc.y, a[2 * G]));
     }
     double o[2 * G + 1];
-    wg_sum<2 * G + 1>(a, sh, o);
+    wg_sum<2 * G + 1, TT>(a, sh, o);
     if (threadIdx.x < G && threadIdx.x < n)
         sh.h2[threadIdx.x] = make_double2(sh.cs[threadIdx.x] * o[2 * threadIdx.x], sh.cs[threadIdx.x] * o[2 * threadIdx.x + 1]);
     __syncthreads();
@@ -319,10 +340,11 @@ __device__ double wg_sub_dots(const double2* V, int64_t ld, int n, double2* w, i
 }
 
 // h2[i] = cs[i] <u_i|w> for kSubKeep <= i < n (the second pass's dots beyond those of sweep B)
+template <int TT>
 __device__ void wg_more_dots(const double2* V, int64_t ld, int n, const double2* w, int64_t N, Shared& sh) {
     constexpr int G = kSubKeep;
     if (n <= G) return;
-    wg_dots(V + G * ld, ld, n - G, w, N, sh);
+    wg_dots<TT>(V + G * ld, ld, n - G, w, N, sh);
     if (threadIdx.x < n - G) {
         const double c = sh.cs[G + threadIdx.x];
         sh.h2[G + threadIdx.x] = make_double2(c * sh.h[threadIdx.x].x, c * sh.h[threadIdx.x].y);
@@ -331,11 +353,12 @@ __device__ void wg_more_dots(const double2* V, int64_t ld, int n, const double2*
 }
 
 // sweep C: w -= sum_i coef_i u_i; returns |w_new|^2
+template <int TT>
 __device__ double wg_sub_norm(const double2* V, int64_t ld, int n, double2* w, int64_t N, Shared& sh) {
     constexpr int G = 8;
     double a[1] = {0.0};
     #pragma unroll 1
-    for (int64_t x = threadIdx.x; x < N; x += kTT) {
+    for (int64_t x = threadIdx.x; x < N; x += TT) {
         double2 acc = w[x];
         for (int i0 = 0; i0 < n; i0 += G) {
             double2 v[G];
@@ -354,108 +377,210 @@ __device__ double wg_sub_norm(const double2* V, int64_t ld, int n, double2* w, i
         a[0] = fma(acc.x, acc.x, fma(acc.y, acc.y, a[0]));
     }
     double o[1];
-    wg_sum<1>(a, sh, o);
+    wg_sum<1, TT>(a, sh, o);
     return o[0];
 }
 
 // Per-site populations: pop[p] = sum_{bit p of x = 0} |psi_x|^2 (p = bit), pop[L] = total.
+template <int TT>
 __device__ void wg_pops(const double2* psi, int L, Shared& sh) {
-    double a[kMaxL + 1];
+    double a[kTrajL + 1];
 #pragma unroll
-    for (int i = 0; i <= kMaxL; ++i) a[i] = 0.0;
-    const int64_t N = int64_t(1) << L;
+    for (int i = 0; i <= kTrajL; ++i) a[i] = 0.0;
+    const int N = 1 << L;
     #pragma unroll 1
-    for (int64_t x = threadIdx.x; x < N; x += kTT) {
+    for (int x = threadIdx.x; x < N; x += TT) {
         const double2 y = psi[x];
         const double q = fma(y.x, y.x, y.y * y.y);
-        a[kMaxL] += q;
+        a[kTrajL] += q;
 #pragma unroll
-        for (int p = 0; p < kMaxL; ++p)
-            if (p < L && !((x >> p) & 1)) a[p] += q;
+        for (int p = 0; p < kTrajL; ++p) a[p] += ((x >> p) & 1) ? 0.0 : q;
     }
-    double o[kMaxL + 1];
-    wg_sum<kMaxL + 1>(a, sh, o);
-    if (threadIdx.x == 0) {
-        for (int p = 0; p < L; ++p) sh.pop[p] = o[p];
-        sh.pop[kMaxL] = o[kMaxL];
+    double o[kTrajL + 1];
+    wg_sum<kTrajL + 1, TT>(a, sh, o);
+    if (threadIdx.x < L) sh.pop[threadIdx.x] = sh.tot[threadIdx.x];
+    if (threadIdx.x == 0) sh.pop[kMaxL] = sh.tot[kTrajL];
+    __syncthreads();
+}
+
+// The model's operators into LDS (once per trajectory).
+template <int TT>
+__device__ void wg_tables(const TrajModel& md, Shared& sh) {
+    const int L = md.L, t = threadIdx.x;
+    const double2* __restrict__ site = md.tb.site;
+    const double2* __restrict__ bond = md.tb.bond;
+    // sum of the diagonal entries of sites s0..s1-1 and bonds b0..b1-1 for index x
+    auto diag = [&](int x, int s0, int s1, int b0, int b1) {
+        double2 d = make_double2(0.0, 0.0);
+        for (int p = s0; p < s1 && p < L; ++p) {
+            const double2 e = site[4 * p + 3 * ((x >> p) & 1)];
+            d.x += e.x;
+            d.y += e.y;
+        }
+        for (int p = b0; p < b1 && p + 1 < L; ++p) {
+            const double2 e = bond[16 * p + 5 * ((x >> p) & 3)];
+            d.x += e.x;
+            d.y += e.y;
+        }
+        return d;
+    };
+    __syncthreads();  // the last trajectory's reads are over
+    for (int e = t; e < 256; e += TT) sh.dlo[e] = diag(e, 0, 8, 0, 7);
+    for (int e = t; e < 32; e += TT) sh.dmid[e] = diag(e << 7, 8, 12, 7, 11);
+    for (int e = t; e < (1 << (kTrajL - 11)); e += TT) sh.dhi[e] = diag(e << 11, 12, kTrajL, 11, kTrajL);
+    for (int e = t; e < 2 * L; e += TT) sh.cs1[e >> 1][e & 1] = site[4 * (e >> 1) + ((e & 1) ? 2 : 1)];
+    for (int e = t; e < 12 * (L - 1); e += TT) {
+        const int p = e / 12, m = (e % 12) / 4, l = e & 3;
+        sh.cb[m][p][l] = bond[16 * p + 4 * l + (l ^ (m + 1))];
     }
     __syncthreads();
 }
 
-// dst = H_eff src for the whole small state of this workgroup; partner amplitudes are read from
-// global memory (the state of one trajectory is at most 1 MiB).
+// (H_eff src)[x]: partners from global memory (the state of one trajectory is at most 1 MiB), four bits'
+// gathers in flight together; operators from LDS (per-lane reads of the model's tables in global
+// memory were three of every four loads of a product).
 template <unsigned CLS>
-__device__ void wg_apply(const TrajModel& md, const double2* src, double scale, double2* dst, Shared& sh) {
+__device__ __forceinline__ double2 traj_entry(const double2* src, int L, int x, const Shared& sh) {
+    constexpr bool OFFR = CLS & kOffReal;
+    constexpr int CH = 4;
+    const double2 v = src[x];
+    double2 acc = make_double2(0.0, 0.0);
+    for (int p0 = 0; p0 < L; p0 += CH) {
+        double2 w[4][CH];
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const int p = p0 + k < L ? p0 + k : 0, pb = p0 + k + 1 < L ? p0 + k : 0;
+            if (CLS & kSiteOff) w[0][k] = src[x ^ (1 << p)];
+            if (CLS & kBondSingle) {
+                w[1][k] = src[x ^ (1 << pb)];
+                w[2][k] = src[x ^ (2 << pb)];
+            }
+            if (CLS & kBondDouble) w[3][k] = src[x ^ (3 << pb)];
+        }
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const int p = p0 + k;
+            if ((CLS & kSiteOff) && p < L) cfma<OFFR>(acc, sh.cs1[p][(x >> p) & 1], w[0][k]);
+            if (p + 1 < L) {
+#pragma unroll
+                for (int m = 0; m < 3; ++m)
+                    if (CLS & (m == 2 ? kBondDouble : kBondSingle)) cfma<OFFR>(acc, sh.cb[m][p][(x >> p) & 3], w[m + 1][k]);
+            }
+        }
+    }
+    const double2 d0 = sh.dlo[x & 255], d1 = sh.dmid[(x >> 7) & 31], d2 = sh.dhi[x >> 11];
+    const double2 dv = cmul(make_double2(d0.x + d1.x + d2.x, d0.y + d1.y + d2.y), v);
+    return make_double2(acc.x + dv.x, acc.y + dv.y);
+}
+
+// w = scale H_eff u into dst, and sh.h[i] = <u_i|w> for i < n, the first kSubKeep of them in the same
+// sweep
+template <unsigned CLS, int TT>
+__device__ void wg_apply_dots(const TrajModel& md, const double2* src, double scale, double2* dst, const double2* V,
+                              int64_t ld, int n, Shared& sh) {
+    constexpr int G = kSubKeep;
     const int L = md.L;
     const int64_t N = int64_t(1) << L;
-    #pragma unroll 1
-    for (int64_t x = threadIdx.x; x < N; x += kTT) {
-        const double2 y = small_entry<CLS>(src, md.tb.site, md.tb.bond, L, x);
-        dst[x] = make_double2(scale * y.x, scale * y.y);
+    double a[2 * G];
+#pragma unroll
+    for (int i = 0; i < 2 * G; ++i) a[i] = 0.0;
+#pragma unroll 1
+    for (int x = threadIdx.x; x < N; x += TT) {
+        double2 v[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) v[i] = V[(i < n ? i : 0) * ld + x];
+        double2 y = traj_entry<CLS>(src, L, x, sh);
+        y.x *= scale;
+        y.y *= scale;
+        dst[x] = y;
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            if (i < n) {
+                a[2 * i] = fma(v[i].x, y.x, fma(v[i].y, y.y, a[2 * i]));
+                a[2 * i + 1] = fma(v[i].x, y.y, fma(-v[i].y, y.x, a[2 * i + 1]));
+            }
+        }
     }
+    double o[2 * G];
+    wg_sum<2 * G, TT>(a, sh, o);
+    if (threadIdx.x < G && threadIdx.x < n)
+        sh.h[threadIdx.x] = make_double2(sh.tot[2 * threadIdx.x], sh.tot[2 * threadIdx.x + 1]);
     __syncthreads();
+    if (n > G) {  // the rest in a sweep of their own; the results land behind the first ones
+        double2 first = make_double2(0.0, 0.0);
+        if (threadIdx.x < G) first = sh.h[threadIdx.x];
+        wg_dots<TT>(V + G * ld, ld, n - G, dst, N, sh);
+        double2 more = make_double2(0.0, 0.0);
+        if (threadIdx.x < n - G) more = sh.h[threadIdx.x];
+        __syncthreads();
+        if (threadIdx.x < G) sh.h[threadIdx.x] = first;
+        if (threadIdx.x < n - G) sh.h[G + threadIdx.x] = more;
+        __syncthreads();
+    }
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+__device__ __forceinline__ double from_lane(double v, int lane) {  // lane the same for the whole wave
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane(int(b & 0xffffffffll), lane);
+    const int hi = __builtin_amdgcn_readlane(int(b >> 32), lane);
+    return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
 }
 
 // u = exp(-i tau H_m) e_1 for the m x m Hessenberg in sh.H (leading dimension kTMax + 1), by
 // scaling the matrix to norm <= 1/2 and summing the Taylor series of the vector 2^s times.
+// The first wave does it alone, row t in lane t, and the others wait for its end: spread over the
+// workgroup it took four barriers a term, some eighty a call, and a call follows every product (ten
+// steps of 32 trajectories at L = 8: 1.73 ms, 2.00 ms that way; the 320 mixed ones 81 ms, 91 ms).
 __device__ void wg_expv(int m, double tau, Shared& sh) {
     constexpr int LD = kTMax + 1;
-    double nrm = 0.0;
-    for (int j = 0; j < m; ++j) {
-        double cs = 0.0;
-        for (int i = 0; i < m; ++i) {
-            const double2 h = sh.H[i * LD + j];
-            cs += sqrt(h.x * h.x + h.y * h.y);
+    if (threadIdx.x < 64) {
+        const int t = threadIdx.x;
+        double cs = 0.0;  // column t's absolute sum
+        if (t < m)
+            for (int i = 0; i < m; ++i) {
+                const double2 h = sh.H[i * LD + t];
+                cs += sqrt(h.x * h.x + h.y * h.y);
+            }
+        double nrm = wave_max(cs) * fabs(tau);
+        int sq = 0;
+        while (nrm > 0.5 && sq < kMaxHalvings) {
+            nrm *= 0.5;
+            ++sq;
         }
-        nrm = fmax(nrm, cs);
-    }
-    nrm *= fabs(tau);
-    int sq = 0;
-    while (nrm > 0.5 && sq < kMaxHalvings) {
-        nrm *= 0.5;
-        ++sq;
-    }
-    const double sc = tau * ldexp(1.0, -sq);  // A = -i sc H
-    const int t = threadIdx.x;
-    if (t < m) sh.u[t] = make_double2(t == 0 ? 1.0 : 0.0, 0.0);
-    __syncthreads();
-    const long reps = 1L << sq;
-    for (long rep = 0; rep < reps; ++rep) {
-        if (t < m) {
-            sh.term[t] = sh.u[t];
-            sh.acc[t] = sh.u[t];
-        }
-        __syncthreads();
-        for (int k = 1; k <= 40; ++k) {
-            double2 nt = make_double2(0.0, 0.0);
-            if (t < m) {
+        const double sc = tau * ldexp(1.0, -sq);  // A = -i sc H
+        const int row = t < m ? t * LD : 0;
+        double2 u = make_double2(t == 0 ? 1.0 : 0.0, 0.0);
+        const long reps = 1L << sq;
+        for (long rep = 0; rep < reps; ++rep) {
+            double2 term = u, acc = u;
+            for (int k = 1; k <= 40; ++k) {
+                double2 nt = make_double2(0.0, 0.0);
                 for (int j = 0; j < m; ++j) {
-                    const double2 h = sh.H[t * LD + j], v = sh.term[j];
-                    nt.x += h.x * v.x - h.y * v.y;
-                    nt.y += h.x * v.y + h.y * v.x;
+                    const double2 h = sh.H[row + j];
+                    const double vx = from_lane(term.x, j), vy = from_lane(term.y, j);
+                    nt.x += h.x * vx - h.y * vy;
+                    nt.y += h.x * vy + h.y * vx;
                 }
                 // multiply by -i sc / k
                 const double f = sc / k;
-                nt = make_double2(f * nt.y, -f * nt.x);
+                term = t < m ? make_double2(f * nt.y, -f * nt.x) : make_double2(0.0, 0.0);
+                acc.x += term.x;
+                acc.y += term.y;
+                const double tn = wave_max(fabs(term.x) + fabs(term.y));
+                const double an = wave_max(fabs(acc.x) + fabs(acc.y));
+                if (tn <= 1e-18 * an) break;
             }
-            __syncthreads();
-            if (t < m) {
-                sh.term[t] = nt;
-                sh.acc[t].x += nt.x;
-                sh.acc[t].y += nt.y;
-            }
-            __syncthreads();
-            double tn = 0.0, an = 0.0;
-            for (int j = 0; j < m; ++j) {
-                tn = fmax(tn, fabs(sh.term[j].x) + fabs(sh.term[j].y));
-                an = fmax(an, fabs(sh.acc[j].x) + fabs(sh.acc[j].y));
-            }
-            __syncthreads();
-            if (tn <= 1e-18 * an) break;
+            u = acc;
         }
-        if (t < m) sh.u[t] = sh.acc[t];
-        __syncthreads();
+        if (t < m) sh.u[t] = u;
     }
+    __syncthreads();
 }
 
 __device__ double unorm2(int m, Shared& sh) {
@@ -464,7 +589,7 @@ __device__ double unorm2(int m, Shared& sh) {
     return s;
 }
 
-template <unsigned CLS>
+template <unsigned CLS, int TT>
 __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared& sh) {
     constexpr int LD = kTMax + 1;
     const TrajModel& md = a.models[a.model_of[tr]];
@@ -481,17 +606,18 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
         ++ndraw;
         return u;
     };
-    for (int64_t x = t; x < N; x += kTT) psi[x] = md.psi0[x];
+    wg_tables<TT>(md, sh);
+    for (int64_t x = t; x < N; x += TT) psi[x] = md.psi0[x];
     __syncthreads();
     {
-        const double n2 = wg_norm2(psi, N, sh);
-        wg_scale(psi, N, 1.0 / sqrt(n2));
+        const double n2 = wg_norm2<TT>(psi, N, sh);
+        wg_scale<TT>(psi, N, 1.0 / sqrt(n2));
     }
     double r = draw();
     int njump = 0, mtot = 0, nunconv = 0;
     double* szo = a.sz_out + int64_t(tr) * a.n_out * a.Lmax;
     auto record = [&](int slot) {
-        wg_pops(psi, L, sh);
+        wg_pops<TT>(psi, L, sh);
         const double tot = sh.pop[kMaxL];
         if (t < L) {
             const int p = L - 1 - t;  // site k = t+1 sits at bit L-1-t
@@ -506,7 +632,7 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
         double tau_left = a.dt;
         for (int ev = 0; tau_left > 0.0; ++ev) {
             // Krylov basis of the current state
-            const double n2 = wg_norm2(psi, N, sh);
+            const double n2 = wg_norm2<TT>(psi, N, sh);
             const double nrm = sqrt(n2);
             if (!(n2 > 0.0) || !isfinite(n2) || ev >= kMaxEventsPerStep) {
                 failed = true;  // uniform: every thread sees the same n2 and ev
@@ -515,7 +641,7 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
             // v_0 = psi / |psi|: u_0 is psi itself, scaled by cs[0]
             if (t == 0) sh.cs[0] = 1.0 / nrm;
             if (t < LD * LD) {
-                for (int e = t; e < LD * LD; e += kTT) sh.H[e] = make_double2(0.0, 0.0);
+                for (int e = t; e < LD * LD; e += TT) sh.H[e] = make_double2(0.0, 0.0);
             }
             __syncthreads();
             int m = 0;
@@ -527,8 +653,7 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
                 // w = H v_j = cs[j] H u_j, then classical Gram-Schmidt: dots, subtraction (with the
                 // second pass's dots and the new norm), and the second subtraction only when the first
                 // removed more than half of the squared norm (the DGKS test, eta = 1/sqrt(2))
-                wg_apply<CLS>(md, Vj, sh.cs[j], Wn, sh);
-                wg_dots(V, ldv, j + 1, Wn, N, sh);  // sh.h = <u_i|w>
+                wg_apply_dots<CLS, TT>(md, Vj, sh.cs[j], Wn, V, ldv, j + 1, sh);  // sh.h = <u_i|w>
                 if (t <= j) {
                     const double c = sh.cs[t];
                     const double2 g = make_double2(c * sh.h[t].x, c * sh.h[t].y);  // <v_i|w>
@@ -536,14 +661,14 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
                     sh.coef[t] = make_double2(c * g.x, c * g.y);  // w -= <v_i|w> v_i = (c_i <v_i|w>) u_i
                 }
                 __syncthreads();
-                const double nw2 = wg_sub_dots(V, ldv, j + 1, Wn, N, sh);  // sh.h2 = <v_i|w'>, |w'|^2
+                const double nw2 = wg_sub_dots<TT>(V, ldv, j + 1, Wn, N, sh);  // sh.h2 = <v_i|w'>, |w'|^2
                 // |w|^2 = |w'|^2 + sum_i |<v_i|w>|^2: the same sum on every thread, in the same order
                 double removed = 0.0;
                 for (int i = 0; i <= j; ++i)
                     removed += sh.H[i * LD + j].x * sh.H[i * LD + j].x + sh.H[i * LD + j].y * sh.H[i * LD + j].y;
                 double b2 = nw2;
                 if (!(nw2 >= removed)) {
-                    wg_more_dots(V, ldv, j + 1, Wn, N, sh);
+                    wg_more_dots<TT>(V, ldv, j + 1, Wn, N, sh);
                     if (t <= j) {
                         const double c = sh.cs[t];
                         sh.H[t * LD + j].x += sh.h2[t].x;
@@ -551,7 +676,7 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
                         sh.coef[t] = make_double2(c * sh.h2[t].x, c * sh.h2[t].y);
                     }
                     __syncthreads();
-                    b2 = wg_sub_norm(V, ldv, j + 1, Wn, N, sh);
+                    b2 = wg_sub_norm<TT>(V, ldv, j + 1, Wn, N, sh);
                 }
                 beta = sqrt(b2);
                 m = j + 1;
@@ -581,7 +706,7 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
             if (f_end > 0.0) {
                 if (t < m) sh.acc[t] = make_double2(nrm * sh.cs[t] * sh.u[t].x, nrm * sh.cs[t] * sh.u[t].y);
                 __syncthreads();
-                wg_combine(V, ldv, m, sh.acc, 1.0, psi, N);
+                wg_combine<TT>(V, ldv, m, sh.acc, 1.0, psi, N);
                 tau_left = 0.0;
                 break;
             }
@@ -619,10 +744,10 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
             wg_expv(m, tau, sh);
             if (t < m) sh.acc[t] = make_double2(nrm * sh.cs[t] * sh.u[t].x, nrm * sh.cs[t] * sh.u[t].y);
             __syncthreads();
-            wg_combine(V, ldv, m, sh.acc, 1.0, psi, N);
+            wg_combine<TT>(V, ldv, m, sh.acc, 1.0, psi, N);
             const double t_abs = step * a.dt + (a.dt - tau_left) + tau;
             // jump probabilities p_nu = rate_nu <psi| J^dag J |psi>_nu (J^dag J diagonal)
-            wg_pops(psi, L, sh);
+            wg_pops<TT>(psi, L, sh);
             const double tot = sh.pop[kMaxL];
             const double rk = draw();
             int kappa = L - 1;
@@ -646,7 +771,7 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
             {
                 const int p = L - 1 - kappa;
                 const int64_t half = N >> 1;
-                for (int64_t q = t; q < half; q += kTT) {
+                for (int64_t q = t; q < half; q += TT) {
                     const int64_t lowm = (int64_t(1) << p) - 1;
                     const int64_t x0 = ((q & ~lowm) << 1) | (q & lowm);
                     const int64_t x1 = x0 | (int64_t(1) << p);
@@ -659,8 +784,8 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
                     psi[x1] = n1;
                 }
                 __syncthreads();
-                const double jn2 = wg_norm2(psi, N, sh);
-                wg_scale(psi, N, 1.0 / sqrt(jn2));
+                const double jn2 = wg_norm2<TT>(psi, N, sh);
+                wg_scale<TT>(psi, N, 1.0 / sqrt(jn2));
             }
             if (t == 0 && njump < a.max_jumps) {
                 a.jump_t[int64_t(tr) * a.max_jumps + njump] = t_abs;
@@ -683,8 +808,8 @@ __device__ void run_trajectory(const TrajArgs& a, int tr, double2* base, Shared&
 
 // Persistent launch: the workgroups take the trajectories of order[] (heaviest first) one at a
 // time from a queue (an atomic counter); every loop below is bounded.
-template <unsigned CLS>
-__global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(2))) void traj_kernel(TrajArgs a) {
+template <unsigned CLS, int TT>
+__global__ __launch_bounds__(TT) __attribute__((amdgpu_waves_per_eu(TT == 256 ? 2 : 4))) void traj_kernel(TrajArgs a) {
     __shared__ Shared sh;
     double2* base = a.scratch + int64_t(blockIdx.x) * a.scratch_stride;
     __shared__ int qnext;
@@ -697,7 +822,7 @@ __global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(2))) void t
         const int q = qnext;
         __syncthreads();
         if (q >= a.n_traj) break;
-        run_trajectory<CLS>(a, a.order[q], base, sh);
+        run_trajectory<CLS, TT>(a, a.order[q], base, sh);
     }
     if (threadIdx.x == 0) a.busy[blockIdx.x] = static_cast<long long>(wall_clock64() - t0);
 }
@@ -713,15 +838,16 @@ __global__ void zero_doubles(double* p, int64_t n) {
 }
 
 template <int I>
-hipError_t launch_traj(unsigned cls, dim3 grid, size_t shm, hipStream_t s, const TrajArgs& a) {
+hipError_t launch_traj(unsigned cls, int threads, dim3 grid, hipStream_t s, const TrajArgs& a) {
     if constexpr (I >= kNumVariants) {
         return hipErrorInvalidValue;
     } else {
         if (variant_fits(kVariants[I], cls)) {
-            hipLaunchKernelGGL((traj_kernel<kVariants[I]>), grid, dim3(kTT), 0, s, a);
+            if (threads == kWideTT) hipLaunchKernelGGL((traj_kernel<kVariants[I], kWideTT>), grid, dim3(kWideTT), 0, s, a);
+            else hipLaunchKernelGGL((traj_kernel<kVariants[I], kTT>), grid, dim3(kTT), 0, s, a);
             return hipGetLastError();
         }
-        return launch_traj<I + 1>(cls, grid, shm, s, a);
+        return launch_traj<I + 1>(cls, threads, grid, s, a);
     }
 }
 
@@ -893,32 +1019,51 @@ static double heff_bound(const ed_model* m) {
 // most one per trajectory, and at most what a 32 GiB scratch budget holds (each workgroup keeps a
 // state and its Krylov basis: (m_max + 2) 2^Lmax amplitudes). variant < 0: the largest count over
 // the variants (used to size the workspace).
+static int cu_count() {
+    int dev = 0, cu = 256, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+        cu = v;
+    return cu;
+}
+
+// Threads of a trajectory workgroup. A workgroup's rate is set by the loads it keeps in flight: where
+// the long chains (14 sites and more) of a batch are no more than the CUs, each takes a CU to itself
+// with 1024 threads (320 trajectories of L = 8..16, ten steps: 91 ms, 132 ms with 256 threads; 256 at
+// L = 14: 24 ms). More
+// of them fill the chip with 256 threads each, two workgroups per CU, whose queue ends more evenly
+// (300 at L = 14: 37 and 40 ms), and short chains have too little work for 1024 (300 at L = 12:
+// 7.4 and 12.2 ms).
+static int traj_threads(const ed_traj_desc* d) {
+    int64_t wide = 0;
+    for (int t = 0; t < d->n_traj; ++t) wide += d->models[d->model_of_traj[t]]->L >= kWideL;
+    return wide > 0 && wide <= cu_count() ? kWideTT : kTT;
+}
+
 template <int I>
-static int resident_per_cu(int variant) {
+static int resident_per_cu(int variant, int threads) {
     if constexpr (I >= kNumVariants) {
         return 1;
     } else {
         if (I == variant) {
             int nb = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, traj_kernel<kVariants[I]>, kTT, 0) != hipSuccess)
-                nb = 1;
-            return std::max(nb, 1);
+            const hipError_t e =
+                threads == kWideTT
+                    ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, traj_kernel<kVariants[I], kWideTT>, kWideTT, 0)
+                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, traj_kernel<kVariants[I], kTT>, kTT, 0);
+            return e == hipSuccess ? std::max(nb, 1) : 1;
         }
-        return resident_per_cu<I + 1>(variant);
+        return resident_per_cu<I + 1>(variant, threads);
     }
 }
 
-static int persistent_blocks(int n_traj, int Lmax, int m_max, int variant) {
-    int dev = 0, cu = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t pr;
-        if (hipGetDeviceProperties(&pr, dev) == hipSuccess) cu = pr.multiProcessorCount;
-    }
+static int persistent_blocks(const ed_traj_desc* d, int Lmax, int m_max, int variant) {
+    const int n_traj = std::max(d->n_traj, 1), cu = cu_count(), threads = traj_threads(d);
     int per_cu = 1;
     if (variant >= 0) {
-        per_cu = resident_per_cu<0>(variant);
+        per_cu = resident_per_cu<0>(variant, threads);
     } else {
-        for (int v = 0; v < kNumVariants; ++v) per_cu = std::max(per_cu, resident_per_cu<0>(v));
+        for (int v = 0; v < kNumVariants; ++v) per_cu = std::max(per_cu, resident_per_cu<0>(v, threads));
     }
     const double per_bytes = double(m_max + 2) * double(int64_t(1) << Lmax) * sizeof(double2);
     const int64_t by_mem = std::max<int64_t>(1, int64_t((double(int64_t(32) << 30)) / per_bytes));
@@ -963,7 +1108,7 @@ extern "C" ed_status ed_trajectories_workspace(const ed_traj_desc* d, const ed_t
     int Lmax = 0;
     for (int i = 0; i < d->n_models; ++i) Lmax = std::max(Lmax, d->models[i]->L);
     const int n_out = d->n_steps / d->out_stride + 1;
-    *bytes = traj_bytes(d, p, Lmax, n_out, persistent_blocks(std::max(d->n_traj, 1), Lmax, p->m_max, -1));
+    *bytes = traj_bytes(d, p, Lmax, n_out, persistent_blocks(d, Lmax, p->m_max, -1));
     return ED_OK;
 }
 
@@ -978,7 +1123,7 @@ extern "C" ed_status ed_trajectories_batch(const ed_traj_desc* d, const ed_traj_
     hipStream_t s = static_cast<hipStream_t>(stream);
     TrajSetup st;
     ED_TRY(build_setup(d, &st));
-    const int G = persistent_blocks(std::max(d->n_traj, 1), st.Lmax, p->m_max, pick_variant(st.cls));
+    const int G = persistent_blocks(d, st.Lmax, p->m_max, pick_variant(st.cls));
     const int Lmax = st.Lmax, n_out = st.n_out, nt = d->n_traj;
     // carve
     char* c = static_cast<char*>(ws);
@@ -1057,7 +1202,7 @@ extern "C" ed_status ed_trajectories_batch(const ed_traj_desc* d, const ed_traj_
         if (nt == 0) return hipGetLastError();
         const int64_t nz = int64_t(nt) * n_out * Lmax;
         hipLaunchKernelGGL(zero_doubles, dim3(unsigned((nz + 255) / 256)), dim3(256), 0, s, sz, nz);
-        return launch_traj<0>(st.cls, dim3(G), 0, s, a);
+        return launch_traj<0>(st.cls, traj_threads(d), dim3(G), s, a);
     };
     if (s == nullptr) {
         hipError_t e = enqueue();

@@ -189,3 +189,24 @@ def test_batched_deterministic():
     # every workgroup reports its busy time; the plain path reports none
     bz = c["info"]["busy_ms"]
     assert 0.0 < bz["min"] <= bz["mean"] <= bz["max"], bz
+
+
+def test_workgroup_widths_agree():
+    """Few long chains run in 1024-thread workgroups, many in 256-thread ones: the same trajectories
+    of L = 14 (first of a batch of 3, and of 300), jumps within the two steps included, and a batch of
+    both lengths. Sums in another order: 1e-11 on the observables, the jump times' own 1e-12."""
+    gamma = 2.0
+    def run(lengths, which):
+        ms = [P.Model(E.xxz(L, 1.0, 1.0)) for L in lengths]
+        p0 = [torch.from_numpy(E.product_state(L, E.neel_index(L))).to(DEV) for L in lengths]
+        return P.trajectories(ms, E.SMINUS, [np.full(L, gamma) for L in lengths], p0, np.array(which, np.int32), 0.02, 4,
+                              2, 11, m_max=20, tol=1e-12)
+    few, many = run([14], [0] * 3), run([14], [0] * 300)
+    assert few["n_jumps"].sum() > 0
+    assert np.array_equal(few["n_jumps"], many["n_jumps"][:3])
+    assert np.array_equal(few["jump_site"], many["jump_site"][:3])
+    assert np.max(np.abs(few["jump_t"] - many["jump_t"][:3])) < 1e-12
+    assert np.max(np.abs(few["sz"] - many["sz"][:3])) < 1e-11
+    mixed, short = run([9, 14], [0, 0, 0, 1]), run([9], [0] * 3)
+    assert np.array_equal(mixed["n_jumps"][:3], short["n_jumps"])
+    assert np.max(np.abs(mixed["sz"][:3, :, :9] - short["sz"])) < 1e-11
