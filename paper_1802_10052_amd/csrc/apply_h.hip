@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void hpsi_small(const double2* __restrict__ ps
     const int64_t D = int64_t(1) << L;
     const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (x >= D) return;
-    double2 y = small_entry<CLS>(psi, site, bond, L, x);
+    double2 y = small_entry<CLS>([=](int mask) { return psi[x ^ mask]; }, site, bond, L, x);
     if (lr_full) {  // long-range zz energy of basis state x
         const double2 e = lr_full[x], v = psi[x];
         y.x += e.x * v.x - e.y * v.y;
@@ -40,7 +40,6 @@ __global__ __launch_bounds__(256) void hpsi_small(const double2* __restrict__ ps
 // tables: one launch of 2^L / 256 workgroups. A product of up to 2^18 amplitudes is bound by launches
 // and by how little of the chip its 2^(L-12) tiles fill; one launch of many small workgroups takes both
 // away, at the price of one 16-byte gather per term, which the caches of a state this small serve.
-// Chunks of four bits have all their gathers in flight before the first is used.
 // DOT: dot_part[b] (stride 2 with psi2) = the sum over workgroup b of conj(psi) out, and of
 // conj(psi2) out beside it.
 template <unsigned CLS, bool DOT>
@@ -52,43 +51,9 @@ __global__ __launch_bounds__(kTileThreads) void hpsi_direct(const double2* __res
                                                             const double2* __restrict__ dhi, int L,
                                                             double2* __restrict__ dot_part,
                                                             const double2* __restrict__ psi2) {
-    constexpr bool OFFR = CLS & kOffReal;
-    constexpr int CH = 4;
     const int x = blockIdx.x * kTileThreads + threadIdx.x;
     const double2 v = psi[x];
-    const double2 d0 = dlo[x & 255], d1 = dmid[(x >> 7) & 31], d2 = dhi[x >> 11];
-    double2 acc = cmul(make_double2(d0.x + d1.x + d2.x, d0.y + d1.y + d2.y), v);
-    for (int p0 = 0; p0 < L; p0 += CH) {
-        double2 w[4][CH];
-#pragma unroll
-        for (int k = 0; k < CH; ++k) {
-            const int p = p0 + k < L ? p0 + k : 0, pb = p0 + k + 1 < L ? p0 + k : 0;
-            if (CLS & kSiteOff) w[0][k] = psi[x ^ (1 << p)];
-            if (CLS & kBondSingle) {
-                w[1][k] = psi[x ^ (1 << pb)];
-                w[2][k] = psi[x ^ (2 << pb)];
-            }
-            if (CLS & kBondDouble) w[3][k] = psi[x ^ (3 << pb)];
-        }
-#pragma unroll
-        for (int k = 0; k < CH; ++k) {
-            const int p = p0 + k;
-            if ((CLS & kSiteOff) && p < L) {
-                const double2 c01 = site[4 * p + 1], c10 = site[4 * p + 2];
-                cfma<OFFR>(acc, sel2((x >> p) & 1, c01, c10), w[0][k]);
-            }
-            if ((CLS & (kBondSingle | kBondDouble)) && p + 1 < L) {
-                const double2* B = bond + 16 * p;
-                const int l = (x >> p) & 3;
-#pragma unroll
-                for (int m = 1; m < 4; ++m) {
-                    if (!(CLS & (m == 3 ? kBondDouble : kBondSingle))) continue;
-                    const double2 b0 = B[0 + (0 ^ m)], b1 = B[4 + (1 ^ m)], b2 = B[8 + (2 ^ m)], b3 = B[12 + (3 ^ m)];
-                    cfma<OFFR>(acc, sel4(l, b0, b1, b2, b3), w[m][k]);
-                }
-            }
-        }
-    }
+    const double2 acc = direct_entry<CLS>([=](int mask) { return psi[x ^ mask]; }, v, site, bond, dlo, dmid, dhi, L, x);
     out[x] = acc;
     if constexpr (DOT) {
         __shared__ double2 sD[2][kTileThreads / 64];

@@ -414,17 +414,16 @@ __device__ __forceinline__ void tile_body(const double2* __restrict__ psi, doubl
                                                        v, acc);
 }
 
-// Per-amplitude body for one x (small L, or one small state per workgroup): partners read from
-// `src` (global memory or LDS). Sites are taken 4 at a time, and every load of a chunk (partner
+// Per-amplitude body for one x (small L, or one small state per workgroup): partner(mask) is
+// src[x ^ mask] (from global memory or LDS). Sites are taken CH at a time, and every load of a chunk (partner
 // amplitudes and per-lane table entries) is issued before any is used; out-of-range sites load
 // index 0 entries and add nothing. A wave so keeps a chunk's loads in flight instead of waiting
 // on one partner per term.
-template <unsigned CLS>
-__device__ __forceinline__ double2 small_entry(const double2* src, const double2* __restrict__ site,
+template <unsigned CLS, int CH = 4, class Partner>
+__device__ __forceinline__ double2 small_entry(Partner partner, const double2* __restrict__ site,
                                                const double2* __restrict__ bond, int L, int64_t x) {
     constexpr bool OFFR = CLS & kOffReal;
-    constexpr int CH = 4;
-    const double2 v = src[x];
+    const double2 v = partner(0);
     double2 diag = make_double2(0.0, 0.0);
     double2 acc = make_double2(0.0, 0.0);
     for (int p0 = 0; p0 < L; p0 += CH) {
@@ -440,17 +439,17 @@ __device__ __forceinline__ double2 small_entry(const double2* src, const double2
             ds[k] = site[4 * ps + 3 * b];
             db[k] = B[5 * l];
             if (CLS & kSiteOff) {
-                ws[k] = src[x ^ (int64_t(1) << ps)];
+                ws[k] = partner(1 << ps);
                 cs[k] = site[4 * ps + (b ? 2 : 1)];
             }
             if (CLS & kBondSingle) {
-                w1[k] = src[x ^ (int64_t(1) << pb)];
+                w1[k] = partner(1 << pb);
                 c1[k] = B[4 * l + (l ^ 1)];
-                w2[k] = src[x ^ (int64_t(2) << pb)];
+                w2[k] = partner(2 << pb);
                 c2[k] = B[4 * l + (l ^ 2)];
             }
             if (CLS & kBondDouble) {
-                w3[k] = src[x ^ (int64_t(3) << pb)];
+                w3[k] = partner(3 << pb);
                 c3[k] = B[4 * l + (l ^ 3)];
             }
         }
@@ -475,6 +474,52 @@ __device__ __forceinline__ double2 small_entry(const double2* src, const double2
     }
     const double2 dv = cmul(diag, v);
     return make_double2(acc.x + dv.x, acc.y + dv.y);
+}
+
+// (H src)[x] of a state of at least 2^12 amplitudes, v = src[x]: the diagonal from the tile passes'
+// tables, every partner src[x ^ mask] from partner(mask), the gathers of four bits in flight before the
+// first is used. site and bond are read as scalars (the caller's kernel must not write them).
+template <unsigned CLS, class Partner>
+__device__ __forceinline__ double2 direct_entry(Partner partner, double2 v, const double2* __restrict__ site,
+                                                const double2* __restrict__ bond, const double2* __restrict__ dlo,
+                                                const double2* __restrict__ dmid, const double2* __restrict__ dhi, int L,
+                                                int x) {
+    constexpr bool OFFR = CLS & kOffReal;
+    constexpr int CH = 4;
+    const double2 d0 = dlo[x & 255], d1 = dmid[(x >> 7) & 31], d2 = dhi[x >> 11];
+    double2 acc = cmul(make_double2(d0.x + d1.x + d2.x, d0.y + d1.y + d2.y), v);
+    for (int p0 = 0; p0 < L; p0 += CH) {
+        double2 w[4][CH];
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const int p = p0 + k < L ? p0 + k : 0, pb = p0 + k + 1 < L ? p0 + k : 0;
+            if (CLS & kSiteOff) w[0][k] = partner(1 << p);
+            if (CLS & kBondSingle) {
+                w[1][k] = partner(1 << pb);
+                w[2][k] = partner(2 << pb);
+            }
+            if (CLS & kBondDouble) w[3][k] = partner(3 << pb);
+        }
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const int p = p0 + k;
+            if ((CLS & kSiteOff) && p < L) {
+                const double2 c01 = site[4 * p + 1], c10 = site[4 * p + 2];
+                cfma<OFFR>(acc, sel2((x >> p) & 1, c01, c10), w[0][k]);
+            }
+            if ((CLS & (kBondSingle | kBondDouble)) && p + 1 < L) {
+                const double2* B = bond + 16 * p;
+                const int l = (x >> p) & 3;
+#pragma unroll
+                for (int m = 1; m < 4; ++m) {
+                    if (!(CLS & (m == 3 ? kBondDouble : kBondSingle))) continue;
+                    const double2 b0 = B[0 + (0 ^ m)], b1 = B[4 + (1 ^ m)], b2 = B[8 + (2 ^ m)], b3 = B[12 + (3 ^ m)];
+                    cfma<OFFR>(acc, sel4(l, b0, b1, b2, b3), w[m][k]);
+                }
+            }
+        }
+    }
+    return acc;
 }
 
 // Kernel variants: a model runs on the first variant whose work flags cover its own and whose

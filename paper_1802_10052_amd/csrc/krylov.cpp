@@ -378,7 +378,7 @@ extern "C" ed_status ed_lanczos_ground(const ed_model* model, const ed_c64* v0, 
         w.c.resize(m);
         for (int i = 0; i < m; ++i) {
             w.u[i] = w.slot(i);
-            w.c[i] = 1.0;
+            w.c[i] = i > 0 && be[i - 1] > 0.0 ? 1.0 / be[i - 1] : 1.0;  // the device basis is not normalised
         }
         const ed_status res =
             conv ? ED_OK : fail(ED_ERR_NOCONV, "Lanczos did not reach the tolerance within max_iter products");

@@ -86,6 +86,24 @@ def test_lanczos_device_resident(L):
         assert overlap_err(psi_d.cpu().numpy(), po) <= 1e-9
 
 
+@pytest.mark.parametrize("L", [3, 8, 9, 11, 13])
+def test_lanczos_device_slices(L):
+    """The edges of the device recurrence's split: a state smaller than one slice (and a basis that
+    exhausts it), one slice, several slices with and without the tile tables."""
+    print(f"lanczos device slices L={L}", flush=True)
+    desc = E.xxz(L, 1.0, 0.5, E.random_fields(L, 5))
+    m = P.Model(desc)
+    e, psi, info = P.lanczos_ground(m, dev(E.random_state(L, 6)), tol=1e-10, max_iter=200)
+    assert info["device_resident"] and info["converged"]
+    H = OH.hamiltonian_sparse(desc)
+    eo = np.linalg.eigvalsh(H.toarray())[0] if L <= 9 else OL.ground_state_eigsh(H, tol=1e-14)[0]
+    assert abs(e - eo) <= 1e-10 * abs(eo)
+    r = H @ psi.cpu().numpy() - e * psi.cpu().numpy()
+    # the test's estimate, and the rounding of a product of |H| <= 2 L
+    assert np.linalg.norm(r) <= 2e-10
+    assert abs(np.linalg.norm(r) - info["residual"]) <= 1e-12
+
+
 def test_lanczos_breakdown_and_noconv():
     L = 12
     m = P.Model(E.tfim(L, 0.0))
