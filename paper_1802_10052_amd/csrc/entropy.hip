@@ -11,8 +11,9 @@
 //      GPU, in blocked form: a read-only matrix-vector sweep of the stored lower triangle per
 //      step, the last kPanel rank-2 updates kept pending in a panel and folded into the matrix
 //      every kPanel steps by one product on the matrix cores.
+//      Up to n = 2048 instead in one launch that holds the matrix in registers (hh_resident).
 //   3. Eigenvalues of the tridiagonal matrix by multisection on Sturm counts on the GPU, 16 lanes
-//      per eigenvalue.
+//      or a whole wave per eigenvalue.
 // When every amplitude of the state has a zero imaginary part (a real state, such as the ground
 // state of a real Hamiltonian started from a real vector), R and rho are real, and so are every
 // Householder vector, tau and panel column: steps 1 and 2 then run in real arithmetic (kernels
@@ -25,6 +26,7 @@
 #include <vector>
 
 #include "ed_internal.h"
+#include "wave_ops.h"
 
 namespace ed {
 namespace {
@@ -694,18 +696,236 @@ __global__ __launch_bounds__(256) void hh_flush(T* __restrict__ A, int n, int s,
             }
 }
 
+// ------------------------------------------------------------------------------ resident reduction
+// The same reduction, unblocked, of a matrix of n <= kResMaxN in one cooperative launch that holds the
+// whole Hermitian matrix in registers: workgroup b of G keeps rows b, b + G, ..., thread t of it the
+// columns t, t + blockDim, ... A step then costs one exchange between workgroups: each applies the last
+// step's rank-2 term to its rows, forms its rows' entries of A v, and publishes them with row c + 1 (the
+// next column, by symmetry, from its one owner); after the barrier every workgroup reads both and forms
+// w, the updated column and the next Householder vector for itself. Rows are dealt cyclically, so the
+// trailing block stays spread over the chip.
+// What bounds it: the latency of that exchange, 7.6 us a step at n = 2048 (3 us of it the wait, 1.7 us
+// the rows' update and product, 1.6 us the reads of what was published and the sums over them), where
+// the three dependent launches of a blocked step take 21 us whatever the trailing size. Whole calls,
+// by launches and here: n = 16 356 and 173 us, n = 64 1.17 and 0.36 ms, n = 1024 20.8 and 6.4 ms,
+// n = 2048 47.5 and 18.1 ms (real 37.8 and 13.3 ms). 1024 threads of two columns spill at n = 2048.
+constexpr int kResRows = 8;
+constexpr int kResMaxN = 2048;             // 256 workgroups of 8 rows; 512 threads of 4 columns
+constexpr int kResThreads = 512;
+constexpr unsigned kResSpins = 1u << 23;   // polls before a workgroup gives up
+// Arrivals are counted on up to 16 counters in lines of their own: one counter takes 256 additions in
+// turn, and a flag per workgroup makes every poll read 1 KB from a few channels (the wait was 3.8 us a
+// step).
+constexpr int kResLeaves = 16, kResLeafStride = 64;
+
+__device__ __forceinline__ void sub_mul_cj(double2& a, double2 x, double2 y) {  // a -= x conj(y)
+    a.x = fma(-x.x, y.x, fma(-x.y, y.y, a.x));
+    a.y = fma(-x.y, y.x, fma(x.x, y.y, a.y));
+}
+__device__ __forceinline__ void sub_mul_cj(double& a, double x, double y) { a = fma(-x, y, a); }
+__device__ __forceinline__ void add_mul(double2& a, double2 x, double2 y) {  // a += x y
+    a.x = fma(x.x, y.x, fma(-x.y, y.y, a.x));
+    a.y = fma(x.x, y.y, fma(x.y, y.x, a.y));
+}
+__device__ __forceinline__ void add_mul(double& a, double x, double y) { a = fma(x, y, a); }
+
+// the sum over each row of 16 lanes, on each of them
+template <typename T>
+__device__ __forceinline__ T sum16(T v) {
+    v = add(v, dpp<kDppXor1>(v));
+    v = add(v, dpp<kDppXor2>(v));
+    v = add(v, dpp<kDppHalfMirror>(v));
+    return add(v, dpp<kDppMirror>(v));
+}
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+    v = sum16(v);
+    v = pair_sum16(v, v);
+    return pair_sum32(v, v);
+}
+
+// leaf[kResLeafStride l]: steps published by the workgroups b = l mod (number of leaves), zero at launch;
+// *stop: set when a wait ran out. ybuf, cbuf: [2][n], of step parity.
+template <typename T, int NC>
+__global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__ A, int n, double* __restrict__ d,
+                                                           double* __restrict__ e, T* ybuf, T* cbuf, int* leaf,
+                                                           int* stop) {
+    constexpr int NW = 16;  // the sums over the waves take 16 entries; those of absent waves stay zero
+    static_assert(kResThreads / 64 <= NW, "waves");
+    __shared__ T sh_v[kResRows], sh_w[kResRows];  // the last step's v and w at this workgroup's rows
+    __shared__ T wred[NW][kResRows], s_yhv[NW], s_col[2], s_y1;
+    __shared__ double s_nx[NW];
+    __shared__ int bad;
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), TT = blockDim.x;
+    const int b = blockIdx.x, G = gridDim.x, lg = __builtin_ctz(G);  // G is a power of two
+    const int leaves = min(G, kResLeaves), per_leaf = G / leaves;
+    const T zero = mk<T>(0.0, 0.0);
+    if (t < NW) {
+        s_yhv[t] = zero;
+        s_nx[t] = 0.0;
+        for (int q = 0; q < kResRows; ++q) wred[t][q] = zero;
+    }
+    if (t == 0) bad = 0;
+    T a[kResRows][NC], v[NC], w[NC], col[NC];
+#pragma unroll
+    for (int p = 0; p < NC; ++p) {
+        const int j = t + TT * p;
+        v[p] = zero;
+        w[p] = zero;
+        col[p] = j < n ? A[int64_t(j) * n] : zero;
+#pragma unroll
+        for (int q = 0; q < kResRows; ++q) {
+            const int i = b + G * q;
+            a[q][p] = zero;
+            if (i < n && j < n) a[q][p] = j <= i ? A[int64_t(i) * n + j] : cj(A[int64_t(j) * n + i]);
+        }
+    }
+    __syncthreads();
+    for (int c = 0;; ++c) {
+        // the next Householder vector from column c (col, rows >= c)
+        double nx = 0.0;
+#pragma unroll
+        for (int p = 0; p < NC; ++p) {
+            const int j = t + TT * p;
+            if (j >= c + 2) nx += abs2(col[p]);
+            if (j == c) s_col[0] = col[p];
+            if (j == c + 1) s_col[1] = col[p];
+        }
+        nx = wave_sum(nx);
+        if (lane == 0) s_nx[wv] = nx;
+        __syncthreads();
+        if (b == 0 && t == 0) d[c] = re(s_col[0]);
+        if (c + 1 >= n) return;
+        nx = sum16(s_nx[lane & 15]);
+        T tau, inv;
+        double beta;
+        reflector(s_col[1], nx, &tau, &beta, &inv);
+        if (b == 0 && t == 0) e[c] = fabs(beta);
+        T vn[NC];
+#pragma unroll
+        for (int p = 0; p < NC; ++p) {
+            const int j = t + TT * p;
+            vn[p] = j > c + 1 ? mul(col[p], inv) : j == c + 1 ? mk<T>(1.0, 0.0) : zero;
+        }
+        // the last step's rank-2 term, and A v, on this workgroup's rows > c; rows q and q + 4 fold
+        // into one register each, four lane halves
+        T* const cb = cbuf + (c & 1) * n;
+        T r[kResRows / 2];
+#pragma unroll
+        for (int h = 0; h < kResRows / 2; ++h) {
+            T acc[2] = {zero, zero};
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int q = h + u * (kResRows / 2), i = b + G * q;
+                if (i > c && i < n) {
+                    const T vi = sh_v[q], wi = sh_w[q];
+#pragma unroll
+                    for (int p = 0; p < NC; ++p) {
+                        if (c > 0) {
+                            sub_mul_cj(a[q][p], vi, w[p]);
+                            sub_mul_cj(a[q][p], wi, v[p]);
+                        }
+                        add_mul(acc[u], a[q][p], vn[p]);
+                        const int j = t + TT * p;
+                        if (i == c + 1 && j > c && j < n) st_shared(cb + j, a[q][p]);
+                    }
+                }
+            }
+            r[h] = pair_sum32(acc[0], acc[1]);
+        }
+        r[0] = pair_sum16(r[0], r[2]);
+        r[1] = pair_sum16(r[1], r[3]);
+        const bool up = (lane & 8) != 0;
+        T s = add(up ? r[1] : r[0], dpp<kDppRor8>(up ? r[0] : r[1]));
+        s = add(s, dpp<kDppHalfMirror>(s));
+        s = add(s, dpp<kDppXor1>(s));
+        s = add(s, dpp<kDppXor2>(s));
+        if ((lane & 7) == 0) wred[wv][lane >> 3] = s;  // lane bits 5, 4, 3 are the row's bits 2, 1, 0
+        drain();                                       // row c + 1, where this workgroup owns it
+        __syncthreads();
+        if (wv == 0) {
+            const int q = lane & 7, i = b + G * q;
+            s = add(wred[lane >> 3][q], wred[8 + (lane >> 3)][q]);
+            s = add(s, dpp<kDppRor8>(s));
+            s = pair_sum16(s, s);
+            s = pair_sum32(s, s);
+            if (lane < kResRows && i > c && i < n) st_shared(ybuf + (c & 1) * n + i, s);
+            drain();
+            if (lane == 0)
+                __hip_atomic_fetch_add(leaf + kResLeafStride * (b & (leaves - 1)), 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            unsigned spins = 0;
+            for (;;) {
+                const bool there = lane >= leaves || ld_shared(leaf + kResLeafStride * lane) >= (c + 1) * per_leaf;
+                if (__all(there)) break;
+                if (++spins > kResSpins || (spins % 256 == 0 && ld_shared(stop) != 0)) {
+                    if (lane == 0) {
+                        st_shared(stop, 1);
+                        bad = 1;
+                    }
+                    break;
+                }
+            }
+            drain();
+        }
+        __syncthreads();
+        if (bad) return;
+        // y = tau (A v), w = y - 1/2 tau (y^H v) v, and column c + 1 with this step's rank-2 term
+        T yhv = zero;
+#pragma unroll
+        for (int p = 0; p < NC; ++p) {
+            const int j = t + TT * p;
+            v[p] = vn[p];
+            w[p] = zero;
+            col[p] = zero;
+            if (j > c && j < n) {
+                w[p] = ld_shared(ybuf + (c & 1) * n + j);
+                col[p] = ld_shared(cb + j);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NC; ++p) {
+            w[p] = mul(tau, w[p]);
+            yhv = add(yhv, mul(cj(w[p]), v[p]));
+            if (t + TT * p == c + 1) s_y1 = w[p];
+        }
+        yhv = wave_sum(yhv);
+        if (lane == 0) s_yhv[wv] = yhv;
+        __syncthreads();
+        yhv = sum16(s_yhv[lane & 15]);
+        const T alpha = scale(mul(tau, yhv), -0.5);
+        const T wc = add(s_y1, alpha);  // w at row c + 1, where v is 1
+#pragma unroll
+        for (int p = 0; p < NC; ++p) {
+            const int j = t + TT * p;
+            w[p] = add(w[p], mul(alpha, v[p]));
+            col[p] = sub(cj(col[p]), add(mul(v[p], cj(wc)), w[p]));
+            if ((j & (G - 1)) == b && j < n) {
+                sh_v[j >> lg] = v[p];
+                sh_w[j >> lg] = w[p];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void clear_flags(int* p, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) p[i] = 0;
+}
+
 // ------------------------------------------------------------------------------ tridiagonal eigenvalues
 // Every eigenvalue of the real symmetric tridiagonal T (diagonal d, off-diagonal e >= 0) by
 // bisection on Sturm counts: the pivots of the LDL^T factorisation of T - x I have as many
 // negative entries as T has eigenvalues below x (Sylvester's law of inertia), and the pivots
 // obey q_0 = d_0 - x, q_i = d_i - x - e_{i-1}^2 / q_{i-1}. A pivot smaller in magnitude than
 // pivmin is replaced by -pivmin (a perturbation of T of at most pivmin per entry), so no pivot
-// is zero. A group of kMS lanes finds the k-th smallest eigenvalue on its own, from the
+// is zero. A group of MS lanes finds the k-th smallest eigenvalue on its own, from the
 // Gershgorin interval down to a width of eps |T|, by multisection: each round the lanes count at
-// kMS equally spaced interior points and the interval shrinks to the gap where the count first
-// exceeds k (log2(kMS + 1) bits per round instead of one). The result depends on d, e and k only.
+// MS equally spaced interior points and the interval shrinks to the gap where the count first
+// exceeds k (log2(MS + 1) bits per round instead of one). The result depends on d, e and k only.
 constexpr int kBisThreads = 256;
-constexpr int kMS = 16;  // lanes per eigenvalue
+// Lanes per eigenvalue: a count is one serial chain, so up to n = 2048 the chip has lanes to spare and a
+// whole wave per eigenvalue takes 9 rounds instead of 13 (1.9 -> 1.5 ms at n = 2048); larger matrices fill it with 16 lanes.
+constexpr int kMSFew = 64, kMSMany = 16, kMSFewMaxN = 2048;
 constexpr int kBndThreads = 1024;
 
 // One workgroup: e2[i] = e[i]^2 (i < n-1); bnd = {lower, upper bound of the spectrum, pivmin,
@@ -779,25 +999,26 @@ __device__ __forceinline__ int sturm_count(const double* __restrict__ d, const d
     return cnt;
 }
 
-// lam[k] = the k-th smallest eigenvalue, k < n; group k of kMS lanes. Invariant: count(lo) <= k <
+// lam[k] = the k-th smallest eigenvalue, k < n; group k of MS lanes. Invariant: count(lo) <= k <
 // count(hi). Every lane of a group computes the same lo, hi and step, so the points are shared
 // exactly: point l is lo + (l + 1) h, and the new bounds are points of the round.
+template <int MS>
 __global__ __launch_bounds__(kBisThreads) void tri_bisect(const double* __restrict__ d, const double* __restrict__ e2,
                                                           int n, const double* __restrict__ bnd, double* __restrict__ lam) {
     const int gid = int(blockIdx.x) * kBisThreads + int(threadIdx.x);
-    const int k0 = gid / kMS, l = gid % kMS;
+    const int k0 = gid / MS, l = gid % MS;
     const int k = k0 < n ? k0 : n - 1;  // surplus lanes repeat the last eigenvalue and write nothing
-    const int g0 = (int(threadIdx.x) & 63) & ~(kMS - 1);  // the group's first lane in the wave
+    const int g0 = (int(threadIdx.x) & 63) & ~(MS - 1);  // the group's first lane in the wave
     double lo = bnd[0], hi = bnd[1];
     const double pivmin = bnd[2], tol = bnd[3];
     for (int it = 0; it < 200 && hi - lo > tol; ++it) {
-        const double h = (hi - lo) / (kMS + 1);
+        const double h = (hi - lo) / (MS + 1);
         const double x = lo + (l + 1) * h;
         const unsigned long long above = __ballot(sturm_count(d, e2, n, x, pivmin) > k);
-        const unsigned gm = unsigned(above >> g0) & ((1u << kMS) - 1);
-        const int f = gm ? __builtin_ctz(gm) : kMS;  // first point whose count exceeds k
+        const unsigned long long gm = (above >> g0) & (~0ull >> (64 - MS));
+        const int f = gm ? __builtin_ctzll(gm) : MS;  // first point whose count exceeds k
         const double nlo = f == 0 ? lo : lo + f * h;
-        const double nhi = f == kMS ? hi : lo + (f + 1) * h;
+        const double nhi = f == MS ? hi : lo + (f + 1) * h;
         if (!(nlo > lo || nhi < hi)) break;  // no point strictly inside: the interval cannot shrink
         lo = nlo;
         hi = nhi;
@@ -863,12 +1084,9 @@ EntWS<T> carve_ent(void* ws, int n) {
     return w;
 }
 
-// Steps 1 and 2 in arithmetic T: the Gram matrix of R (n x K, R = M when left_small, else M^T)
-// and its reduction to the tridiagonal (w.d, w.e), all on stream s.
+// Step 1 in arithmetic T: the Gram matrix of R (n x K, R = M when left_small, else M^T), lower triangle
 template <typename T>
-ed_status gram_tridiagonal(const EntWS<T>& w0, const double2* p, bool left_small, int n, int64_t K, hipStream_t s) {
-    EntWS<T> w = w0;
-    // 1. Gram matrix on the matrix cores
+ed_status gram(const EntWS<T>& w, const double2* p, bool left_small, int n, int64_t K, hipStream_t s) {
     const int nb = (n + kGB - 1) / kGB;
     const int nblocks = nb * (nb + 1) / 2;
     if (left_small)  // R = M: row a of M is psi[a*K .. a*K+K)
@@ -877,8 +1095,56 @@ ed_status gram_tridiagonal(const EntWS<T>& w0, const double2* p, bool left_small
         hipLaunchKernelGGL((gram_mfma<false, T>), dim3(nblocks), dim3(256), 0, s, p, int64_t(1), int64_t(n), n, K,
                            w.rho);
     ED_HIP_TRY(hipGetLastError());
+    return ED_OK;
+}
+
+int resident_groups(int n) { return std::max(1, n / kResRows); }
+// the resident reduction's counters, after its four vectors in the panel area, and the stop flag
+template <typename T>
+int* resident_leaves(const EntWS<T>& w, int n) {
+    return reinterpret_cast<int*>(w.panel + 4 * size_t(n));
+}
+template <typename T>
+int* resident_stop(const EntWS<T>& w, int n) {
+    return resident_leaves(w, n) + kResLeafStride * std::min(resident_groups(n), kResLeaves);
+}
+
+// Step 2 by the resident reduction; *ran = false when the matrix is too large for it or its workgroups
+// cannot all be resident now. It only reads rho, so the launches below can follow it.
+template <typename T>
+ed_status tridiagonal_resident(const EntWS<T>& w, int n, bool* ran, hipStream_t s) {
+    *ran = false;
+    if (n < 2 || n > kResMaxN) return ED_OK;
+    int nn = n;
+    const int G = resident_groups(n);
+    // 4 n entries and at most (n / 8) lines of 256 bytes, one at least, and the flag
+    static_assert(kPW * sizeof(double2) >= 4 * sizeof(double2) + kResLeafStride * sizeof(int) / 2 + sizeof(int), "panel area");
+    const T* A = w.rho;
+    double *d = w.d, *e = w.e;
+    T *yb = w.panel, *cb = w.panel + 2 * size_t(n);
+    int *leaf = resident_leaves(w, n), *stop = resident_stop(w, n);
+    hipLaunchKernelGGL(clear_flags, dim3(1), dim3(256), 0, s, leaf, int(stop - leaf) + 1);
+    void* params[] = {&A, &nn, &d, &e, &yb, &cb, &leaf, &stop};
+    const void* f = n > 2 * kResThreads ? reinterpret_cast<const void*>(&hh_resident<T, 4>)
+                    : n > kResThreads   ? reinterpret_cast<const void*>(&hh_resident<T, 2>)
+                                        : reinterpret_cast<const void*>(&hh_resident<T, 1>);
+    const int threads = std::min(kResThreads, std::max(64, n));
+    const hipError_t err = hipLaunchCooperativeKernel(f, dim3(G), dim3(threads), params, 0, s);
+    if (err == hipErrorCooperativeLaunchTooLarge) {
+        (void)hipGetLastError();
+        return ED_OK;
+    }
+    if (err != hipSuccess)
+        return fail(ED_ERR_HIP, std::string("resident tridiagonalisation launch: ") + hipGetErrorString(err));
+    *ran = true;
+    return ED_OK;
+}
+
+// Step 2 by launches: the reduction of rho to the tridiagonal (w.d, w.e), all on stream s.
+template <typename T>
+ed_status tridiagonal(const EntWS<T>& w0, int n, hipStream_t s) {
+    EntWS<T> w = w0;
     if (n < 2) return ED_OK;
-    // 2. Householder tridiagonalisation
     ED_HIP_TRY(hipMemsetAsync(w.v, 0, size_t(n) * sizeof(T), s));
     ED_HIP_TRY(hipMemsetAsync(w.y, 0, size_t(n) * sizeof(T), s));
     ED_HIP_TRY(hipMemsetAsync(w.vn, 0, size_t(n) * sizeof(T), s));
@@ -968,25 +1234,42 @@ ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, do
     const bool real = cx == 0;
     if (real_arith) *real_arith = real ? 1 : 0;
     const EntWS<double> wr = carve_ent<double>(ws, n);
-    if (real) ED_TRY(gram_tridiagonal<double>(wr, p, left_small, n, K, s));
-    else ED_TRY(gram_tridiagonal<double2>(wc, p, left_small, n, K, s));
-    // 3. eigenvalues of the tridiagonal matrix by bisection on the GPU (the partial-sum area is
-    // free now: n eigenvalues, n squared off-diagonals, 4 bounds), sorted on the host
+    if (real) ED_TRY(gram<double>(wr, p, left_small, n, K, s));
+    else ED_TRY(gram<double2>(wc, p, left_small, n, K, s));
     std::vector<double> dd(n);
     if (n == 1) {
         // rho is the 1x1 matrix |psi|^2, its real part first in either arithmetic
         ED_HIP_TRY(hipMemcpyAsync(dd.data(), wr.rho, sizeof(double), hipMemcpyDeviceToHost, s));
         ED_HIP_TRY(hipStreamSynchronize(s));
     } else {
-        double* lam = wr.part;
-        double* e2 = lam + n;
-        double* bnd = e2 + n;
-        hipLaunchKernelGGL(tri_bounds, dim3(1), dim3(kBndThreads), 0, s, wr.d, wr.e, n, e2, bnd);
-        hipLaunchKernelGGL(tri_bisect, dim3((n * kMS + kBisThreads - 1) / kBisThreads), dim3(kBisThreads), 0, s, wr.d,
-                           e2, n, bnd, lam);
-        ED_HIP_TRY(hipGetLastError());
-        ED_HIP_TRY(hipMemcpyAsync(dd.data(), lam, sizeof(double) * n, hipMemcpyDeviceToHost, s));
-        ED_HIP_TRY(hipStreamSynchronize(s));
+        bool resident = false;
+        if (real) ED_TRY(tridiagonal_resident<double>(wr, n, &resident, s));
+        else ED_TRY(tridiagonal_resident<double2>(wc, n, &resident, s));
+        for (;; resident = false) {
+            if (!resident) {
+                if (real) ED_TRY(tridiagonal<double>(wr, n, s));
+                else ED_TRY(tridiagonal<double2>(wc, n, s));
+            }
+            // 3. eigenvalues of the tridiagonal matrix by bisection on the GPU (the partial-sum area is
+            // free now: n eigenvalues, n squared off-diagonals, 4 bounds), sorted on the host
+            double* lam = wr.part;
+            double* e2 = lam + n;
+            double* bnd = e2 + n;
+            hipLaunchKernelGGL(tri_bounds, dim3(1), dim3(kBndThreads), 0, s, wr.d, wr.e, n, e2, bnd);
+            const int ms = n <= kMSFewMaxN ? kMSFew : kMSMany;
+            hipLaunchKernelGGL(ms == kMSFew ? tri_bisect<kMSFew> : tri_bisect<kMSMany>,
+                               dim3((n * ms + kBisThreads - 1) / kBisThreads), dim3(kBisThreads), 0, s, wr.d, e2, n,
+                               bnd, lam);
+            ED_HIP_TRY(hipGetLastError());
+            int gave_up = 0;
+            if (resident) {
+                const int* stop = real ? resident_stop(wr, n) : resident_stop(wc, n);
+                ED_HIP_TRY(hipMemcpyAsync(&gave_up, stop, sizeof(int), hipMemcpyDeviceToHost, s));
+            }
+            ED_HIP_TRY(hipMemcpyAsync(dd.data(), lam, sizeof(double) * n, hipMemcpyDeviceToHost, s));
+            ED_HIP_TRY(hipStreamSynchronize(s));
+            if (gave_up == 0) break;  // else the resident workgroups did not all run: by launches
+        }
         std::sort(dd.begin(), dd.end());
     }
     double tr = 0.0;

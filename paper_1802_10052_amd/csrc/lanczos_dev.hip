@@ -24,6 +24,7 @@
 #include "ed_vec.h"
 #include "hpsi_device.h"
 #include "krylov_core.h"
+#include "wave_ops.h"
 
 namespace ed {
 namespace {
@@ -51,38 +52,14 @@ struct DevLzArgs {
     double tol;
 };
 
-__device__ __forceinline__ int ld_ctl(int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_ctl(int* p, int v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // What one workgroup writes and another reads within the launch (the partial sums, the new basis
-// vector, the recurrence's scalars) goes through these agent-scope accesses, which pass by the caches
-// that are not shared by the whole chip. The barriers then need no cache write-back or invalidation: a
-// workgroup's own slices of the basis, which every sweep reads, stay in its XCD's L2. With plain
-// accesses and a fence at each barrier a group of 16 vectors took 3.8 us to sum and a barrier 6 to 9 us.
-__device__ __forceinline__ double ld_shared(const double* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_shared(double* p, double v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double2 ld_shared(const double2* p) {
-    const double* q = reinterpret_cast<const double*>(p);
-    return make_double2(ld_shared(q), ld_shared(q + 1));
-}
-__device__ __forceinline__ void st_shared(double2* p, double2 v) {
-    double* q = reinterpret_cast<double*>(p);
-    st_shared(q, v.x);
-    st_shared(q + 1, v.y);
-}
-// every access of this wave so far has been performed (and none below is moved above it)
-__device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+// vector, the recurrence's scalars) goes through ld_shared and st_shared. The barriers then need no
+// cache write-back or invalidation: a workgroup's own slices of the basis, which every sweep reads, stay
+// in its XCD's L2. With plain accesses and a fence at each barrier a group of 16 vectors took 3.8 us to
+// sum and a barrier 6 to 9 us.
 
 // Grid barrier number gen + 1 of the G workgroups that own slices: the counter reaches (gen + 1) G
-// once every one has arrived. It orders the agent-scope accesses above and nothing else. Returns false
+// once every one has arrived. It orders ld_shared and st_shared accesses and nothing else. Returns false
 // (and flags the error) when the wait exceeds the limit or another workgroup failed.
 __device__ bool grid_sync(const DevLzArgs& a, int G, unsigned& gen, int* bad) {
     drain();
@@ -93,8 +70,8 @@ __device__ bool grid_sync(const DevLzArgs& a, int G, unsigned& gen, int* bad) {
         const unsigned target = (gen + 1) * unsigned(G);
         unsigned spins = 0;
         while (__hip_atomic_load(a.bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if (++spins > kSpinLimit || (spins % 64 == 0 && ld_ctl(a.ctl) != 0)) {
-                st_ctl(a.ctl, 1);
+            if (++spins > kSpinLimit || (spins % 64 == 0 && ld_shared(a.ctl) != 0)) {
+                st_shared(a.ctl, 1);
                 *bad = 1;
                 break;
             }
@@ -106,27 +83,6 @@ __device__ bool grid_sync(const DevLzArgs& a, int G, unsigned& gen, int* bad) {
     __syncthreads();
     return *bad == 0;
 }
-
-// b + the lanes' other halves: with lanes paired at distance 32 (16), the lower lane of a pair gets the
-// pair's sum of a and the upper lane the pair's sum of b
-__device__ __forceinline__ double pair_sum32(double a, double b) {
-    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane32_swap(unsigned(ua), unsigned(ub), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(unsigned(ua >> 32), unsigned(ub >> 32), false, false);
-    return __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
-}
-__device__ __forceinline__ double pair_sum16(double a, double b) {
-    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane16_swap(unsigned(ua), unsigned(ub), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(unsigned(ua >> 32), unsigned(ub >> 32), false, false);
-    return __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double a) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(a), CTRL, 0xf, 0xf, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(a), CTRL, 0xf, 0xf, true));
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
 
 // part[i] (i < n) = sum over the workgroup's amplitudes of conj(V_i[x]) w, w from LDS. Wave wv takes
 // the vectors i = wv, wv + 4, ..., eight at a time with four amplitudes a lane, so that a sum ends in
@@ -351,19 +307,19 @@ __device__ void run_tests(const DevLzArgs& a, double* sd, double* se, double* se
         if (threadIdx.x == 0) {
             unsigned spins = 0;
             int ok = 1;
-            while (ld_ctl(a.ctl + 2) < n) {
-                if (++spins > kSpinLimit) st_ctl(a.ctl, 1);
-                if (ld_ctl(a.ctl) != 0 || ld_ctl(a.ctl + 3) != 0) {
+            while (ld_shared(a.ctl + 2) < n) {
+                if (++spins > kSpinLimit) st_shared(a.ctl, 1);
+                if (ld_shared(a.ctl) != 0 || ld_shared(a.ctl + 3) != 0) {
                     ok = 0;
                     break;
                 }
                 __builtin_amdgcn_s_sleep(32);
             }
             drain();
-            const int brk = ld_ctl(a.ctl + 3);  // written before the count of its product
+            const int brk = ld_shared(a.ctl + 3);  // written before the count of its product
             // a breakdown after product n leaves the test of T_n to be made: the count may have
             // passed n between the two reads
-            if (!ok && ld_ctl(a.ctl) == 0 && ld_ctl(a.ctl + 2) >= n) ok = 1;
+            if (!ok && ld_shared(a.ctl) == 0 && ld_shared(a.ctl + 2) >= n) ok = 1;
             if (brk != 0 && brk <= n) ok = 0;
             *go = ok;
         }
@@ -373,7 +329,7 @@ __device__ void run_tests(const DevLzArgs& a, double* sd, double* se, double* se
         const double last = ritz_last(a.alpha, a.beta, n, theta_prev, sd, se, se2, lu, first, &th);
         theta_prev = th;
         if (ld_shared(a.beta + n - 1) * last <= a.tol) {
-            if (threadIdx.x == 0) st_ctl(a.ctl + 1, n);
+            if (threadIdx.x == 0) st_shared(a.ctl + 1, n);
             return;
         }
         if (n == a.nmax) return;
@@ -438,7 +394,7 @@ __global__ __launch_bounds__(kLT, 2) void lanczos_dev_kernel(DevLzArgs a, const 
         __syncthreads();
         block_dots(a.V, a.D, n, x0, wsh, a.p1 + int64_t(g) * a.pld);
         if (!grid_sync(a, G, gen, &bad)) return;
-        if (ld_ctl(a.stop) != 0) return;
+        if (ld_shared(a.stop) != 0) return;
         // first pass: h1_i = <v_i|w>, w -= sum_i h1_i v_i
         sum_partials(a.p1, a.pld, G, n, ks);
         scale_coefs(false, n);
@@ -482,11 +438,11 @@ __global__ __launch_bounds__(kLT, 2) void lanczos_dev_kernel(DevLzArgs a, const 
         if (g == 0 && t == 0) {
             st_shared(a.alpha + j, hs[j].x);
             st_shared(a.beta + j, beta);
-            if (brk) st_ctl(a.ctl + 3, n);
+            if (brk) st_shared(a.ctl + 3, n);
             drain();
-            st_ctl(a.ctl + 2, n);
+            st_shared(a.ctl + 2, n);
             // read by every workgroup after the next barrier, so that all stop together
-            if (ld_ctl(a.ctl + 1) != 0) st_ctl(a.stop, 1);
+            if (ld_shared(a.ctl + 1) != 0) st_shared(a.stop, 1);
         }
         if (brk) return;  // the same on every workgroup
         __syncthreads();

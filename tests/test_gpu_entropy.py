@@ -58,6 +58,22 @@ def test_entropy_real_states(L, l):
     assert abs(S3 - Sref) <= 1e-10 * abs(Sref) + 1e-12
 
 
+@pytest.mark.parametrize("L,l,real", [(20, 10, False), (20, 10, True), (22, 11, False), (22, 11, True)])
+def test_entropy_resident_columns(L, l, real):
+    """The resident reduction with two and with four columns a thread (n = 1024, 2048, its largest)."""
+    from threadpoolctl import threadpool_limits
+    print(f"entropy L={L} l={l} real={real}", flush=True)
+    psi = E.random_state(L, 90 + L, normalise=False, real=real)
+    S, spec, inf = P.entropy(dev(psi), L, l, spectrum=True, info=True)
+    assert inf["real_arith"] == real
+    with threadpool_limits(limits=_host_threads()):
+        ref = OO.schmidt_spectrum(psi, L, l)
+    lam = ref[ref > 1e-300]
+    Sref = float(-(lam * np.log(lam)).sum())
+    assert abs(S - Sref) <= 1e-10 * abs(Sref) + 1e-12
+    assert np.max(np.abs(spec - ref)) < 1e-13
+
+
 def test_entropy_complex_state_flag():
     L = 10
     S, inf = P.entropy(dev(E.random_state(L, 5)), L, 5, info=True)
