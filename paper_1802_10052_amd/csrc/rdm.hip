@@ -127,12 +127,30 @@ __device__ __forceinline__ void run_one(double (&acc)[kRdmPairsPerWave][kRdmOff]
     }
 }
 
+// acc += x conj(y), a complex entry at acc[0], acc[1]
+__device__ __forceinline__ void mul_conj(double* acc, double2 x, double2 y) {
+    acc[0] = fma(x.x, y.x, fma(x.y, y.y, acc[0]));
+    acc[1] = fma(x.y, y.x, fma(-x.x, y.y, acc[1]));
+}
+
+// Positions of a slot's six entries (r, c), r < c, among its 12 doubles
+constexpr int kE01 = 0, kE02 = 2, kE03 = 4, kE12 = 6, kE13 = 8, kE23 = 10;
+
 // The pairs (a,b), (a,c) and, if TRI, (b,c) of the item bits a, b, c (distinct, in any order) into
 // slots S0, S0 + 1, S0 + 2 (full tiles: 512 bases, 8 rows of 64). y[k] = amplitude at
 // base + (k & 1) A + ((k >> 1) & 1) B + (k >> 2) C.
+// An entry of a pair that flips one bit is, at one base, the product along one edge of the cube, and
+// the two pairs of that bit sum the same four edges in different ways. So the loop keeps each edge's
+// sum apart and cube_entries() adds them at the end: a triangle takes 24 products a base instead of 36, a
+// star 20 instead of 24, in as many registers as before. Edge sums lie in the slots' own places:
+// edges along a at (b, c) = (0,0), (1,0) in kE01, kE23 of slot S0 and (0,1), (1,1) in those of S0 + 1;
+// for a triangle, along b at (a, c) = (0,0), (1,0) in kE02, kE13 of S0 and (0,1), (1,1) in kE01, kE23 of
+// S0 + 2; along c at (a, b) = (0,0), (1,0) in kE02, kE13 of S0 + 1 and (0,1), (1,1) in those of S0 + 2.
+// What bounds a pass: the FP64 units and the LDS reads beside them, at two waves a SIMD.
 template <bool TRI, int S0>
 __device__ __forceinline__ void run_cube(double (&acc)[kRdmPairsPerWave][kRdmOff], const double2* s, int lane,
                                          const int* bits, int piece, int ns) {
+    constexpr int S2 = TRI ? S0 + 2 : S0;
     const int a = bits[0], b = bits[1], c = bits[2];
     const int lo = min(a, min(b, c)), hi = max(a, max(b, c)), mid = a + b + c - lo - hi;
     const int A = 1 << a, B = 1 << b, C = 1 << c;
@@ -141,13 +159,59 @@ __device__ __forceinline__ void run_cube(double (&acc)[kRdmPairsPerWave][kRdmOff
         const double2* q = s + (xl | insert_three(64 * r, lo, mid, hi));
         const double2 y0 = q[0], y1 = q[A], y2 = q[B], y3 = q[A + B];
         const double2 y4 = q[C], y5 = q[A + C], y6 = q[B + C], y7 = q[A + B + C];
-        quad_accumulate(acc[S0], y0, y1, y2, y3);
-        quad_accumulate(acc[S0], y4, y5, y6, y7);
-        quad_accumulate(acc[S0 + 1], y0, y1, y4, y5);
-        quad_accumulate(acc[S0 + 1], y2, y3, y6, y7);
+        mul_conj(acc[S0] + kE01, y0, y1);
+        mul_conj(acc[S0] + kE23, y2, y3);
+        mul_conj(acc[S0 + 1] + kE01, y4, y5);
+        mul_conj(acc[S0 + 1] + kE23, y6, y7);
+        mul_conj(acc[S0] + kE02, y0, y2);
+        mul_conj(acc[S0] + kE13, y1, y3);
+        mul_conj(acc[S2] + (TRI ? kE01 : kE02), y4, y6);
+        mul_conj(acc[S2] + (TRI ? kE23 : kE13), y5, y7);
+        mul_conj(acc[S0 + 1] + kE02, y0, y4);
+        mul_conj(acc[S0 + 1] + kE13, y1, y5);
+        mul_conj(acc[TRI ? S2 : S0 + 1] + kE02, y2, y6);
+        mul_conj(acc[TRI ? S2 : S0 + 1] + kE13, y3, y7);
+        mul_conj(acc[S0] + kE03, y0, y3);
+        mul_conj(acc[S0] + kE12, y1, y2);
+        mul_conj(acc[S0 + 1] + kE03, y0, y5);
+        mul_conj(acc[S0 + 1] + kE12, y1, y4);
+        mul_conj(acc[S0] + kE03, y4, y7);
+        mul_conj(acc[S0] + kE12, y5, y6);
+        mul_conj(acc[S0 + 1] + kE03, y2, y7);
+        mul_conj(acc[S0 + 1] + kE12, y3, y6);
         if (TRI) {
-            quad_accumulate(acc[S0 + 2], y0, y2, y4, y6);
-            quad_accumulate(acc[S0 + 2], y1, y3, y5, y7);
+            mul_conj(acc[S2] + kE03, y0, y6);
+            mul_conj(acc[S2] + kE12, y2, y4);
+            mul_conj(acc[S2] + kE03, y1, y7);
+            mul_conj(acc[S2] + kE12, y3, y5);
+        }
+    }
+}
+
+// run_cube's edge sums to the entries of its pairs, in place
+template <bool TRI, int S0>
+__device__ __forceinline__ void cube_entries(double (&acc)[kRdmPairsPerWave][kRdmOff]) {
+    constexpr int S1 = S0 + 1, S2 = TRI ? S0 + 2 : S0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const double a00 = acc[S0][kE01 + e], a10 = acc[S0][kE23 + e], a01 = acc[S1][kE01 + e], a11 = acc[S1][kE23 + e];
+        acc[S0][kE01 + e] = a00 + a01;
+        acc[S0][kE23 + e] = a10 + a11;
+        acc[S1][kE01 + e] = a00 + a10;
+        acc[S1][kE23 + e] = a01 + a11;
+        if (TRI) {
+            const double b00 = acc[S0][kE02 + e], b10 = acc[S0][kE13 + e];
+            const double b01 = acc[S2][kE01 + e], b11 = acc[S2][kE23 + e];
+            const double c00 = acc[S1][kE02 + e], c10 = acc[S1][kE13 + e];
+            const double c01 = acc[S2][kE02 + e], c11 = acc[S2][kE13 + e];
+            acc[S0][kE02 + e] = b00 + b01;
+            acc[S0][kE13 + e] = b10 + b11;
+            acc[S2][kE01 + e] = b00 + b10;
+            acc[S2][kE23 + e] = b01 + b11;
+            acc[S1][kE02 + e] = c00 + c01;
+            acc[S1][kE13 + e] = c10 + c11;
+            acc[S2][kE02 + e] = c00 + c10;
+            acc[S2][kE13 + e] = c01 + c11;
         }
     }
 }
@@ -221,6 +285,9 @@ __device__ __forceinline__ void tile_loop(const double2* __restrict__ psi, const
         __syncthreads();  // tile n has been read and tile n + G stored
     }
 #undef ED_SLOT
+    if (LAY == kLayTriOne) cube_entries<true, 0>(acc);
+    if (LAY == kLayCubeCube || LAY == kLayCubeOneOne) cube_entries<false, 0>(acc);
+    if (LAY == kLayCubeCube) cube_entries<false, 2>(acc);
 }
 
 // FULL: 2^12-amplitude tiles (L >= 12); otherwise the whole state (2^L < 4096) is one tile
@@ -288,20 +355,31 @@ __global__ __launch_bounds__(kRdmThreads) void rdm_pass(const double2* __restric
     }
 }
 
-// tile-position probabilities summed over the workgroups, in order
-__global__ void rdm_hist_reduce(const double* __restrict__ hist, int nblocks, int tsize, double* __restrict__ H) {
-    const int y = blockIdx.x * blockDim.x + threadIdx.x;
-    if (y >= tsize) return;
+// tile-position probabilities summed over the workgroups: a workgroup takes 32 positions, its thread
+// (group, position) every eighth row, and the eight sums are added in order
+constexpr int kHistPos = 32, kHistGroups = 8;
+__global__ __launch_bounds__(kHistPos * kHistGroups) void rdm_hist_reduce(const double* __restrict__ hist, int nblocks,
+                                                                          int tsize, double* __restrict__ H) {
+    __shared__ double red[kHistGroups][kHistPos];
+    const int l = threadIdx.x % kHistPos, q = threadIdx.x / kHistPos;
+    const int y = blockIdx.x * kHistPos + l;
     double sum = 0.0;
+    if (y < tsize) {
 #pragma unroll 8
-    for (int g = 0; g < nblocks; ++g) sum += hist[size_t(g) * (1 << kTileBits) + y];
-    H[y] = sum;
+        for (int g = q; g < nblocks; g += kHistGroups) sum += hist[size_t(g) * (1 << kTileBits) + y];
+    }
+    red[q][l] = sum;
+    __syncthreads();
+    if (q == 0 && y < tsize) {
+        for (int k = 1; k < kHistGroups; ++k) sum += red[k][l];
+        H[y] = sum;
+    }
 }
 
 // one workgroup per pair of the pass: the table row's diagonal is the marginal of H over the
 // pair's two tile bits (strided partial sums, then a fixed LDS tree); the upper entries are the
-// sums of the per-workgroup rows of the accumulator slots holding the pair (slots, then
-// workgroups, in order)
+// sums of the per-workgroup rows of the accumulator slots holding the pair: 16 threads per entry take
+// the rows 16 apart of each slot in order, and their sums are added in order
 __global__ __launch_bounds__(256) void rdm_reduce(const double* __restrict__ part, int nblocks, RdmPass pa,
                                                   const double* __restrict__ H, double* __restrict__ table) {
     __shared__ double red[4][256];
@@ -325,15 +403,17 @@ __global__ __launch_bounds__(256) void rdm_reduce(const double* __restrict__ par
     }
     double* row = table + size_t(pa.slot[pi]) * kRdmVals;
     if (t < 4) row[t] = red[t][0];
-    if (t >= 4 && t < kRdmVals) {
-        const int e = t - 4, o = e >> 1;
-        // a swapped slot holds the entries in the basis with states 1 and 2 exchanged: entry
-        // (0,1) is at (0,2), (0,2) at (0,1), (1,3) at (2,3), (2,3) at (1,3), and (1,2) is the
-        // conjugate of the stored one
-        constexpr int kSwapFrom[6] = {1, 0, 2, 3, 5, 4};
-        const int e_sw = 2 * kSwapFrom[o] + (e & 1);
-        const double sign_sw = (o == 3 && (e & 1)) ? -1.0 : 1.0;
-        double sum = 0.0;
+    constexpr int kG = 16;  // threads per entry
+    static_assert(kRdmOff * kG <= 256, "threads");
+    const int e = t % kRdmOff, g0 = t / kRdmOff, o = e >> 1;
+    // a swapped slot holds the entries in the basis with states 1 and 2 exchanged: entry
+    // (0,1) is at (0,2), (0,2) at (0,1), (1,3) at (2,3), (2,3) at (1,3), and (1,2) is the
+    // conjugate of the stored one
+    constexpr int kSwapFrom[6] = {1, 0, 2, 3, 5, 4};
+    const int e_sw = 2 * kSwapFrom[o] + (e & 1);
+    const double sign_sw = (o == 3 && (e & 1)) ? -1.0 : 1.0;
+    double sum = 0.0;
+    if (g0 < kG)
         for (int it = 0; it < kWaves * kRdmPairsPerWave; ++it) {  // the slots holding this pair, in order
             const int w = it / kRdmPairsPerWave, k = it % kRdmPairsPerWave;
             if (pa.wpair[w][k] != pi) continue;
@@ -341,10 +421,15 @@ __global__ __launch_bounds__(256) void rdm_reduce(const double* __restrict__ par
             const int src = sw ? e_sw : e;
             double acc = 0.0;
 #pragma unroll 8
-            for (int g = 0; g < nblocks; ++g) acc += part[(size_t(it) * nblocks + g) * kRdmOff + src];
+            for (int g = g0; g < nblocks; g += kG) acc += part[(size_t(it) * nblocks + g) * kRdmOff + src];
             sum += sw ? sign_sw * acc : acc;
         }
-        row[t] = sum;
+    __syncthreads();  // row's diagonal has been read from red
+    red[0][t] = sum;
+    __syncthreads();
+    if (t < kRdmOff) {
+        for (int k = 1; k < kG; ++k) sum += red[0][t + k * kRdmOff];
+        row[4 + t] = sum;
     }
 }
 
@@ -654,17 +739,34 @@ bool pack_waves(RdmPass& pa, bool full, int max_tri) {
     }
     if (int(waves.size()) > kWaves) return false;
     // wave programs: (wave, piece, nsplit). Few waves are repeated with their bases split between
-    // the copies; otherwise the heaviest waves are split in two while waves are idle. The programs
-    // are then placed so that the two waves of each SIMD (waves w and w + 4) carry similar loads.
+    // the copies; otherwise one wave is split in two for each idle one, chosen so that the two waves of
+    // each SIMD (waves w and w + 4) carry similar loads: a pass takes as long as its fullest SIMD
+    // (splitting the heaviest waves instead left it 15% above the mean).
     const int W = int(waves.size());
     auto load_of = [](const Wave& w) {
-        int l = 0;
-        for (const Item& it : w.items) l += it.kind == 1 ? 16 : 16 * it.npair;  // quads per lane and tile
+        int l = 0;  // products per lane and tile: 16 quads of 6, or 8 bases of 20 (star) or 24 (triangle)
+        for (const Item& it : w.items) l += it.kind == 1 ? 96 : it.npair == 3 ? 192 : 160;
         return l;
     };
     struct Prog {
         int w, piece, nsplit;
         double load;
+    };
+    // the programs in the order of their loads, dealt to the SIMD with the least; returns the largest load
+    constexpr int kSimds = 4;
+    auto deal = [&](std::vector<Prog>& ps, std::vector<int>* dst) {
+        std::stable_sort(ps.begin(), ps.end(), [](const Prog& x, const Prog& y) { return x.load > y.load; });
+        double simd_load[kSimds] = {0, 0, 0, 0};
+        int simd_used[kSimds] = {0, 0, 0, 0};
+        for (const Prog& pr : ps) {
+            int sm = -1;
+            for (int q = 0; q < kSimds; ++q)
+                if (simd_used[q] < kWaves / kSimds && (sm < 0 || simd_load[q] < simd_load[sm])) sm = q;
+            if (dst) dst->push_back(sm + kSimds * simd_used[sm]);
+            ++simd_used[sm];
+            simd_load[sm] += pr.load;
+        }
+        return *std::max_element(simd_load, simd_load + kSimds);
     };
     std::vector<Prog> progs;
     if (W > 0 && W <= kWaves / 2) {
@@ -672,21 +774,23 @@ bool pack_waves(RdmPass& pa, bool full, int max_tri) {
         for (int c = 0; c < copies; ++c)
             for (int w = 0; w < W; ++w) progs.push_back({w, c, copies, double(load_of(waves[w])) / copies});
     } else {
-        for (int w = 0; w < W; ++w) progs.push_back({w, 0, 1, double(load_of(waves[w]))});
-        while (int(progs.size()) < kWaves) {
-            int h = -1;
-            for (int i = 0; i < int(progs.size()); ++i)
-                if (progs[i].nsplit == 1 && (h < 0 || progs[i].load > progs[h].load)) h = i;
-            if (h < 0) break;
-            progs[h].nsplit = 2;
-            progs[h].load /= 2;
-            progs.push_back({progs[h].w, 1, 2, progs[h].load});
+        double best = -1.0;
+        for (int mask = 0; mask < (1 << W); ++mask) {  // the waves split in two, one for each idle wave
+            if (__builtin_popcount(unsigned(mask)) != kWaves - W) continue;
+            std::vector<Prog> ps;
+            for (int w = 0; w < W; ++w) {
+                const int ns = (mask >> w) & 1 ? 2 : 1;
+                for (int c = 0; c < ns; ++c) ps.push_back({w, c, ns, double(load_of(waves[w])) / ns});
+            }
+            const double worst = deal(ps, nullptr);
+            if (best < 0.0 || worst < best) {
+                best = worst;
+                progs = ps;
+            }
         }
     }
-    std::stable_sort(progs.begin(), progs.end(), [](const Prog& x, const Prog& y) { return x.load > y.load; });
-    constexpr int kSimds = 4;
-    double simd_load[kSimds] = {0, 0, 0, 0};
-    int simd_used[kSimds] = {0, 0, 0, 0};
+    std::vector<int> place;
+    deal(progs, &place);
     for (int w = 0; w < kWaves; ++w) {
         pa.layout[w] = kLayNone;
         pa.piece[w] = 0;
@@ -696,12 +800,9 @@ bool pack_waves(RdmPass& pa, bool full, int max_tri) {
             pa.wswap[w][k] = 0;
         }
     }
-    for (const Prog& pr : progs) {
-        int sm = -1;
-        for (int q = 0; q < kSimds; ++q)
-            if (simd_used[q] < kWaves / kSimds && (sm < 0 || simd_load[q] < simd_load[sm])) sm = q;
-        const int dst = sm + kSimds * simd_used[sm]++;
-        simd_load[sm] += pr.load;
+    for (size_t i = 0; i < progs.size(); ++i) {
+        const Prog& pr = progs[i];
+        const int dst = place[i];
         const Wave& src = waves[pr.w];
         pa.layout[dst] = src.layout;
         pa.piece[dst] = pr.piece;
@@ -967,7 +1068,8 @@ extern "C" ed_status ed_rdm(const ed_c64* psi, int L, ed_c64* rho1, ed_c64* rho2
         }
         ED_HIP_TRY(hipGetLastError());
         const int tsize = 1 << pa.T;
-        hipLaunchKernelGGL(rdm_hist_reduce, dim3((tsize + 255) / 256), dim3(256), 0, s, hist, G, tsize, H);
+        hipLaunchKernelGGL(rdm_hist_reduce, dim3((tsize + kHistPos - 1) / kHistPos),
+                           dim3(kHistPos * kHistGroups), 0, s, hist, G, tsize, H);
         ED_HIP_TRY(hipGetLastError());
         hipLaunchKernelGGL(rdm_reduce, dim3(pa.npairs), dim3(256), 0, s, part, G, pa, H, table);
         ED_HIP_TRY(hipGetLastError());
