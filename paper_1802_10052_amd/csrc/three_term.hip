@@ -152,6 +152,7 @@ struct SubArgs {
 // y <- u_{j+1} in place, N_{j+1}. Bound by memory: 64 B per amplitude (13 us at L = 20, in the last-level
 // cache). Up to kOwnParts per-tile partials of the product's projection are summed by every workgroup
 // for itself, which costs less than a reduction launch (5 us).
+template <bool NT>
 __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
     __shared__ double lds[kThr / 64][4];
     __shared__ double lds1[kThr / 64][1];
@@ -200,8 +201,8 @@ __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
         for (int u = 0; u < U; ++u) {
             const int64_t x = x0 + u * kThr < hi ? x0 + u * kThr : x0;
             y[u] = A.y[x];
-            v[u] = A.u[x];
-            w[u] = A.um1 ? A.um1[x] : make_double2(0.0, 0.0);
+            v[u] = load_vec<NT>(A.u + x);
+            w[u] = A.um1 ? load_vec<NT>(A.um1 + x) : make_double2(0.0, 0.0);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -584,7 +585,7 @@ ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace&
             if (a.both)
                 ED_L(dots_ptr(const_cast<const double2* const*>(&w.u[j - 1]), 1, a.y, D, T.SP + 2 * j + 1, w.part, s));
         }
-        hipLaunchKernelGGL(three_term_sub, dim3(G), dim3(kThr), 0, s, a);
+        hipLaunchKernelGGL(outgrows_cache(3, w.D) ? three_term_sub<true> : three_term_sub<false>, dim3(G), dim3(kThr), 0, s, a);
         if (!one) hipLaunchKernelGGL(sum_rows, dim3(1), dim3(kSmallThr), 0, s, a.part, int64_t(G), 1, &T.N[j + 1].x);
         ED_L(hipGetLastError());
     }

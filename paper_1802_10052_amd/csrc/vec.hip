@@ -249,7 +249,7 @@ struct Scales {
 };
 
 // part[b][i] = sum_x conj(u_i[x]) w[x] over block b's chunk, i < n <= kDotGroup
-template <int NG>
+template <int NG, bool NT>
 __global__ __launch_bounds__(kThreads) void dot_partial_ptr(VecPtrs U, int n, const double2* __restrict__ w,
                                                             int64_t D, double2* __restrict__ part, int part_ld) {
     __shared__ double lds[kWaves * 2 * NG];
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kThreads) void dot_partial_ptr(VecPtrs U, int n, co
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
             if (i < n) {
-                const double2 v = U.p[i][x];
+                const double2 v = load_vec<NT>(U.p[i] + x);
                 a[2 * i] = fma(v.x, y.x, fma(v.y, y.y, a[2 * i]));
                 a[2 * i + 1] = fma(v.x, y.y, fma(-v.y, y.x, a[2 * i + 1]));
             }
@@ -279,7 +279,8 @@ __global__ __launch_bounds__(kThreads) void dot_partial_ptr(VecPtrs U, int n, co
 
 // One sweep of w against up to kChunk basis vectors: w -= sum_i (s_i coef[i]) u_i (coef device,
 // s host). Every element of w is read and written once whatever n is; the vectors are loaded 8
-// at a time with all loads of a group issued before use. NORM: part[b][0] = sum |w_new|^2 over
+// at a time with all loads of a group issued before use (no vector is read twice: a repeated
+// non-temporal read goes to memory again). NORM: part[b][0] = sum |w_new|^2 over
 // block b's chunk. KEEP (> 0): the values of the first KEEP vectors stay in registers and
 // part[b][i] = sum conj(u_i) w_new over the chunk for i < min(n, KEEP): the dots of the next
 // Gram-Schmidt pass, taken in the same sweep.
@@ -288,7 +289,7 @@ struct ChunkArgs {
     double s[kChunk];
 };
 
-template <bool NORM, int KEEP>
+template <bool NORM, int KEEP, bool NT>
 __global__ __launch_bounds__(kThreads) void sub_sweep(ChunkArgs U, int n, const double2* __restrict__ coef,
                                                       double2* __restrict__ w, int64_t D,
                                                       double2* __restrict__ part, int part_ld) {
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(kThreads) void sub_sweep(ChunkArgs U, int n, const 
         int i0 = 0;
         if constexpr (KEEP > 0) {
 #pragma unroll
-            for (int i = 0; i < KEEP; ++i) keep[i] = U.p[i < n ? i : 0][x];
+            for (int i = 0; i < KEEP; ++i) keep[i] = i < n ? load_vec<NT>(U.p[i] + x) : make_double2(0.0, 0.0);
 #pragma unroll
             for (int i = 0; i < KEEP; ++i) {
                 if (i < n) {
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(kThreads) void sub_sweep(ChunkArgs U, int n, const 
         for (; i0 < n; i0 += G) {
             double2 v[G];
 #pragma unroll
-            for (int i = 0; i < G; ++i) v[i] = U.p[i0 + i < n ? i0 + i : i0][x];
+            for (int i = 0; i < G; ++i) v[i] = i0 + i < n ? load_vec<NT>(U.p[i0 + i] + x) : make_double2(0.0, 0.0);
 #pragma unroll
             for (int i = 0; i < G; ++i) {
                 if (i0 + i < n) {
@@ -576,15 +577,18 @@ hipError_t set_scalar(double2* dst, double2 v, hipStream_t s) {
 
 hipError_t dots_ptr(const double2* const* U, int n, const double2* w, int64_t D, double2* out, double2* part,
                     hipStream_t s) {
+    const bool nt = outgrows_cache(n + 1, D);
     const int G = grid_for(D);
     for (int i0 = 0; i0 < n; i0 += kDotGroup) {
         const int nn = n - i0 < kDotGroup ? n - i0 : kDotGroup;
         VecPtrs vp;
         for (int i = 0; i < kDotGroup; ++i) vp.p[i] = i < nn ? U[i0 + i] : nullptr;
         if (nn <= 4) {
-            hipLaunchKernelGGL((dot_partial_ptr<4>), dim3(G), dim3(kThreads), 0, s, vp, nn, w, D, part, kPartLd);
+            hipLaunchKernelGGL((nt ? dot_partial_ptr<4, true> : dot_partial_ptr<4, false>), dim3(G), dim3(kThreads),
+                               0, s, vp, nn, w, D, part, kPartLd);
         } else {
-            hipLaunchKernelGGL((dot_partial_ptr<kDotGroup>), dim3(G), dim3(kThreads), 0, s, vp, nn, w, D, part, kPartLd);
+            hipLaunchKernelGGL((nt ? dot_partial_ptr<kDotGroup, true> : dot_partial_ptr<kDotGroup, false>), dim3(G),
+                               dim3(kThreads), 0, s, vp, nn, w, D, part, kPartLd);
         }
         hipLaunchKernelGGL(reduce_partials, dim3(nn), dim3(kThreads), 0, s, part, kPartLd, G, out + i0, nullptr);
     }
@@ -593,6 +597,7 @@ hipError_t dots_ptr(const double2* const* U, int n, const double2* w, int64_t D,
 
 hipError_t axpy_norm_ptr(const double2* const* U, int n, const double2* coef, const double* scale, double2* w,
                          int64_t D, double2* nrm_out, double2* part, hipStream_t s) {
+    const bool nt = outgrows_cache(n + 1, D);
     const int G = grid_for(D);
     for (int i0 = 0; i0 < n || i0 == 0; i0 += kChunk) {
         const int nn = n - i0 < kChunk ? n - i0 : kChunk;
@@ -603,12 +608,12 @@ hipError_t axpy_norm_ptr(const double2* const* U, int n, const double2* coef, co
             ca.s[i] = i < nn ? scale[i0 + i] : 0.0;
         }
         if (last) {
-            hipLaunchKernelGGL((sub_sweep<true, 0>), dim3(G), dim3(kThreads), 0, s, ca, nn, coef + i0, w, D, part,
-                               kPartLd);
+            hipLaunchKernelGGL((nt ? sub_sweep<true, 0, true> : sub_sweep<true, 0, false>), dim3(G), dim3(kThreads),
+                               0, s, ca, nn, coef + i0, w, D, part, kPartLd);
             hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part, kPartLd, G, nrm_out, nullptr);
         } else {
-            hipLaunchKernelGGL((sub_sweep<false, 0>), dim3(G), dim3(kThreads), 0, s, ca, nn, coef + i0, w, D, part,
-                               kPartLd);
+            hipLaunchKernelGGL((nt ? sub_sweep<false, 0, true> : sub_sweep<false, 0, false>), dim3(G), dim3(kThreads),
+                               0, s, ca, nn, coef + i0, w, D, part, kPartLd);
         }
         if (n == 0) break;
     }
@@ -617,6 +622,7 @@ hipError_t axpy_norm_ptr(const double2* const* U, int n, const double2* coef, co
 
 hipError_t axpy_dots_ptr(const double2* const* U, int n, const double2* coef, const double* scale, double2* w,
                          int64_t D, double2* dots_out, double2* part, hipStream_t s) {
+    const bool nt = outgrows_cache(n + 1, D);
     if (n > kChunk) {
         // the subtraction takes several sweeps: dots afterwards, in their own sweeps
         for (int i0 = 0; i0 < n; i0 += kChunk) {
@@ -626,8 +632,8 @@ hipError_t axpy_dots_ptr(const double2* const* U, int n, const double2* coef, co
                 ca.p[i] = i < nn ? U[i0 + i] : nullptr;
                 ca.s[i] = i < nn ? scale[i0 + i] : 0.0;
             }
-            hipLaunchKernelGGL((sub_sweep<false, 0>), dim3(grid_for(D)), dim3(kThreads), 0, s, ca, nn, coef + i0, w,
-                               D, part, kPartLd);
+            hipLaunchKernelGGL((nt ? sub_sweep<false, 0, true> : sub_sweep<false, 0, false>), dim3(grid_for(D)),
+                               dim3(kThreads), 0, s, ca, nn, coef + i0, w, D, part, kPartLd);
         }
         return dots_ptr(U, n, w, D, dots_out, part, s);
     }
@@ -637,8 +643,8 @@ hipError_t axpy_dots_ptr(const double2* const* U, int n, const double2* coef, co
         ca.p[i] = i < n ? U[i] : nullptr;
         ca.s[i] = i < n ? scale[i] : 0.0;
     }
-    hipLaunchKernelGGL((sub_sweep<false, kKeepDots>), dim3(G), dim3(kThreads), 0, s, ca, n, coef, w, D, part,
-                       kPartLd);
+    hipLaunchKernelGGL((nt ? sub_sweep<false, kKeepDots, true> : sub_sweep<false, kKeepDots, false>), dim3(G),
+                       dim3(kThreads), 0, s, ca, n, coef, w, D, part, kPartLd);
     const int nk = n < kKeepDots ? n : kKeepDots;
     hipLaunchKernelGGL(reduce_partials, dim3(nk), dim3(kThreads), 0, s, part, kPartLd, G, dots_out, nullptr);
     if (n > kKeepDots) return dots_ptr(U + kKeepDots, n - kKeepDots, w, D, dots_out + kKeepDots, part, s);
@@ -652,13 +658,15 @@ hipError_t axpy_dots_norm_ptr(const double2* const* U, int n, const double2* coe
         *ndots = 0;
         return axpy_norm_ptr(U, n, coef, scale, w, D, nrm_out, part, s);
     }
+    const bool nt = outgrows_cache(n + 1, D);
     const int G = grid_for(D);
     ChunkArgs ca;
     for (int i = 0; i < kChunk; ++i) {
         ca.p[i] = i < n ? U[i] : nullptr;
         ca.s[i] = i < n ? scale[i] : 0.0;
     }
-    hipLaunchKernelGGL((sub_sweep<true, kKeepDots>), dim3(G), dim3(kThreads), 0, s, ca, n, coef, w, D, part, kPartLd);
+    hipLaunchKernelGGL((nt ? sub_sweep<true, kKeepDots, true> : sub_sweep<true, kKeepDots, false>), dim3(G),
+                       dim3(kThreads), 0, s, ca, n, coef, w, D, part, kPartLd);
     const int nk = n < kKeepDots ? n : kKeepDots;
     hipLaunchKernelGGL(reduce_partials, dim3(nk), dim3(kThreads), 0, s, part, kPartLd, G, dots_out, nullptr);
     hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(kThreads), 0, s, part + kKeepDots, kPartLd, G, nrm_out, nullptr);
