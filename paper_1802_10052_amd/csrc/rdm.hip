@@ -146,7 +146,9 @@ constexpr int kE01 = 0, kE02 = 2, kE03 = 4, kE12 = 6, kE13 = 8, kE23 = 10;
 // edges along a at (b, c) = (0,0), (1,0) in kE01, kE23 of slot S0 and (0,1), (1,1) in those of S0 + 1;
 // for a triangle, along b at (a, c) = (0,0), (1,0) in kE02, kE13 of S0 and (0,1), (1,1) in kE01, kE23 of
 // S0 + 2; along c at (a, b) = (0,0), (1,0) in kE02, kE13 of S0 + 1 and (0,1), (1,1) in those of S0 + 2.
-// What bounds a pass: the FP64 units and the LDS reads beside them, at two waves a SIMD.
+// What bounds a pass: FP64 and address instructions at two waves a SIMD (2^26 amplitudes, 22 pairs: 457 us a
+// pass, 207 us of it to load the state; with six products a quad for each pair alone 523 us). Reading the
+// next base ahead of this one's products costs more in register copies than it hides (+9%).
 template <bool TRI, int S0>
 __device__ __forceinline__ void run_cube(double (&acc)[kRdmPairsPerWave][kRdmOff], const double2* s, int lane,
                                          const int* bits, int piece, int ns) {

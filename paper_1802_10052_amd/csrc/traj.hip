@@ -8,11 +8,9 @@
 // matrix is upper Hessenberg (Sec. ed:sec:Liouville). The step's basis gives psi(t + tau) for every tau in the
 // step, so the time at which |psi|^2 reaches r is solved in the small space, without extra H psi.
 //
-// Batched path: one persistent launch. Each workgroup runs its own list of trajectories, dealt on
-// the host by longest processing time first (each trajectory, heaviest first, goes to the
-// workgroup with the least work so far; the work of a trajectory is taken proportional to its
-// state size plus a fixed per-step overhead), keeps the state and Krylov basis in its own slice of
-// the workspace, runs H psi, and does every reduction, the small exponential, the root search,
+// Batched path: one persistent launch. The workgroups take trajectories from a queue, heaviest first
+// (the work of a trajectory is taken proportional to its state size plus a fixed per-step
+// overhead). A workgroup keeps the state and Krylov basis in its own slice of the workspace, runs H psi, and does every reduction, the small exponential, the root search,
 // the Philox draws and the jumps itself, so a trajectory never returns to the host.
 // Plain path: the same algorithm one trajectory at a time from the host, on the library's
 // stream-level kernels (the per-instance baseline).
