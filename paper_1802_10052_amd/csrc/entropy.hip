@@ -712,7 +712,7 @@ __global__ __launch_bounds__(256) void hh_flush(T* __restrict__ A, int n, int s,
 constexpr int kResRows = 8;
 constexpr int kResMaxN = 2048;             // 256 workgroups of 8 rows; 512 threads of 4 columns
 constexpr int kResThreads = 512;
-constexpr unsigned kResSpins = 1u << 23;   // polls before a workgroup gives up
+constexpr unsigned kResSpins = 1u << 18;   // polls (about 0.2 s) before a workgroup gives up and the launches run
 // Arrivals are counted on up to 16 counters in lines of their own: one counter takes 256 additions in
 // turn, and a flag per workgroup makes every poll read 1 KB from a few channels (the wait was 3.8 us a
 // step).
