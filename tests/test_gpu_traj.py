@@ -204,8 +204,10 @@ def test_workgroup_widths_agree():
     few, many = run([14], [0] * 3), run([14], [0] * 300)
     assert few["n_jumps"].sum() > 0
     assert np.array_equal(few["n_jumps"], many["n_jumps"][:3])
-    assert np.array_equal(few["jump_site"], many["jump_site"][:3])
-    assert np.max(np.abs(few["jump_t"] - many["jump_t"][:3])) < 1e-12
+    for tr in range(3):  # entries past n_jumps are not written
+        nj = few["n_jumps"][tr]
+        assert np.array_equal(few["jump_site"][tr, :nj], many["jump_site"][tr, :nj])
+        assert np.allclose(few["jump_t"][tr, :nj], many["jump_t"][tr, :nj], rtol=0.0, atol=1e-12)
     assert np.max(np.abs(few["sz"] - many["sz"][:3])) < 1e-11
     mixed, short = run([9, 14], [0, 0, 0, 1]), run([9], [0] * 3)
     assert np.array_equal(mixed["n_jumps"][:3], short["n_jumps"])
