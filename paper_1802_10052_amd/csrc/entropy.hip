@@ -11,7 +11,8 @@
 //      GPU, in blocked form: a read-only matrix-vector sweep of the stored lower triangle per
 //      step, the last kPanel rank-2 updates kept pending in a panel and folded into the matrix
 //      every kPanel steps by one product on the matrix cores.
-//      Up to n = 2048 instead in one launch that holds the matrix in registers (hh_resident).
+//      The last 2048 rows (a smaller matrix whole) instead in one launch that holds them in registers
+//      (hh_resident).
 //   3. Eigenvalues of the tridiagonal matrix by multisection on Sturm counts on the GPU, 16 lanes
 //      or a whole wave per eigenvalue.
 // When every amplitude of the state has a zero imaginary part (a real state, such as the ground
@@ -709,6 +710,8 @@ __global__ __launch_bounds__(256) void hh_flush(T* __restrict__ A, int n, int s,
 // the three dependent launches of a blocked step take 21 us whatever the trailing size. Whole calls,
 // by launches and here: n = 16 356 and 173 us, n = 64 1.17 and 0.36 ms, n = 1024 20.8 and 6.4 ms,
 // n = 2048 47.5 and 18.1 ms (real 37.8 and 13.3 ms). 1024 threads of two columns spill at n = 2048.
+// A larger matrix enters it once the panel is folded with at most kResMaxN rows left (2047 of 4096, 8192):
+// n = 4096 132 and 109 ms (real 99.6 and 81.3 ms).
 constexpr int kResRows = 8;
 constexpr int kResMaxN = 2048;             // 256 workgroups of 8 rows; 512 threads of 4 columns
 constexpr int kResThreads = 512;
@@ -745,11 +748,13 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 // leaf[kResLeafStride l]: steps published by the workgroups b = l mod (number of leaves), zero at launch;
-// *stop: set when a wait ran out. ybuf, cbuf: [2][n], of step parity.
-template <typename T, int NC>
-__global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__ A, int n, double* __restrict__ d,
-                                                           double* __restrict__ e, T* ybuf, T* cbuf, int* leaf,
-                                                           int* stop) {
+// *stop: set when a wait ran out. A: the lower triangle of n rows of lda entries. FROM (the trailing block
+// of a larger reduction): v0 is the first step's vector with its *tau0, formed already. ybuf, cbuf: [2][n], of step parity.
+template <typename T, int NC, bool FROM>
+__global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__ A, int n, int lda,
+                                                           const T* __restrict__ v0, const T* __restrict__ tau0,
+                                                           double* __restrict__ d, double* __restrict__ e, T* ybuf,
+                                                           T* cbuf, int* leaf, int* stop) {
     constexpr int NW = 16;  // the sums over the waves take 16 entries; those of absent waves stay zero
     static_assert(kResThreads / 64 <= NW, "waves");
     __shared__ T sh_v[kResRows], sh_w[kResRows];  // the last step's v and w at this workgroup's rows
@@ -772,40 +777,47 @@ __global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__
         const int j = t + TT * p;
         v[p] = zero;
         w[p] = zero;
-        col[p] = j < n ? A[int64_t(j) * n] : zero;
+        col[p] = j < n && !FROM ? A[int64_t(j) * lda] : zero;
 #pragma unroll
         for (int q = 0; q < kResRows; ++q) {
             const int i = b + G * q;
             a[q][p] = zero;
-            if (i < n && j < n) a[q][p] = j <= i ? A[int64_t(i) * n + j] : cj(A[int64_t(j) * n + i]);
+            if (i < n && j < n) a[q][p] = j <= i ? A[int64_t(i) * lda + j] : cj(A[int64_t(j) * lda + i]);
         }
     }
     __syncthreads();
-    for (int c = 0;; ++c) {
-        // the next Householder vector from column c (col, rows >= c)
-        double nx = 0.0;
+    constexpr int c0 = FROM ? -1 : 0;
+    for (int c = c0;; ++c) {
+        T tau, vn[NC];
+        if (!FROM || c >= 0) {
+            // the next Householder vector from column c (col, rows >= c)
+            double nx = 0.0;
 #pragma unroll
-        for (int p = 0; p < NC; ++p) {
-            const int j = t + TT * p;
-            if (j >= c + 2) nx += abs2(col[p]);
-            if (j == c) s_col[0] = col[p];
-            if (j == c + 1) s_col[1] = col[p];
-        }
-        nx = wave_sum(nx);
-        if (lane == 0) s_nx[wv] = nx;
-        __syncthreads();
-        if (b == 0 && t == 0) d[c] = re(s_col[0]);
-        if (c + 1 >= n) return;
-        nx = sum16(s_nx[lane & 15]);
-        T tau, inv;
-        double beta;
-        reflector(s_col[1], nx, &tau, &beta, &inv);
-        if (b == 0 && t == 0) e[c] = fabs(beta);
-        T vn[NC];
+            for (int p = 0; p < NC; ++p) {
+                const int j = t + TT * p;
+                if (j >= c + 2) nx += abs2(col[p]);
+                if (j == c) s_col[0] = col[p];
+                if (j == c + 1) s_col[1] = col[p];
+            }
+            nx = wave_sum(nx);
+            if (lane == 0) s_nx[wv] = nx;
+            __syncthreads();
+            if (b == 0 && t == 0) d[c] = re(s_col[0]);
+            if (c + 1 >= n) return;
+            nx = sum16(s_nx[lane & 15]);
+            T inv;
+            double beta;
+            reflector(s_col[1], nx, &tau, &beta, &inv);
+            if (b == 0 && t == 0) e[c] = fabs(beta);
 #pragma unroll
-        for (int p = 0; p < NC; ++p) {
-            const int j = t + TT * p;
-            vn[p] = j > c + 1 ? mul(col[p], inv) : j == c + 1 ? mk<T>(1.0, 0.0) : zero;
+            for (int p = 0; p < NC; ++p) {
+                const int j = t + TT * p;
+                vn[p] = j > c + 1 ? mul(col[p], inv) : j == c + 1 ? mk<T>(1.0, 0.0) : zero;
+            }
+        } else {
+            tau = *tau0;
+#pragma unroll
+            for (int p = 0; p < NC; ++p) vn[p] = t + TT * p < n ? v0[t + TT * p] : zero;
         }
         // the last step's rank-2 term, and A v, on this workgroup's rows > c; rows q and q + 4 fold
         // into one register each, four lane halves
@@ -821,7 +833,7 @@ __global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__
                     const T vi = sh_v[q], wi = sh_w[q];
 #pragma unroll
                     for (int p = 0; p < NC; ++p) {
-                        if (c > 0) {
+                        if (c > c0) {
                             sub_mul_cj(a[q][p], vi, w[p]);
                             sub_mul_cj(a[q][p], wi, v[p]);
                         }
@@ -856,7 +868,7 @@ __global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__
                                        __HIP_MEMORY_SCOPE_AGENT);
             unsigned spins = 0;
             for (;;) {
-                const bool there = lane >= leaves || ld_shared(leaf + kResLeafStride * lane) >= (c + 1) * per_leaf;
+                const bool there = lane >= leaves || ld_shared(leaf + kResLeafStride * lane) >= (c - c0 + 1) * per_leaf;
                 if (__all(there)) break;
                 if (++spins > kResSpins || (spins % 256 == 0 && ld_shared(stop) != 0)) {
                     if (lane == 0) {
@@ -1098,7 +1110,11 @@ ed_status gram(const EntWS<T>& w, const double2* p, bool left_small, int n, int6
     return ED_OK;
 }
 
-int resident_groups(int n) { return std::max(1, n / kResRows); }
+int resident_groups(int n) {  // a power of two
+    int G = 1;
+    while (G * kResRows < n) G *= 2;
+    return G;
+}
 // the resident reduction's counters, after its four vectors in the panel area, and the stop flag
 template <typename T>
 int* resident_leaves(const EntWS<T>& w, int n) {
@@ -1109,26 +1125,27 @@ int* resident_stop(const EntWS<T>& w, int n) {
     return resident_leaves(w, n) + kResLeafStride * std::min(resident_groups(n), kResLeaves);
 }
 
-// Step 2 by the resident reduction; *ran = false when the matrix is too large for it or its workgroups
-// cannot all be resident now. It only reads rho, so the launches below can follow it.
+// Step 2 by the resident reduction, of rho's rows and columns >= s0 (n of them; s0 > 0: from the vector
+// in w.vn and its tau, with nothing pending in the panel); *ran = n, or 0 when its workgroups cannot all
+// be resident now. It only reads rho, w.vn and tau, so the launches can go on from there instead.
 template <typename T>
-ed_status tridiagonal_resident(const EntWS<T>& w, int n, bool* ran, hipStream_t s) {
-    *ran = false;
-    if (n < 2 || n > kResMaxN) return ED_OK;
-    int nn = n;
+ed_status tridiagonal_resident(const EntWS<T>& w, int N, int s0, int* ran, hipStream_t s) {
+    *ran = 0;
+    int n = N - s0, lda = N;
     const int G = resident_groups(n);
     // 4 n entries and at most (n / 8) lines of 256 bytes, one at least, and the flag
     static_assert(kPW * sizeof(double2) >= 4 * sizeof(double2) + kResLeafStride * sizeof(int) / 2 + sizeof(int), "panel area");
-    const T* A = w.rho;
-    double *d = w.d, *e = w.e;
+    const T *A = w.rho + size_t(s0) * (N + 1), *v0 = s0 > 0 ? w.vn + s0 : nullptr, *tau0 = w.sc;
+    double *d = w.d + s0, *e = w.e + s0;
     T *yb = w.panel, *cb = w.panel + 2 * size_t(n);
     int *leaf = resident_leaves(w, n), *stop = resident_stop(w, n);
     hipLaunchKernelGGL(clear_flags, dim3(1), dim3(256), 0, s, leaf, int(stop - leaf) + 1);
-    void* params[] = {&A, &nn, &d, &e, &yb, &cb, &leaf, &stop};
-    const void* f = n > 2 * kResThreads ? reinterpret_cast<const void*>(&hh_resident<T, 4>)
-                    : n > kResThreads   ? reinterpret_cast<const void*>(&hh_resident<T, 2>)
-                                        : reinterpret_cast<const void*>(&hh_resident<T, 1>);
-    const int threads = std::min(kResThreads, std::max(64, n));
+    void* params[] = {&A, &n, &lda, &v0, &tau0, &d, &e, &yb, &cb, &leaf, &stop};
+    const void* f = s0 > 0                ? reinterpret_cast<const void*>(&hh_resident<T, 4, true>)
+                    : n > 2 * kResThreads ? reinterpret_cast<const void*>(&hh_resident<T, 4, false>)
+                    : n > kResThreads     ? reinterpret_cast<const void*>(&hh_resident<T, 2, false>)
+                                          : reinterpret_cast<const void*>(&hh_resident<T, 1, false>);
+    const int threads = std::min(kResThreads, (n + 63) / 64 * 64);
     const hipError_t err = hipLaunchCooperativeKernel(f, dim3(G), dim3(threads), params, 0, s);
     if (err == hipErrorCooperativeLaunchTooLarge) {
         (void)hipGetLastError();
@@ -1136,15 +1153,23 @@ ed_status tridiagonal_resident(const EntWS<T>& w, int n, bool* ran, hipStream_t 
     }
     if (err != hipSuccess)
         return fail(ED_ERR_HIP, std::string("resident tridiagonalisation launch: ") + hipGetErrorString(err));
-    *ran = true;
+    *ran = n;
     return ED_OK;
 }
 
-// Step 2 by launches: the reduction of rho to the tridiagonal (w.d, w.e), all on stream s.
+// Step 2: the reduction of rho to the tridiagonal (w.d, w.e), all on stream s. resident: the trailing block
+// of at most kResMaxN rows (the whole matrix up to there) in one launch, *ran = its rows (0: it could
+// not be launched); the steps before it by launches.
 template <typename T>
-ed_status tridiagonal(const EntWS<T>& w0, int n, hipStream_t s) {
+ed_status tridiagonal(const EntWS<T>& w0, int n, bool resident, int* ran, hipStream_t s) {
     EntWS<T> w = w0;
+    *ran = 0;
     if (n < 2) return ED_OK;
+    if (resident && n <= kResMaxN) {
+        ED_TRY(tridiagonal_resident(w, n, 0, ran, s));
+        if (*ran > 0) return ED_OK;
+        resident = false;
+    }
     ED_HIP_TRY(hipMemsetAsync(w.v, 0, size_t(n) * sizeof(T), s));
     ED_HIP_TRY(hipMemsetAsync(w.y, 0, size_t(n) * sizeof(T), s));
     ED_HIP_TRY(hipMemsetAsync(w.vn, 0, size_t(n) * sizeof(T), s));
@@ -1155,6 +1180,11 @@ ed_status tridiagonal(const EntWS<T>& w0, int n, hipStream_t s) {
                        static_cast<T*>(nullptr));
     int np = 0;  // pending pairs in the panel
     for (int k = 0; k + 1 < n; ++k) {
+        if (resident && np == 0 && n - k - 1 <= kResMaxN) {  // every earlier update is in rho
+            ED_TRY(tridiagonal_resident(w, n, k + 1, ran, s));
+            if (*ran > 0) return ED_OK;
+            resident = false;
+        }
         // the current vector (rows >= k+1) becomes v; the trailing block is rows/cols >= k+1
         std::swap(w.v, w.vn);
         const int s0 = k + 1;
@@ -1242,14 +1272,10 @@ ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, do
         ED_HIP_TRY(hipMemcpyAsync(dd.data(), wr.rho, sizeof(double), hipMemcpyDeviceToHost, s));
         ED_HIP_TRY(hipStreamSynchronize(s));
     } else {
-        bool resident = false;
-        if (real) ED_TRY(tridiagonal_resident<double>(wr, n, &resident, s));
-        else ED_TRY(tridiagonal_resident<double2>(wc, n, &resident, s));
-        for (;; resident = false) {
-            if (!resident) {
-                if (real) ED_TRY(tridiagonal<double>(wr, n, s));
-                else ED_TRY(tridiagonal<double2>(wc, n, s));
-            }
+        for (bool resident = true;; resident = false) {
+            int ran = 0;
+            if (real) ED_TRY(tridiagonal<double>(wr, n, resident, &ran, s));
+            else ED_TRY(tridiagonal<double2>(wc, n, resident, &ran, s));
             // 3. eigenvalues of the tridiagonal matrix by bisection on the GPU (the partial-sum area is
             // free now: n eigenvalues, n squared off-diagonals, 4 bounds), sorted on the host
             double* lam = wr.part;
@@ -1262,13 +1288,16 @@ ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, do
                                bnd, lam);
             ED_HIP_TRY(hipGetLastError());
             int gave_up = 0;
-            if (resident) {
-                const int* stop = real ? resident_stop(wr, n) : resident_stop(wc, n);
+            if (ran > 0) {
+                const int* stop = real ? resident_stop(wr, ran) : resident_stop(wc, ran);
                 ED_HIP_TRY(hipMemcpyAsync(&gave_up, stop, sizeof(int), hipMemcpyDeviceToHost, s));
             }
             ED_HIP_TRY(hipMemcpyAsync(dd.data(), lam, sizeof(double) * n, hipMemcpyDeviceToHost, s));
             ED_HIP_TRY(hipStreamSynchronize(s));
-            if (gave_up == 0) break;  // else the resident workgroups did not all run: by launches
+            if (gave_up == 0) break;
+            // the resident workgroups did not all run: again from the Gram matrix, by launches
+            if (real) ED_TRY(gram<double>(wr, p, left_small, n, K, s));
+            else ED_TRY(gram<double2>(wc, p, left_small, n, K, s));
         }
         std::sort(dd.begin(), dd.end());
     }
