@@ -229,7 +229,7 @@ ed_status build_basis(const ed_model* mod, const double2* psi, double dt_err, co
                       bool alias, hipStream_t s) {
     const int mmax = p->m_max;
     const int guess = B->m;
-    B->T.sigma = three_term_scale(mod);
+    B->T.scale = three_term_scale(mod);
     ED_TRY(three_term_start(B->T, B->w, psi, alias, false, s));
     std::vector<double> a(mmax + 1), b(mmax + 1);
     std::vector<double2> hv(B->T.count());
@@ -255,8 +255,8 @@ ed_status build_basis(const ed_model* mod, const double2* psi, double dt_err, co
             const double hp =
                 j > 0 ? std::hypot(hS[2 * j + 1].x, hS[2 * j + 1].y) / std::sqrt(hN[j - 1].x * hN[j].x) : 0.0;
             a[j] = h.real();
-            b[j] = std::sqrt(std::max(hN[j + 1].x, 0.0) / hN[j].x) / B->T.sigma;
-            const bool brk = b[j] <= 1e-14 * std::max(std::max(std::abs(h), hp), 1e-300) || b[j] == 0.0;
+            bool brk = false;
+            ED_TRY(three_term_beta(hN, j, std::max(std::abs(h), hp), &b[j], &brk));
             m = j + 1;
             stop = brk || m >= mmax;
             if (p->m_fixed > 0) {

@@ -788,8 +788,8 @@ ed_status evolve_three_term(const ed_model* m, const Workspace& w, double2* psi,
                 const double bprev = j > 0 ? be[j - 1] : 0.0;
                 const cplx h(hS[2 * j].x / hN[j].x, hS[2 * j].y / hN[j].x);
                 al[j] = h.real();
-                be[j] = std::sqrt(std::max(hN[j + 1].x, 0.0) / hN[j].x) / T.sigma;
-                const bool brk = be[j] <= 1e-14 * std::max(std::max(std::abs(h), bprev), 1e-300) || be[j] == 0.0;
+                bool brk = false;
+                ED_TRY(three_term_beta(hN, j, std::max(std::abs(h), bprev), &be[j], &brk));
                 mm = j + 1;
                 if (p->fixed_m > 0) stop = brk || mm >= std::min(p->fixed_m, mmax);
                 else stop = brk || mm >= mmax;

@@ -114,21 +114,25 @@ ed_status start_vector(const Workspace& w, const double2* psi, double* nrm, hipS
 // out = sum_i xi_i v_i over the first m basis vectors (xi host); out may be u_0.
 ed_status combine_basis(const Workspace& w, int m, const double2* xi, double2* out, hipStream_t s);
 ed_status measure_state(const double2* psi, int L, const Workspace& w, double* sz, double* nrm, hipStream_t s);
-// Three-term recurrence with device scalars (three_term.hip). N[j].x = |u_j|^2, SP[2 j] = <u_j|H u_j>,
-// SP[2 j + 1] = <u_{j-1}|H u_j> (where taken), all in the workspace's scalar area right before the
+// Three-term recurrence with device scalars (three_term.hip). N[j].x = |u_j|^2, N[j + 1].y = s_j (the power
+// of two that scaled u_{j+1}), SP[2 j] = <u_j|H u_j>, SP[2 j + 1] = <u_{j-1}|H u_j> (where taken), all in the workspace's scalar area right before the
 // observables at kObs, so that one copy fetches everything. ticket: the sweeps' arrival counters at the
 // front of the scalar area, zero when no sweep runs.
 constexpr int kThreeTermFree = 140;  // scalars at the front that N and SP leave
 constexpr int kThreeTermMax = 256;  // basis dimensions whose scalars fit there
 struct ThreeTerm {
     int mmax = 0;
-    double sigma = 1.0;
+    double scale = 1.0;  // the model's, for the first step
     double2 *N = nullptr, *SP = nullptr;
     unsigned* ticket = nullptr;
     int count() const { return 3 * mmax + 2; }
 };
 ed_status three_term_init(const ed_model* m, const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s);
 double three_term_scale(const ed_model* m);
+// beta_j from the fetched scalars, and whether the space is invariant: beta_j <= 1e-14 hmax (hmax: the step's
+// largest projection). Every s_j keeps |u_{j+1}| near 1 for a beta_j near beta_{j-1}, so N_{j+1} leaves the
+// normal numbers only for a beta_j far below that bound; should it do so otherwise, ED_ERR_NUMERIC.
+ed_status three_term_beta(const double2* N, int j, double hmax, double* beta, bool* brk);
 // Basis vector 0: psi itself (alias) or a copy in slot 0, and N[0] unless it is known to hold |psi|^2.
 ed_status three_term_start(const ThreeTerm& T, const Workspace& w, const double2* psi, bool alias, bool have_norm,
                            hipStream_t s);

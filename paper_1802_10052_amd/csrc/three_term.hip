@@ -2,13 +2,16 @@
 // device, so that iterations run back to back: the host reads them once per batch, not once per
 // product.
 //
-// The basis is kept unnormalised: u_{j+1} = sigma (H u_j - a_j u_j - b_j u_{j-1}), with
-//   a_j = <u_j|H u_j> / N_j,   b_j = N_j / (sigma N_{j-1})   (N_j = |u_j|^2; the second is the previous
+// The basis is kept unnormalised: u_{j+1} = s_j (H u_j - a_j u_j - b_j u_{j-1}), with
+//   a_j = <u_j|H u_j> / N_j,   b_j = N_j / (s_{j-1} N_{j-1})   (N_j = |u_j|^2; the second is the previous
 // step's norm, for a Hermitian H), or b_j = <u_{j-1}|H u_j> / N_{j-1} where both projections are taken.
-// So alpha_j = a_j and beta_j = sqrt(N_{j+1} / N_j) / sigma, and every coefficient of a sweep comes
-// from device scalars that earlier kernels of the same stream wrote. sigma is a power of two at or
-// below 1 / |H|, so no norm grows along the recurrence and scaling by it is exact.
+// So alpha_j = a_j and beta_j = sqrt(N_{j+1} / N_j) / s_j, and every coefficient of a sweep comes
+// from device scalars that earlier kernels of the same stream wrote. s_j (kept in N[j+1].y) is the power
+// of two that brings |u_{j+1}| near 1 if beta_j is near beta_{j-1}; s_0 comes from a bound of |H|. Scaling by
+// it is exact. One factor for all steps would not do: a bound of |H| can be far above every beta (a
+// uniform field that only turns the phase), and the norms then underflow within a basis.
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 
 #include "ed_vec.h"
@@ -26,6 +29,19 @@ constexpr int kTicketBlocks = 1024;     // sweeps of at most this many workgroup
 constexpr int kTickets = 32;            // leaf counters of a sweep (and one root)
 constexpr int kTicketStride = 16;       // unsigneds between counters: 64 bytes
 constexpr int kOwnParts = 1024;         // per-tile partials that every workgroup of a sweep sums for itself
+
+// floor(log2 v) of a positive normal v (-1023 for zero and subnormals, 1024 for infinity and NaN)
+__device__ __forceinline__ int exponent_of(double v) {
+    return int((__double_as_longlong(v) >> 52) & 0x7ff) - 1023;
+}
+
+// s_j from N_j and, past the first step, N_{j-1} and s_{j-1}: |H u_j - ...| is about beta_{j-1} sqrt(N_j) =
+// N_j / (s_{j-1} sqrt(N_{j-1})). first: the model's scale, a power of two at or below 1 / |H|.
+__device__ __forceinline__ double step_scale(int j, double first, double nj, double nm, double sm) {
+    const int k = j == 0 ? exponent_of(first) - (exponent_of(nj) >> 1)
+                         : exponent_of(sm) - exponent_of(nj) + (exponent_of(nm) >> 1);
+    return __longlong_as_double(static_cast<long long>(min(max(k, -1000), 1000) + 1023) << 52);
+}
 
 // Sums of NA values over a workgroup of W waves; every thread receives them (fixed order).
 template <int NA, int W>
@@ -140,9 +156,9 @@ struct SubArgs {
     const double2* u;
     double2* y;
     int64_t D;
-    double2 *N, *SP;  // N_j in N[j].x; SP[2 j] = <u_j|y>, SP[2 j + 1] = <u_{j-1}|y>
+    double2 *N, *SP;  // N_j in N[j].x, s_{j-1} in N[j].y; SP[2 j] = <u_j|y>, SP[2 j + 1] = <u_{j-1}|y>
     int j, both;
-    double sigma;
+    double scale;     // the model's
     const double2* tiles;  // per-tile partials of <u_j|y> (and <u_{j-1}|y>), or null: SP holds the sums
     int ntiles;
     double* part;
@@ -186,10 +202,14 @@ __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
     const double nj = A.N[A.j].x;
     const double2 a = make_double2(p[0] / nj, p[1] / nj);
     double2 b = make_double2(0.0, 0.0);
+    double nm = 1.0, sm = 1.0;
     if (A.um1) {
-        const double nm = A.N[A.j - 1].x;
-        b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (A.sigma * nm), 0.0);
+        nm = A.N[A.j - 1].x;
+        sm = A.N[A.j].y;
+        b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (sm * nm), 0.0);
     }
+    const double sj = step_scale(A.j, A.scale, nj, nm, sm);
+    if (blockIdx.x == 0 && t == 0) A.N[A.j + 1].y = sj;
     double n2[1] = {0.0};
     const int64_t chunk = (A.D + gridDim.x - 1) / gridDim.x;
     const int64_t lo = int64_t(blockIdx.x) * chunk;
@@ -212,8 +232,8 @@ __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
             r.y -= a.x * v[u].y + a.y * v[u].x;
             r.x -= b.x * w[u].x - b.y * w[u].y;
             r.y -= b.x * w[u].y + b.y * w[u].x;
-            r.x *= A.sigma;
-            r.y *= A.sigma;
+            r.x *= sj;
+            r.y *= sj;
             A.y[x0 + u * kThr] = r;
             n2[0] = fma(r.x, r.x, fma(r.y, r.y, n2[0]));
         }
@@ -230,7 +250,7 @@ struct SmallArgs {
     int64_t D;
     double2 *N, *SP;
     int j0, nj;
-    double sigma;
+    double scale;
 };
 
 // Iterations j0 .. j0 + nj - 1 for a state of at most 2^12 amplitudes in one workgroup: u_j sits in
@@ -248,7 +268,7 @@ __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const
     __shared__ double lds1[kSmallThr / 64][1];
     const int t = threadIdx.x, D = int(A.D), L = A.L;
     double2 u[E], um1[E], diag[E];
-    double nj, nm = 1.0;
+    double nj, nm = 1.0, sm = 1.0;
     {
         const double2* src = A.j0 == 0 ? A.u0 : A.V + int64_t(A.j0) * A.D;
         const double2* prev = A.j0 == 1 ? A.u0 : A.V + int64_t(A.j0 - 1) * A.D;
@@ -305,6 +325,7 @@ __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const
         } else {
             nj = A.N[A.j0].x;
             nm = A.N[A.j0 - 1].x;
+            sm = A.N[A.j0].y;
             __syncthreads();
         }
     }
@@ -350,7 +371,8 @@ __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const
         group_sums<4, kSmallThr / 64>(p, lds);  // (its first barrier also ends the reads of s)
         const double2 a = make_double2(p[0] / nj, p[1] / nj);
         double2 b = make_double2(0.0, 0.0);
-        if (j > 0) b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (A.sigma * nm), 0.0);
+        if (j > 0) b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (sm * nm), 0.0);
+        sm = step_scale(j, A.scale, nj, nm, sm);
         double n2[1] = {0.0};
         double2* out = A.V + int64_t(j + 1) * A.D;
 #pragma unroll
@@ -361,8 +383,8 @@ __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const
             r.y -= a.x * u[e].y + a.y * u[e].x;
             r.x -= b.x * um1[e].x - b.y * um1[e].y;
             r.y -= b.x * um1[e].y + b.y * um1[e].x;
-            r.x *= A.sigma;
-            r.y *= A.sigma;
+            r.x *= sm;
+            r.y *= sm;
             n2[0] = fma(r.x, r.x, fma(r.y, r.y, n2[0]));
             um1[e] = u[e];
             u[e] = r;
@@ -377,7 +399,7 @@ __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const
         if (t == 0) {
             A.SP[2 * j] = make_double2(p[0], p[1]);
             A.SP[2 * j + 1] = make_double2(p[2], p[3]);
-            A.N[j + 1] = make_double2(nj, 0.0);
+            A.N[j + 1] = make_double2(nj, sm);
         }
     }
 }
@@ -484,10 +506,18 @@ double three_term_scale(const ed_model* m) {
     return std::ldexp(1.0, -e);
 }
 
+ed_status three_term_beta(const double2* N, int j, double hmax, double* beta, bool* brk) {
+    const double n1 = std::max(N[j + 1].x, 0.0);
+    *beta = std::sqrt(n1) / std::sqrt(N[j].x) / N[j + 1].y;
+    *brk = *beta <= 1e-14 * std::max(hmax, 1e-300) || *beta == 0.0;
+    if (!*brk && n1 < DBL_MIN) return fail(ED_ERR_NUMERIC, "a vector of the Krylov recurrence underflows");
+    return ED_OK;
+}
+
 ed_status three_term_init(const ed_model* m, const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s) {
     if (mmax > kThreeTermMax || kThreeTermFree + 3 * mmax + 2 > kObs) return fail(ED_ERR_UNSUPPORTED, "basis too large for device scalars");
     T->mmax = mmax;
-    T->sigma = three_term_scale(m);
+    T->scale = three_term_scale(m);
     T->N = w.scal + kObs - T->count();
     T->SP = T->N + mmax + 2;
     static_assert((kTickets + 1) * kTicketStride * sizeof(unsigned) <= kThreeTermFree * sizeof(double2), "scalar area");
@@ -547,7 +577,7 @@ ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace&
         a.SP = T.SP;
         a.j0 = j0;
         a.nj = nj;
-        a.sigma = T.sigma;
+        a.scale = T.scale;
         ED_L(launch_small<0>(m->op_class, a, m->d_site, m->d_bond, s));
         return ED_OK;
     }
@@ -563,7 +593,7 @@ ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace&
         a.SP = T.SP;
         a.j = j;
         a.both = both && j > 0 ? 1 : 0;
-        a.sigma = T.sigma;
+        a.scale = T.scale;
         a.tiles = nullptr;
         a.ntiles = 0;
         // the product's projections per tile go to the front of the partial buffer, the sweep's to its end

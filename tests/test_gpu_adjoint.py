@@ -108,3 +108,24 @@ def test_bond_sums_over_tiles(L):
             fd = (P.evolve_loss(m, Jp, p0, 0.1, w, **kw) - P.evolve_loss(m, Jm, p0, 0.1, w, **kw)) / (2 * h)
             got = float(np.sum(g[s, sel] * J[s, sel]))
             assert abs(got - fd) <= 1e-6 * max(abs(fd), float(np.max(np.abs(g * J)))), (L, s, sel, got, fd)
+
+
+@pytest.mark.parametrize("L", [12, 13])
+def test_gradient_unchanged_by_a_uniform_field(L):
+    """A uniform z field commutes with the XXZ bonds and the observable and only turns the phase of a
+    state in one Sz sector: loss and gradient are those without it. The field's rounding in alpha_j
+    (1e-11 at h = 1e4) over a slice of length 2 stays below 1e-8 of the largest gradient."""
+    print(f"adjoint strong field L={L}", flush=True)
+    J = E.adjoint_couplings(1, L - 1, 5)
+    psi0 = torch.from_numpy(E.product_state(L, E.neel_index(L))).to(DEV)
+    w = np.array([(-1) ** k for k in range(L)], np.float64) / L
+    bonds = dict(bond_ops=[E.SXSX + E.SYSY + 0.5 * E.SZSZ], bond_coef=np.ones((1, L - 1)))
+    for kw in (dict(tol=1e-12), dict(m_fixed=56)):
+        got = []
+        for h in (0.0, 1e4):
+            m = P.Model(E.ModelDesc(L, site_ops=[E.SZ], site_coef=np.full((1, L), h), **bonds))
+            got.append(P.evolve_adjoint(m, J, psi0, 2.0, w, substeps=1, quad_nodes=8, m_max=64, **kw))
+        (l0, g0), (l1, g1) = got
+        print("  ", kw, abs(l0 - l1), np.max(np.abs(g0 - g1)), np.max(np.abs(g0)), flush=True)
+        assert abs(l0 - l1) < 1e-8, (L, kw, l0, l1)
+        assert np.max(np.abs(g0 - g1)) < 1e-8 * np.max(np.abs(g0)), (L, kw)

@@ -384,3 +384,69 @@ def test_krylov_batched_iterations(L):
                     assert abs(obs["norm"][n] - np.sqrt(n2)) < 1e-9
                     assert np.max(np.abs(obs["sz"][n] - OO.sz_all(s, L))) < 1e-9
                     assert abs(obs["energy"][n] - np.vdot(s, H @ s).real / n2) < 1e-9 * max(1.0, abs(obs["energy"][n]))
+
+
+def _sector_evolution(L, dt):
+    """XXZ chain (J = 1, Delta = 0.5, no fields) from the Neel state: the exact state after dt by
+    diagonalisation of its Sz sector, and that sector's sum of sigma^z."""
+    H = OH.hamiltonian_sparse(E.xxz(L, 1.0, 0.5)).tocsr()
+    x = np.arange(1 << L)
+    down = np.array([bin(v).count("1") for v in x])
+    idx = x[down == down[E.neel_index(L)]]
+    w, U = np.linalg.eigh(H[idx][:, idx].toarray())
+    out = np.zeros(1 << L, np.complex128)
+    out[idx] = U @ (np.exp(-1j * dt * w) * U[np.searchsorted(idx, E.neel_index(L))].conj())
+    return out, L - 2 * down[E.neel_index(L)]
+
+
+@pytest.mark.parametrize("L", [12, 13])
+@pytest.mark.parametrize("h,dt,m_max", [(0.3, 2.0, 64), (1e3, 2.0, 64), (1e4, 2.0, 64), (1e5, 1.0, 40)])
+def test_krylov_strong_uniform_field(L, h, dt, m_max):
+    """A uniform z field only turns the phase of a state in one Sz sector, so the dimension of a step and
+    its error are those without the field, however far the field lifts a bound of |H| above the
+    recurrence's norms. One workgroup (L = 12) and separate launches (L = 13). alpha_j carries the
+    rounding of h L (1e-10 at most): 1e-9 on the state after dt."""
+    print(f"krylov strong field L={L} h={h}", flush=True)
+    ref, mz = _sector_evolution(L, dt)
+    ref = ref * np.exp(-1j * np.remainder(h * mz * dt, 2 * np.pi))
+    m = P.Model(E.xxz(L, 1.0, 0.5, np.full(L, h)))
+    for kw in (dict(tol=1e-10), dict(fixed_m=min(m_max, 56))):
+        psi = dev(E.product_state(L, E.neel_index(L)))
+        _, _, info = P.krylov_evolve(m, psi, dt, 1, m_max=m_max, **kw)
+        err = np.linalg.norm(psi.cpu().numpy() - ref)
+        print("  ", kw, info, err, flush=True)
+        assert err < 1e-9, (L, h, kw, info, err)
+        assert info["max_err"] > 0.0
+        if "fixed_m" in kw:
+            assert info["max_m"] == kw["fixed_m"]
+
+
+@pytest.mark.parametrize("L", [11, 13])
+@pytest.mark.parametrize("size", [1e-140, 1e140])
+def test_krylov_state_norms(L, size):
+    """The evolution is linear in the state's norm, over the range whose square is a normal number."""
+    m = P.Model(E.xxz(L, 1.0, 0.5, E.random_fields(L, 2)))
+    a, b = dev(E.random_state(L, 5)), dev(E.random_state(L, 5) * size)
+    P.krylov_evolve(m, a, 0.5, 2, fixed_m=40, m_max=40)
+    P.krylov_evolve(m, b, 0.5, 2, fixed_m=40, m_max=40)
+    assert torch.linalg.vector_norm(b / size - a) < 1e-12
+
+
+@pytest.mark.parametrize("L", [12, 13])
+def test_krylov_exact_breakdown(L):
+    """An eigenstate (all spins up, |H| far above the residual's rounding) and a two-dimensional
+    invariant space still end the basis: one and two vectors, no error."""
+    h = 1e4
+    psi = dev(E.product_state(L, 0))
+    m = P.Model(E.xxz(L, 1.0, 0.5, np.full(L, h)))
+    _, _, info = P.krylov_evolve(m, psi, 0.3, 1, m_max=20, tol=1e-10)
+    e = 0.5 * (L - 1) + h * L
+    assert info["max_m"] == 1 and info["max_err"] == 0.0
+    assert abs(psi[0].item() - np.exp(-1j * np.remainder(0.3 * e, 2 * np.pi))) < 1e-10
+    coef = np.zeros((1, L))
+    coef[0, 2] = 0.7            # sigma^x on one site: |0> and its flip
+    m = P.Model(E.ModelDesc(L, site_ops=[E.SX], site_coef=coef, bond_ops=[E.SZSZ], bond_coef=np.zeros((1, L - 1))))
+    psi = dev(E.product_state(L, 0))
+    _, _, info = P.krylov_evolve(m, psi, 0.3, 1, m_max=20, tol=1e-10)
+    assert info["max_m"] == 2 and info["max_err"] == 0.0
+    assert abs(psi[0].item() - np.cos(0.21)) < 1e-14 and abs(psi[1 << (L - 3)].item() + 1j * np.sin(0.21)) < 1e-14
