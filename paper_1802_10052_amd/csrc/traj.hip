@@ -535,8 +535,11 @@ __device__ __forceinline__ double from_lane(double v, int lane) {  // lane the s
 // The first wave does it alone, row t in lane t, and the others wait for its end: spread over the
 // workgroup it took four barriers a term, some eighty a call, and a call follows every product (ten
 // steps of 32 trajectories at L = 8: 1.73 ms, 2.00 ms that way; the 320 mixed ones 81 ms, 91 ms).
+// The leading barrier ends the other waves' reads of the last call's sh.u: the root search reads |u|^2 on
+// every wave and calls again at once, and a wave that read the next call's u would take another branch.
 __device__ void wg_expv(int m, double tau, Shared& sh) {
     constexpr int LD = kTMax + 1;
+    __syncthreads();
     if (threadIdx.x < 64) {
         const int t = threadIdx.x;
         double cs = 0.0;  // column t's absolute sum

@@ -212,3 +212,24 @@ def test_workgroup_widths_agree():
     mixed, short = run([9, 14], [0, 0, 0, 1]), run([9], [0] * 3)
     assert np.array_equal(mixed["n_jumps"][:3], short["n_jumps"])
     assert np.max(np.abs(mixed["sz"][:3, :, :9] - short["sz"])) < 1e-11
+
+
+@pytest.mark.parametrize("n_traj", [16, 300])
+def test_jump_times_repeat(n_traj):
+    """Many jumps in workgroups of either width: the root search calls the small exponential back to
+    back, and its waves must leave each evaluation together. Jump times from the draws alone (1e-8, as
+    above), and every repeat equal to the last bit."""
+    print(f"trajectory jump times n={n_traj}", flush=True)
+    L, dt, steps, seed = 14, 0.05, 60, 9
+    models, rates, psi0, mo = setup_batch([L], n_traj, seed)
+    first = None
+    for _ in range(3):
+        res = P.trajectories(models, E.SMINUS, rates, psi0, mo, dt, steps, 20, seed, m_max=24, tol=1e-10)
+        for tr in range(n_traj):
+            exp_t = expected_jump_times(seed, tr, L, dt * steps)
+            assert res["n_jumps"][tr] == len(exp_t), tr
+            assert np.allclose(res["jump_t"][tr, :len(exp_t)], exp_t, rtol=0, atol=1e-8)
+        if first is not None:
+            assert np.array_equal(res["sz"], first["sz"]) and np.array_equal(res["n_jumps"], first["n_jumps"])
+        first = res
+    assert first["n_jumps"].sum() >= n_traj
