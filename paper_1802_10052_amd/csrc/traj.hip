@@ -1015,11 +1015,6 @@ static double heff_bound(const ed_model* m) {
     return b;
 }
 
-// Workgroups of the persistent launch: as many as can be resident at once for the kernel variant
-// (the deal is static, so a workgroup that had to wait for a free slot would finish late), at
-// most one per trajectory, and at most what a 32 GiB scratch budget holds (each workgroup keeps a
-// state and its Krylov basis: (m_max + 2) 2^Lmax amplitudes). variant < 0: the largest count over
-// the variants (used to size the workspace).
 static int cu_count() {
     int dev = 0, cu = 256, v = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -1058,13 +1053,20 @@ static int resident_per_cu(int variant, int threads) {
     }
 }
 
+// Workgroups of the persistent launch: as many as can be resident at once for the kernel variant and
+// width (one that had to wait for a free slot would find the queue empty), at most one per
+// trajectory, and at most what a 32 GiB scratch budget holds (each workgroup keeps a state and its
+// Krylov basis: (m_max + 2) 2^Lmax amplitudes). variant < 0: the largest count over the variants and
+// widths, which sizes the workspace: it depends on the models and the number of trajectories, not on
+// which trajectory has which model.
 static int persistent_blocks(const ed_traj_desc* d, int Lmax, int m_max, int variant) {
-    const int n_traj = std::max(d->n_traj, 1), cu = cu_count(), threads = traj_threads(d);
+    const int n_traj = std::max(d->n_traj, 1), cu = cu_count();
     int per_cu = 1;
     if (variant >= 0) {
-        per_cu = resident_per_cu<0>(variant, threads);
+        per_cu = resident_per_cu<0>(variant, traj_threads(d));
     } else {
-        for (int v = 0; v < kNumVariants; ++v) per_cu = std::max(per_cu, resident_per_cu<0>(v, threads));
+        for (int v = 0; v < kNumVariants; ++v)
+            for (int threads : {kTT, kWideTT}) per_cu = std::max(per_cu, resident_per_cu<0>(v, threads));
     }
     const double per_bytes = double(m_max + 2) * double(int64_t(1) << Lmax) * sizeof(double2);
     const int64_t by_mem = std::max<int64_t>(1, int64_t((double(int64_t(32) << 30)) / per_bytes));

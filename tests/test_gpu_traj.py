@@ -233,3 +233,16 @@ def test_jump_times_repeat(n_traj):
             assert np.array_equal(res["sz"], first["sz"]) and np.array_equal(res["n_jumps"], first["n_jumps"])
         first = res
     assert first["n_jumps"].sum() >= n_traj
+
+
+def test_workspace_of_any_assignment(monkeypatch):
+    """The workspace is sized by the models and the number of trajectories: a program that sized it once
+    may run any assignment of the same models in it (600 trajectories: more than one per CU)."""
+    sizes, alloc = [], P._workspace
+    monkeypatch.setattr(P, "_workspace", lambda n, dev: (sizes.append(n), alloc(n, dev))[1])
+    models, rates, psi0, _ = setup_batch([8, 14], 600)
+    for n_long in (0, 1, 600):
+        mo = np.zeros(600, np.int32)
+        mo[:n_long] = 1
+        P.trajectories(models, E.SMINUS, rates, psi0, mo, 0.01, 1, 1, 3, m_max=10)
+    assert sizes[0] == sizes[1] == sizes[2], sizes
