@@ -1023,17 +1023,35 @@ static int cu_count() {
     return cu;
 }
 
-// Threads of a trajectory workgroup. A workgroup's rate is set by the loads it keeps in flight: where
-// the long chains (14 sites and more) of a batch are no more than the CUs, each takes a CU to itself
-// with 1024 threads (320 trajectories of L = 8..16, ten steps: 91 ms, 132 ms with 256 threads; 256 at
-// L = 14: 24 ms). More
-// of them fill the chip with 256 threads each, two workgroups per CU, whose queue ends more evenly
-// (300 at L = 14: 37 and 40 ms), and short chains have too little work for 1024 (300 at L = 12:
-// 7.4 and 12.2 ms).
+// Cost of a trajectory in amplitude-equivalents per step: its products and sweeps stream the state, and
+// a step has a fixed cost of reductions and barriers.
+static double traj_cost(int L) {
+    constexpr double kStepOverhead = 2048.0;
+    return double(int64_t(1) << L) + kStepOverhead;
+}
+
+// Threads of a trajectory workgroup. A workgroup's rate is set by the loads it keeps in flight, so a
+// long chain (14 sites and more) is done sooner in a workgroup of 1024 threads that has a CU to itself
+// (ten steps of one chain of 14 and 16 sites: 11.2 and 50 ms, 15.5 and 86 ms with 256), and a short one
+// takes more of a CU there (1024 chains of 8 and 12 sites: 9.5 and 21.8 ms, 3.4 and 16.2 ms with 256,
+// two workgroups per CU). In wide workgroups a batch lasts as long as its whole work over the CUs; in
+// narrow ones at least as long as its longest chain, whose time per amplitude is 1.25 times that of
+// the wide one. Wide where the first is the smaller (300 chains of 12 sites and one of 14: 13.0 and
+// 17.4 ms; 320 of 8 to 16: 79 and 128 ms), narrow elsewhere (4000 of 8 sites and one of 14: 36.6 and
+// 19.6 ms; 2000 of 10 and one of 14: 24.9 and 19.2 ms), and narrow with more long chains than CUs, where
+// a second round of them would end unevenly (300 at L = 14: 40 and 37 ms).
 static int traj_threads(const ed_traj_desc* d) {
-    int64_t wide = 0;
-    for (int t = 0; t < d->n_traj; ++t) wide += d->models[d->model_of_traj[t]]->L >= kWideL;
-    return wide > 0 && wide <= cu_count() ? kWideTT : kTT;
+    int64_t n_long = 0;
+    int longest = 0;
+    double work = 0.0;
+    for (int t = 0; t < d->n_traj; ++t) {
+        const int L = d->models[d->model_of_traj[t]]->L;
+        n_long += L >= kWideL;
+        longest = std::max(longest, L);
+        work += traj_cost(L);
+    }
+    if (n_long == 0 || n_long > cu_count()) return kTT;
+    return work <= 1.25 * cu_count() * double(int64_t(1) << longest) ? kWideTT : kTT;
 }
 
 template <int I>
@@ -1078,17 +1096,14 @@ static int persistent_blocks(const ed_traj_desc* d, int Lmax, int m_max, int var
 static std::mutex g_traj_graph_mu;
 static std::map<std::pair<int, hipStream_t>, hipGraphExec_t> g_traj_graph;
 
-// The queue of the batched launch: trajectories by decreasing cost, a trajectory's cost being
-// 2^L + kStepOverhead amplitude-equivalents per step (its products and sweeps stream the state; a
-// step also has a fixed cost of reductions and barriers). Workgroups take them in this order as
+// The queue of the batched launch: trajectories by decreasing cost. Workgroups take them in this order as
 // they finish (longest processing time first, list scheduling), so the heavy ones start early
 // and the light ones fill the end.
 static void queue_order(const ed_traj_desc* d, std::vector<int>* ord) {
-    constexpr double kStepOverhead = 2048.0;
     const int nt = d->n_traj;
     ord->resize(nt);
     for (int i = 0; i < nt; ++i) (*ord)[i] = i;
-    auto cost = [&](int t) { return double(int64_t(1) << d->models[d->model_of_traj[t]]->L) + kStepOverhead; };
+    auto cost = [&](int t) { return traj_cost(d->models[d->model_of_traj[t]]->L); };
     std::stable_sort(ord->begin(), ord->end(), [&](int x, int y) { return cost(x) > cost(y); });
 }
 

@@ -246,3 +246,19 @@ def test_workspace_of_any_assignment(monkeypatch):
         mo[:n_long] = 1
         P.trajectories(models, E.SMINUS, rates, psi0, mo, 0.01, 1, 1, 3, m_max=10)
     assert sizes[0] == sizes[1] == sizes[2], sizes
+
+
+@pytest.mark.parametrize("n_short,L_short,wide", [(300, 12, True), (4000, 8, False), (2000, 10, False)])
+def test_width_follows_the_work(n_short, L_short, wide):
+    """One long chain does not put a batch of many short ones into wide workgroups (one per CU; narrow
+    ones run two per CU), and the results are those of the parts (1e-11, as for the widths above)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    models, rates, psi0, _ = setup_batch([L_short, 14], 1)
+    def run(mo):
+        return P.trajectories(models, E.SMINUS, rates, psi0, np.array(mo, np.int32), 0.02, 2, 2, 11, m_max=20, tol=1e-12)
+    both = run([0] * n_short + [1])
+    assert (both["info"]["blocks"] <= cus) == wide, both["info"]
+    short = run([0] * n_short)
+    assert short["info"]["blocks"] == min(n_short, 2 * cus)
+    assert np.array_equal(both["n_jumps"][:-1], short["n_jumps"])
+    assert np.max(np.abs(both["sz"][:-1] - short["sz"])) < 1e-11
