@@ -114,7 +114,8 @@ ed_status ed_model_passes(const ed_model* model, int* passes);
  * without neighbour reads), ordered by an estimated cost; the first is selected at creation.
  * A model of 12 to 19 sites (18 with single-flip bond terms) without long-range rules starts on a
  * direct product instead, one launch that gathers every partner amplitude through the caches;
- * ed_model_select_plan and a tuned plan that is faster replace it.
+ * ed_model_select_plan and a tuned or cached plan that is faster replace it. While it runs,
+ * ed_model_plans reports the plan that was selected last (which the direct product stands in for).
  * ed_model_tune times every candidate on the caller's device buffers psi, out (D amplitudes each,
  * `reps` products per candidate, HIP events on stream), selects the fastest and returns its
  * index and the per-candidate times (host, may be NULL; count from ed_model_plans). Selecting or
@@ -129,11 +130,13 @@ ed_status ed_model_tune(ed_model* model, const ed_c64* psi, ed_c64* out, int rep
 
 /* ----------------------------------------------------------------------------------------
  * Tuned-plan cache (host memory, process-wide). An entry maps a model's plan key to the
- * description of its fastest plan. The key names the GPU architecture, L, the operator class
+ * description of its fastest plan, followed by " direct" where the direct product was faster than
+ * every plan. The key names the GPU architecture, L, the operator class
  * (kernel variant), the Liouville and long-range flags and a hash of the model's whole candidate
  * list, so it applies only to models whose planner proposes the same candidates.
- *   ed_model_create / ed_liouville_create select the cached plan when the key has an entry whose
- *     plan is among the candidates (else the planner's first candidate, as without a cache);
+ *   ed_model_create / ed_liouville_create select the cached plan, and the direct product if the
+ *     entry says so and the model can run it, when the key has an entry whose plan is among the
+ *     candidates (else the default described above, as without a cache);
  *   ed_model_tune stores its choice under the model's key;
  *   ed_plan_cache_load merges "<key> TAB <plan>" lines from a text file ('#' starts a comment)
  *     and returns the number of entries read; ed_plan_cache_save writes every entry (replacing the

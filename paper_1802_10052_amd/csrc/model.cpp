@@ -551,7 +551,8 @@ ed_status validate_desc(const ed_model_desc* desc) {
 
 void apply_cached_plan(ed_model* m);
 
-ed_status create_model(const ed_model_desc* desc, ed_model** out) {
+// A model on its default product: what the plan cache holds for its key is not looked up here.
+static ed_status create_default(const ed_model_desc* desc, ed_model** out) {
     ED_TRY(validate_desc(desc));
     ed_model* m = new (std::nothrow) ed_model();
     if (!m) return fail(ED_ERR_NOMEM, "host allocation failed");
@@ -563,8 +564,13 @@ ed_status create_model(const ed_model_desc* desc, ed_model** out) {
         delete m;
         return st;
     }
-    apply_cached_plan(m);
     *out = m;
+    return ED_OK;
+}
+
+ed_status create_model(const ed_model_desc* desc, ed_model** out) {
+    ED_TRY(create_default(desc, out));
+    apply_cached_plan(*out);
     return ED_OK;
 }
 
@@ -649,7 +655,7 @@ ed_status create_liouville(const ed_model_desc* H, int n_jump, const ed_c64* jum
     d.bond_coef = bcoef.data();
     d.n_inf = 0;
     ed_model* m = nullptr;
-    ED_TRY(create_model(&d, &m));
+    ED_TRY(create_default(&d, &m));  // (the chain of 2L sites has another key)
     m->lv_L = L;
     // jump sandwiches i gamma J (x) J^*, row bit q = 2L - k, column bit p = L - k of site k
     for (int k = 1; k <= L; ++k) {
@@ -758,7 +764,11 @@ std::string plan_key(const ed_model* m) {
            " far=" + std::to_string(m->far.size()) + " cands=" + hex;
 }
 
-// Select the cached plan of m, if the cache holds one for its key (no-op otherwise).
+// A cached choice is a plan's description, followed by kDirectMark where the direct launch was faster than
+// every plan (the plan is then what the direct launch was compared with).
+constexpr const char* kDirectMark = " direct";
+
+// Select the cached choice of m, if the cache holds one for its key (no-op otherwise).
 void apply_cached_plan(ed_model* m) {
     std::string want;
     {
@@ -768,11 +778,13 @@ void apply_cached_plan(ed_model* m) {
         if (it == pc.map.end()) return;
         want = it->second;
     }
+    const size_t mark = std::strlen(kDirectMark);
+    const bool direct = want.size() > mark && want.compare(want.size() - mark, mark, kDirectMark) == 0;
+    if (direct) want.resize(want.size() - mark);
     for (int c = 0; c < m->n_cand; ++c) {
         if (describe_plan(m, c) == want) {
-            m->plan = c;
-            m->n_pass = m->cand_np[c];
-            for (int i = 0; i < m->n_pass; ++i) m->pass[i] = m->cand[c][i];
+            (void)ed_model_select_plan(m, c);
+            m->direct = direct && direct_fits(m);
             return;
         }
     }
@@ -780,7 +792,7 @@ void apply_cached_plan(ed_model* m) {
 
 void remember_plan(const ed_model* m) {
     PlanCache& pc = plan_cache();
-    const std::string key = plan_key(m), val = describe_plan(m, m->plan);
+    const std::string key = plan_key(m), val = describe_plan(m, m->plan) + (m->direct ? kDirectMark : "");
     std::lock_guard<std::mutex> lock(pc.mu);
     pc.map[key] = val;
 }

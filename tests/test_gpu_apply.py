@@ -179,3 +179,44 @@ def test_direct_product_equals_the_plans(L):
     best, _ = m.tune(psi, reps=2)
     assert m.plans[1] == best
     assert torch.linalg.vector_norm(P.apply_H(m, psi) - P.apply_H(P.Model(E.tfim(L, 0.5)), psi)) < 1e-12
+
+
+def test_cached_choice_runs_at_creation(tmp_path):
+    """A short chain starts on what the cache says: a plan, or the direct product where the entry ends
+    with " direct" (and the model can run it); a tuned handle and a new one run the same code; a
+    Liouvillian does not take the entry of the chain of as many bits."""
+    L = 16
+    new = lambda: P.Model(E.tfim(L, 0.5))
+    psi = E.random_state_device(L, 11, DEV)
+    try:
+        P.plan_cache_clear()
+        m = new()
+        key, ref = m.plan_key, P.apply_H(m, psi)
+        assert m.passes == 1 and m.plans[1] == 0
+        for mark, passes in (("", 2), (" direct", 1)):
+            P.plan_cache_put(key, m.describe_plan(3) + mark)
+            c = new()
+            assert (c.passes, c.plans[1]) == (passes, 3), mark
+            assert torch.linalg.vector_norm(P.apply_H(c, psi) - ref) < 1e-13
+        c.select_plan(3)
+        assert c.passes == 2
+        best, _ = m.tune(psi, reps=5)
+        assert P.plan_cache_get(key) == m.describe_plan(best) + (" direct" if m.passes == 1 else "")
+        P.plan_cache_save(tmp_path / "plans.tsv")
+        for reload in (False, True):
+            if reload:
+                P.plan_cache_clear()
+                assert P.plan_cache_load(tmp_path / "plans.tsv") == 1
+            c = new()
+            assert (c.passes, c.plans[1]) == (m.passes, best), reload
+        big = P.Model(E.tfim(21, 0.5))
+        P.plan_cache_put(big.plan_key, big.describe_plan(1) + " direct")
+        big = P.Model(E.tfim(21, 0.5))
+        assert (big.passes, big.plans[1]) == (2, 1)     # too long for the direct product: its plan
+        lv = P.Liouville(E.xxz(8, 1.0, 1.0), [], np.zeros((0, 8)))
+        P.plan_cache_put(lv.plan_key.replace("liouville=8", "liouville=0"), lv.describe_plan(2))
+        assert P.Liouville(E.xxz(8, 1.0, 1.0), [], np.zeros((0, 8))).plans[1] == 0
+    finally:
+        P.plan_cache_clear()
+        if os.path.exists(P._lib.DEFAULT_PLANS):
+            P.plan_cache_load(P._lib.DEFAULT_PLANS)
