@@ -348,12 +348,20 @@ ed_status ed_measure_noalloc(const ed_c64* psi, int L, double* sz, double* norm,
  * Workspace: ed_entropy_workspace (the Gram matrix, 16 * 4^min(l, L-l) bytes, plus vectors).
  * ed_entropy_ex: the same, and real_arith (host, may be NULL) is set to 1 when the real
  * arithmetic ran, else 0.
+ * ed_entropy_polls: the same with the limit of a wait chosen by the caller. The last 2048 rows of the
+ * reduction run in one launch whose workgroups wait for each other, each wait for at most `polls` looks
+ * (the other two calls use 2^18, about 0.2 s); a launch that is refused or a wait that runs out leaves
+ * the whole reduction to separate launches, with the same results to rounding. polls = 0 gives up at
+ * the first wait, polls < 0 never starts that launch (both for tests of the separate launches). route
+ * (host, may be NULL): 0 = separate launches only, 1 = the one launch ran, 2 = it gave up.
  * ---------------------------------------------------------------------------------------- */
 ed_status ed_entropy_workspace(int L, int l_cut, size_t* bytes);
 ed_status ed_entropy(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum, void* ws,
                      size_t ws_bytes, void* stream);
 ed_status ed_entropy_ex(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum, int* real_arith,
                         void* ws, size_t ws_bytes, void* stream);
+ed_status ed_entropy_polls(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum, int* real_arith,
+                           int polls, int* route, void* ws, size_t ws_bytes, void* stream);
 
 /* ----------------------------------------------------------------------------------------
  * Liouville space (Sec. ed:sec:Liouville, Eqs. ed:eq:lioutrafo, ed:eq:liousuperket, App. F). The density

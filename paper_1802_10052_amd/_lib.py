@@ -158,6 +158,8 @@ def _declare(l):
     _fn(l, "ed_entropy", [P, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_double), P, P, C.c_size_t, P])
     _fn(l, "ed_entropy_ex", [P, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_double), P, C.POINTER(C.c_int), P,
                              C.c_size_t, P])
+    _fn(l, "ed_entropy_polls", [P, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_double), P, C.POINTER(C.c_int), C.c_int,
+                                C.POINTER(C.c_int), P, C.c_size_t, P])
     _fn(l, "ed_measure", [P, C.c_int, P, P, P, C.c_size_t, P])
     _fn(l, "ed_measure_noalloc", [P, C.c_int, P, P, P])
     _fn(l, "ed_stream_copy", [P, P, C.c_int64, P])

@@ -750,11 +750,12 @@ __device__ __forceinline__ T wave_sum(T v) {
 // leaf[kResLeafStride l]: steps published by the workgroups b = l mod (number of leaves), zero at launch;
 // *stop: set when a wait ran out. A: the lower triangle of n rows of lda entries. FROM (the trailing block
 // of a larger reduction): v0 is the first step's vector with its *tau0, formed already. ybuf, cbuf: [2][n], of step parity.
+// polls: looks at the counters that one wait may take (0: the first wait gives up).
 template <typename T, int NC, bool FROM>
 __global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__ A, int n, int lda,
                                                            const T* __restrict__ v0, const T* __restrict__ tau0,
                                                            double* __restrict__ d, double* __restrict__ e, T* ybuf,
-                                                           T* cbuf, int* leaf, int* stop) {
+                                                           T* cbuf, int* leaf, int* stop, unsigned polls) {
     constexpr int NW = 16;  // the sums over the waves take 16 entries; those of absent waves stay zero
     static_assert(kResThreads / 64 <= NW, "waves");
     __shared__ T sh_v[kResRows], sh_w[kResRows];  // the last step's v and w at this workgroup's rows
@@ -868,15 +869,15 @@ __global__ __launch_bounds__(kResThreads) void hh_resident(const T* __restrict__
                                        __HIP_MEMORY_SCOPE_AGENT);
             unsigned spins = 0;
             for (;;) {
-                const bool there = lane >= leaves || ld_shared(leaf + kResLeafStride * lane) >= (c - c0 + 1) * per_leaf;
-                if (__all(there)) break;
-                if (++spins > kResSpins || (spins % 256 == 0 && ld_shared(stop) != 0)) {
+                if (++spins > polls || (spins % 256 == 0 && ld_shared(stop) != 0)) {
                     if (lane == 0) {
                         st_shared(stop, 1);
                         bad = 1;
                     }
                     break;
                 }
+                const bool there = lane >= leaves || ld_shared(leaf + kResLeafStride * lane) >= (c - c0 + 1) * per_leaf;
+                if (__all(there)) break;
             }
             drain();
         }
@@ -1129,7 +1130,7 @@ int* resident_stop(const EntWS<T>& w, int n) {
 // in w.vn and its tau, with nothing pending in the panel); *ran = n, or 0 when its workgroups cannot all
 // be resident now. It only reads rho, w.vn and tau, so the launches can go on from there instead.
 template <typename T>
-ed_status tridiagonal_resident(const EntWS<T>& w, int N, int s0, int* ran, hipStream_t s) {
+ed_status tridiagonal_resident(const EntWS<T>& w, int N, int s0, unsigned polls, int* ran, hipStream_t s) {
     *ran = 0;
     int n = N - s0, lda = N;
     const int G = resident_groups(n);
@@ -1140,7 +1141,7 @@ ed_status tridiagonal_resident(const EntWS<T>& w, int N, int s0, int* ran, hipSt
     T *yb = w.panel, *cb = w.panel + 2 * size_t(n);
     int *leaf = resident_leaves(w, n), *stop = resident_stop(w, n);
     hipLaunchKernelGGL(clear_flags, dim3(1), dim3(256), 0, s, leaf, int(stop - leaf) + 1);
-    void* params[] = {&A, &n, &lda, &v0, &tau0, &d, &e, &yb, &cb, &leaf, &stop};
+    void* params[] = {&A, &n, &lda, &v0, &tau0, &d, &e, &yb, &cb, &leaf, &stop, &polls};
     const void* f = s0 > 0                ? reinterpret_cast<const void*>(&hh_resident<T, 4, true>)
                     : n > 2 * kResThreads ? reinterpret_cast<const void*>(&hh_resident<T, 4, false>)
                     : n > kResThreads     ? reinterpret_cast<const void*>(&hh_resident<T, 2, false>)
@@ -1158,15 +1159,15 @@ ed_status tridiagonal_resident(const EntWS<T>& w, int N, int s0, int* ran, hipSt
 }
 
 // Step 2: the reduction of rho to the tridiagonal (w.d, w.e), all on stream s. resident: the trailing block
-// of at most kResMaxN rows (the whole matrix up to there) in one launch, *ran = its rows (0: it could
-// not be launched); the steps before it by launches.
+// of at most kResMaxN rows (the whole matrix up to there) in one launch whose waits take up to polls
+// looks, *ran = its rows (0: it could not be launched); the steps before it by launches.
 template <typename T>
-ed_status tridiagonal(const EntWS<T>& w0, int n, bool resident, int* ran, hipStream_t s) {
+ed_status tridiagonal(const EntWS<T>& w0, int n, bool resident, unsigned polls, int* ran, hipStream_t s) {
     EntWS<T> w = w0;
     *ran = 0;
     if (n < 2) return ED_OK;
     if (resident && n <= kResMaxN) {
-        ED_TRY(tridiagonal_resident(w, n, 0, ran, s));
+        ED_TRY(tridiagonal_resident(w, n, 0, polls, ran, s));
         if (*ran > 0) return ED_OK;
         resident = false;
     }
@@ -1181,7 +1182,7 @@ ed_status tridiagonal(const EntWS<T>& w0, int n, bool resident, int* ran, hipStr
     int np = 0;  // pending pairs in the panel
     for (int k = 0; k + 1 < n; ++k) {
         if (resident && np == 0 && n - k - 1 <= kResMaxN) {  // every earlier update is in rho
-            ED_TRY(tridiagonal_resident(w, n, k + 1, ran, s));
+            ED_TRY(tridiagonal_resident(w, n, k + 1, polls, ran, s));
             if (*ran > 0) return ED_OK;
             resident = false;
         }
@@ -1237,9 +1238,11 @@ extern "C" ed_status ed_entropy_workspace(int L, int l_cut, size_t* bytes) {
 }
 
 namespace {
+// polls: see ed_entropy_polls; *route: how the reduction ran
 ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum, int* real_arith,
-                       void* ws, size_t ws_bytes, void* stream) {
+                       int polls, int* route, void* ws, size_t ws_bytes, void* stream) {
     if (!psi || !S) return fail(ED_ERR_ARG, "null argument");
+    if (route) *route = 0;
     if (d != 2) return fail(ED_ERR_UNSUPPORTED, "only d = 2 is supported");
     size_t need = 0;
     ED_TRY(ed_entropy_workspace(L, l_cut, &need));
@@ -1272,10 +1275,11 @@ ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, do
         ED_HIP_TRY(hipMemcpyAsync(dd.data(), wr.rho, sizeof(double), hipMemcpyDeviceToHost, s));
         ED_HIP_TRY(hipStreamSynchronize(s));
     } else {
-        for (bool resident = true;; resident = false) {
+        for (bool resident = polls >= 0;; resident = false) {
             int ran = 0;
-            if (real) ED_TRY(tridiagonal<double>(wr, n, resident, &ran, s));
-            else ED_TRY(tridiagonal<double2>(wc, n, resident, &ran, s));
+            if (real) ED_TRY(tridiagonal<double>(wr, n, resident, unsigned(polls), &ran, s));
+            else ED_TRY(tridiagonal<double2>(wc, n, resident, unsigned(polls), &ran, s));
+            if (ran > 0 && route) *route = 1;
             // 3. eigenvalues of the tridiagonal matrix by bisection on the GPU (the partial-sum area is
             // free now: n eigenvalues, n squared off-diagonals, 4 bounds), sorted on the host
             double* lam = wr.part;
@@ -1296,6 +1300,7 @@ ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, do
             ED_HIP_TRY(hipStreamSynchronize(s));
             if (gave_up == 0) break;
             // the resident workgroups did not all run: again from the Gram matrix, by launches
+            if (route) *route = 2;
             if (real) ED_TRY(gram<double>(wr, p, left_small, n, K, s));
             else ED_TRY(gram<double2>(wc, p, left_small, n, K, s));
         }
@@ -1318,10 +1323,15 @@ ed_status entropy_impl(const ed_c64* psi, int L, int d, int l_cut, double* S, do
 
 extern "C" ed_status ed_entropy(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum, void* ws,
                                 size_t ws_bytes, void* stream) {
-    return entropy_impl(psi, L, d, l_cut, S, spectrum, nullptr, ws, ws_bytes, stream);
+    return entropy_impl(psi, L, d, l_cut, S, spectrum, nullptr, int(kResSpins), nullptr, ws, ws_bytes, stream);
 }
 
 extern "C" ed_status ed_entropy_ex(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum,
                                    int* real_arith, void* ws, size_t ws_bytes, void* stream) {
-    return entropy_impl(psi, L, d, l_cut, S, spectrum, real_arith, ws, ws_bytes, stream);
+    return entropy_impl(psi, L, d, l_cut, S, spectrum, real_arith, int(kResSpins), nullptr, ws, ws_bytes, stream);
+}
+
+extern "C" ed_status ed_entropy_polls(const ed_c64* psi, int L, int d, int l_cut, double* S, double* spectrum,
+                                      int* real_arith, int polls, int* route, void* ws, size_t ws_bytes, void* stream) {
+    return entropy_impl(psi, L, d, l_cut, S, spectrum, real_arith, polls, route, ws, ws_bytes, stream);
 }

@@ -137,3 +137,47 @@ def test_entropy_half_cut_n4096(kind):
     # the spectrum itself, to the Gram route's absolute resolution
     assert np.max(np.abs(np.sort(spec)[::-1] - ref)) < 1e-13
     assert abs(np.sum(spec) - 1.0) < 1e-12
+
+
+def _entropy_polls(psi, L, l, polls):
+    """(S, spectrum, route) with the limit of the resident reduction's waits (ed_entropy_polls)."""
+    import ctypes as C
+    nb, S, route = C.c_size_t(), C.c_double(), C.c_int(-1)
+    P.call("ed_entropy_workspace", L, l, C.byref(nb))
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=DEV)
+    spec = np.zeros(1 << min(l, L - l))
+    P.call("ed_entropy_polls", psi.data_ptr(), L, 2, l, C.byref(S), spec.ctypes.data, None, polls, C.byref(route),
+           ws.data_ptr(), nb.value, P._stream_ptr())
+    return S.value, spec, route.value
+
+
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("L,l", [(2, 1), (4, 2), (7, 3), (7, 5), (10, 5), (13, 4), (14, 7), (16, 8), (17, 9), (19, 6)])
+def test_entropy_by_launches(L, l, real):
+    """The reduction in separate launches at the sizes that the resident one takes otherwise (it is the
+    path of a refused launch), against the oracle's SVD; bounds as at the top."""
+    print(f"entropy by launches L={L} l={l} real={real}", flush=True)
+    psi = E.random_state(L, 30 + L, normalise=False, real=real)
+    S, spec, route = _entropy_polls(dev(psi), L, l, -1)
+    assert route == 0
+    Sref = OO.bond_entropy(psi, L, l)
+    assert abs(S - Sref) <= 1e-10 * abs(Sref) + 1e-12
+    assert np.max(np.abs(spec - OO.schmidt_spectrum(psi, L, l))) < 1e-13
+
+
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("L,l", [(2, 1), (12, 6), (24, 12)])
+def test_entropy_gives_up(L, l, real):
+    """A wait of the resident reduction that runs out (at the first wait with a limit of no looks, and
+    wherever a limit of one look ends it) leaves the work to the launches, from the Gram matrix on: one
+    row a workgroup, several workgroups, and the last rows of a larger matrix. Against the resident
+    result, which the tests above hold against the oracle; each spectrum is within 1e-13 of it."""
+    print(f"entropy gives up L={L} l={l} real={real}", flush=True)
+    psi = E.random_state_device(L, 7, DEV, real=real)
+    S, spec, route = _entropy_polls(psi, L, l, 1 << 18)
+    assert route == 1
+    for polls in (0, 1):
+        S1, spec1, route = _entropy_polls(psi, L, l, polls)
+        assert route == 2 or polls == 1
+        assert abs(S1 - S) <= 1e-10 * abs(S) + 1e-12
+        assert np.max(np.abs(spec1 - spec)) < 2e-13
