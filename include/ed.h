@@ -136,7 +136,8 @@ ed_status ed_model_tune(ed_model* model, const ed_c64* psi, ed_c64* out, int rep
  * list, so it applies only to models whose planner proposes the same candidates.
  *   ed_model_create / ed_liouville_create select the cached plan, and the direct product if the
  *     entry says so and the model can run it, when the key has an entry whose plan is among the
- *     candidates (else the default described above, as without a cache);
+ *     candidates (else the default described above, as without a cache; a Liouvillian without an
+ *     entry takes that of the chain of as many sites and the same class, whose local terms are alike);
  *   ed_model_tune stores its choice under the model's key;
  *   ed_plan_cache_load merges "<key> TAB <plan>" lines from a text file ('#' starts a comment)
  *     and returns the number of entries read; ed_plan_cache_save writes every entry (replacing the

@@ -551,8 +551,7 @@ ed_status validate_desc(const ed_model_desc* desc) {
 
 void apply_cached_plan(ed_model* m);
 
-// A model on its default product: what the plan cache holds for its key is not looked up here.
-static ed_status create_default(const ed_model_desc* desc, ed_model** out) {
+ed_status create_model(const ed_model_desc* desc, ed_model** out) {
     ED_TRY(validate_desc(desc));
     ed_model* m = new (std::nothrow) ed_model();
     if (!m) return fail(ED_ERR_NOMEM, "host allocation failed");
@@ -564,13 +563,8 @@ static ed_status create_default(const ed_model_desc* desc, ed_model** out) {
         delete m;
         return st;
     }
+    apply_cached_plan(m);
     *out = m;
-    return ED_OK;
-}
-
-ed_status create_model(const ed_model_desc* desc, ed_model** out) {
-    ED_TRY(create_default(desc, out));
-    apply_cached_plan(*out);
     return ED_OK;
 }
 
@@ -655,7 +649,7 @@ ed_status create_liouville(const ed_model_desc* H, int n_jump, const ed_c64* jum
     d.bond_coef = bcoef.data();
     d.n_inf = 0;
     ed_model* m = nullptr;
-    ED_TRY(create_default(&d, &m));  // (the chain of 2L sites has another key)
+    ED_TRY(create_model(&d, &m));  // (with what the cache holds for the chain of 2L sites)
     m->lv_L = L;
     // jump sandwiches i gamma J (x) J^*, row bit q = 2L - k, column bit p = L - k of site k
     for (int k = 1; k <= L; ++k) {

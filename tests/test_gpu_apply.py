@@ -184,7 +184,7 @@ def test_direct_product_equals_the_plans(L):
 def test_cached_choice_runs_at_creation(tmp_path):
     """A short chain starts on what the cache says: a plan, or the direct product where the entry ends
     with " direct" (and the model can run it); a tuned handle and a new one run the same code; a
-    Liouvillian does not take the entry of the chain of as many bits."""
+    Liouvillian takes its own entry before that of the chain of as many bits."""
     L = 16
     new = lambda: P.Model(E.tfim(L, 0.5))
     psi = E.random_state_device(L, 11, DEV)
@@ -215,7 +215,9 @@ def test_cached_choice_runs_at_creation(tmp_path):
         assert (big.passes, big.plans[1]) == (2, 1)     # too long for the direct product: its plan
         lv = P.Liouville(E.xxz(8, 1.0, 1.0), [], np.zeros((0, 8)))
         P.plan_cache_put(lv.plan_key.replace("liouville=8", "liouville=0"), lv.describe_plan(2))
-        assert P.Liouville(E.xxz(8, 1.0, 1.0), [], np.zeros((0, 8))).plans[1] == 0
+        assert P.Liouville(E.xxz(8, 1.0, 1.0), [], np.zeros((0, 8))).plans[1] == 2
+        P.plan_cache_put(lv.plan_key, lv.describe_plan(1))
+        assert P.Liouville(E.xxz(8, 1.0, 1.0), [], np.zeros((0, 8))).plans[1] == 1
     finally:
         P.plan_cache_clear()
         if os.path.exists(P._lib.DEFAULT_PLANS):
