@@ -596,15 +596,18 @@ ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace&
         a.scale = T.scale;
         a.tiles = nullptr;
         a.ntiles = 0;
-        // the product's projections per tile go to the front of the partial buffer, the sweep's to its end
-        const int64_t room = int64_t(kPartBytes / sizeof(double2)) - kRedBlocks;
-        a.part = reinterpret_cast<double*>(w.part + room);
+        // the product's projections per tile may fill the partial buffer (2^30 amplitudes do); the sweep's
+        // partials take their place, or the buffer's end where the sweep itself reads the projections
+        constexpr int64_t room = int64_t(kPartBytes / sizeof(double2));
+        static_assert(2 * kOwnParts + kRedBlocks <= room, "partial buffer");
+        a.part = reinterpret_cast<double*>(w.part);
         a.ticket = one ? T.ticket : nullptr;
         int64_t nparts = 0;
         ED_TRY(launch_apply_H_dot(m, a.u, a.y, w.part, room / (a.both ? 2 : 1), &nparts, s, a.both ? a.um1 : nullptr));
         if (nparts > 0 && nparts <= kOwnParts) {
             a.tiles = w.part;
             a.ntiles = int(nparts);
+            a.part = reinterpret_cast<double*>(w.part + room - kRedBlocks);
         } else if (nparts > 0) {
             const int n = a.both ? 4 : 2;  // doubles per tile
             hipLaunchKernelGGL(sum_rows, dim3(unsigned(n)), dim3(kSmallThr), 0, s,
