@@ -232,8 +232,8 @@ ed_status ed_lanczos_ground(const ed_model* model, const ed_c64* v0, const ed_la
  * reorth = 1 orthogonalises every new vector against the whole basis by classical Gram-Schmidt,
  * with a second pass when the first removed more than half of the squared norm (the DGKS test
  * with eta = 1/sqrt(2); info->reorth_skipped counts the second passes found unnecessary);
- * reorth = 0 against the previous two (the three-term recurrence with local re-projection;
- * Hermitian only). Arnoldi (hermitian = 0) needs reorth = 1.
+ * reorth = 0 against the previous two (the three-term recurrence: the projection on the last vector
+ * but one is the previous step's norm; Hermitian only). Arnoldi (hermitian = 0) needs reorth = 1.
  * psi     device, D amplitudes, in place: psi(0) on entry, psi(n_steps dt) on exit; no
  *         renormalisation (the norm drift is measured).
  * obs     arrays, each may be NULL: sz[(n_steps+1) * L] = <sigma^z_k>/<psi|psi> for sites

@@ -18,7 +18,7 @@ constexpr int kMultiOut = 8;      // outputs of one multi-output combination
 
 // Sweeps over basis vectors read them with non-temporal loads when what a sweep reads outgrows the 256 MB
 // cache in front of HBM: nothing of it would be found there by the next sweep, and keeping it out leaves
-// the channels to the rest. w -= sum over 7 vectors of 2^26 amplitudes: 1.96 -> 1.85 ms (4.9 -> 5.2 TB/s);
+// the channels to the rest. w -= sum over 7 vectors of 2^26 amplitudes: 1.82 -> 1.69 ms (5.3 -> 5.7 TB/s);
 // below that size the cache serves the next sweep.
 constexpr int64_t kCacheBytes = int64_t(256) << 20;
 inline bool outgrows_cache(int64_t nvec, int64_t D) { return nvec * D * int64_t(sizeof(double2)) > kCacheBytes; }

@@ -256,8 +256,8 @@ struct SmallArgs {
 // Iterations j0 .. j0 + nj - 1 for a state of at most 2^12 amplitudes in one workgroup: u_j sits in
 // LDS, every other vector of the iteration in registers (up to four amplitudes per thread; the
 // diagonal too, which all iterations share). Bound by latency: an iteration is one product from LDS and
-// two workgroup sums, about 8 us for the XXZ chain at L = 12 (a ten-step quench: 1.91 ms), against 45 us
-// in separate launches with a round trip each (5.25 ms).
+// two workgroup sums, about 8 us for the XXZ chain at L = 12 (a ten-step quench: 1.63 ms), against 45 us
+// in separate launches with a round trip each (4.79 ms).
 template <unsigned CLS>
 __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const double2* __restrict__ site,
                                                               const double2* __restrict__ bond) {
