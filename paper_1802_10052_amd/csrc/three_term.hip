@@ -173,6 +173,8 @@ __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
     __shared__ double lds[kThr / 64][4];
     __shared__ double lds1[kThr / 64][1];
     const int t = threadIdx.x;
+    // the norms come from HBM (another workgroup wrote them): asked for before the tiles are summed
+    const double2 Nj = A.N[A.j], Nm = A.N[A.um1 ? A.j - 1 : A.j];
     double p[4] = {0.0, 0.0, 0.0, 0.0};
     if (A.tiles) {
         const int st = A.both ? 2 : 1;
@@ -199,15 +201,10 @@ __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
             p[3] = A.SP[2 * A.j + 1].y;
         }
     }
-    const double nj = A.N[A.j].x;
+    const double nj = Nj.x, nm = Nm.x, sm = Nj.y;
     const double2 a = make_double2(p[0] / nj, p[1] / nj);
     double2 b = make_double2(0.0, 0.0);
-    double nm = 1.0, sm = 1.0;
-    if (A.um1) {
-        nm = A.N[A.j - 1].x;
-        sm = A.N[A.j].y;
-        b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (sm * nm), 0.0);
-    }
+    if (A.um1) b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (sm * nm), 0.0);
     const double sj = step_scale(A.j, A.scale, nj, nm, sm);
     if (blockIdx.x == 0 && t == 0) A.N[A.j + 1].y = sj;
     double n2[1] = {0.0};
