@@ -229,7 +229,6 @@ ed_status build_basis(const ed_model* mod, const double2* psi, double dt_err, co
                       bool alias, hipStream_t s) {
     const int mmax = p->m_max;
     const int guess = B->m;
-    B->T.scale = three_term_scale(mod);
     ED_TRY(three_term_start(B->T, B->w, psi, alias, false, s));
     std::vector<double> a(mmax + 1), b(mmax + 1);
     std::vector<double2> hv(B->T.count());
@@ -394,8 +393,8 @@ extern "C" ed_status ed_evolve_adjoint(const ed_model* tmpl, int n_slices, doubl
     double2* mun = reinterpret_cast<double2*>(c);
     c += al(vec);
     double* dw = reinterpret_cast<double*>(c);
-    ED_TRY(three_term_init(tmpl, Bp.w, p->m_max, &Bp.T, s));
-    ED_TRY(three_term_init(tmpl, Bm.w, p->m_max, &Bm.T, s));
+    ED_TRY(three_term_init(Bp.w, p->m_max, &Bp.T, s));
+    ED_TRY(three_term_init(Bm.w, p->m_max, &Bm.T, s));
 
     ModelSet ms;
     ED_TRY(slice_models(tmpl, S, J, &ms));
@@ -496,7 +495,7 @@ extern "C" ed_status ed_evolve_loss(const ed_model* tmpl, int n_slices, double s
     const size_t basis_bytes = core_scratch_bytes() + al(size_t(p->m_max + 1) * size_t(D) * sizeof(double2));
     ED_TRY(carve(ws, basis_bytes, D, p->m_max + 1, &B.w));
     double2* psi = reinterpret_cast<double2*>(static_cast<char*>(ws) + basis_bytes);
-    ED_TRY(three_term_init(tmpl, B.w, p->m_max, &B.T, s));
+    ED_TRY(three_term_init(B.w, p->m_max, &B.T, s));
     ModelSet ms;
     ED_TRY(slice_models(tmpl, n_slices, J, &ms));
     ED_HIP_TRY(hipMemcpyAsync(psi, psi0, size_t(D) * sizeof(double2), hipMemcpyDeviceToDevice, s));

@@ -740,7 +740,7 @@ ed_status evolve_three_term(const ed_model* m, const Workspace& w, double2* psi,
     const bool small = three_term_small_fits(m) && mmax <= kMaxComb;
     const int cap = w.D <= (int64_t(1) << 22) ? mmax : 1;
     ThreeTerm T;
-    ED_TRY(three_term_init(m, w, mmax, &T, s));
+    ED_TRY(three_term_init(w, mmax, &T, s));
     double2* const res = w.scal + kObs;
     std::vector<double2> hv(size_t(T.count()) + L + 1);
     const double2* const hN = hv.data();

@@ -122,16 +122,15 @@ constexpr int kThreeTermFree = 140;  // scalars at the front that N and SP leave
 constexpr int kThreeTermMax = 256;  // basis dimensions whose scalars fit there
 struct ThreeTerm {
     int mmax = 0;
-    double scale = 1.0;  // the model's, for the first step
     double2 *N = nullptr, *SP = nullptr;
     unsigned* ticket = nullptr;
     int count() const { return 3 * mmax + 2; }
 };
-ed_status three_term_init(const ed_model* m, const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s);
-double three_term_scale(const ed_model* m);
+ed_status three_term_init(const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s);
 // beta_j from the fetched scalars, and whether the space is invariant: beta_j <= 1e-14 hmax (hmax: the step's
-// largest projection). Every s_j keeps |u_{j+1}| near 1 for a beta_j near beta_{j-1}, so N_{j+1} leaves the
-// normal numbers only for a beta_j far below that bound; should it do so otherwise, ED_ERR_NUMERIC.
+// largest projection). s_j keeps |u_{j+1}| near 1 for a beta_j near beta_{j-1} (near beta_0 for j = 0), so
+// N_{j+1} leaves the normal numbers only for a beta_j far below that bound; should it do so otherwise, as for
+// a beta_0 below 1e-154, ED_ERR_NUMERIC.
 ed_status three_term_beta(const double2* N, int j, double hmax, double* beta, bool* brk);
 // Basis vector 0: psi itself (alias) or a copy in slot 0, and N[0] unless it is known to hold |psi|^2.
 ed_status three_term_start(const ThreeTerm& T, const Workspace& w, const double2* psi, bool alias, bool have_norm,

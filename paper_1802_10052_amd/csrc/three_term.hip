@@ -7,9 +7,9 @@
 // step's norm, for a Hermitian H), or b_j = <u_{j-1}|H u_j> / N_{j-1} where both projections are taken.
 // So alpha_j = a_j and beta_j = sqrt(N_{j+1} / N_j) / s_j, and every coefficient of a sweep comes
 // from device scalars that earlier kernels of the same stream wrote. s_j (kept in N[j+1].y) is the power
-// of two that brings |u_{j+1}| near 1 if beta_j is near beta_{j-1}; s_0 comes from a bound of |H|. Scaling by
-// it is exact. One factor for all steps would not do: a bound of |H| can be far above every beta (a
-// uniform field that only turns the phase), and the norms then underflow within a basis.
+// of two that brings |u_{j+1}| near 1 if beta_j is near beta_{j-1}, and s_0 = 1 / |u_0| to a factor of two.
+// Scaling by it is exact. One factor for all steps, from a bound of |H|, would not do: the bound can be
+// far above every beta (a uniform field that only turns the phase), and the norms then underflow.
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
@@ -36,10 +36,9 @@ __device__ __forceinline__ int exponent_of(double v) {
 }
 
 // s_j from N_j and, past the first step, N_{j-1} and s_{j-1}: |H u_j - ...| is about beta_{j-1} sqrt(N_j) =
-// N_j / (s_{j-1} sqrt(N_{j-1})). first: the model's scale, a power of two at or below 1 / |H|.
-__device__ __forceinline__ double step_scale(int j, double first, double nj, double nm, double sm) {
-    const int k = j == 0 ? exponent_of(first) - (exponent_of(nj) >> 1)
-                         : exponent_of(sm) - exponent_of(nj) + (exponent_of(nm) >> 1);
+// N_j / (s_{j-1} sqrt(N_{j-1})).
+__device__ __forceinline__ double step_scale(int j, double nj, double nm, double sm) {
+    const int k = j == 0 ? -(exponent_of(nj) >> 1) : exponent_of(sm) - exponent_of(nj) + (exponent_of(nm) >> 1);
     return __longlong_as_double(static_cast<long long>(min(max(k, -1000), 1000) + 1023) << 52);
 }
 
@@ -158,7 +157,6 @@ struct SubArgs {
     int64_t D;
     double2 *N, *SP;  // N_j in N[j].x, s_{j-1} in N[j].y; SP[2 j] = <u_j|y>, SP[2 j + 1] = <u_{j-1}|y>
     int j, both;
-    double scale;     // the model's
     const double2* tiles;  // per-tile partials of <u_j|y> (and <u_{j-1}|y>), or null: SP holds the sums
     int ntiles;
     double* part;
@@ -205,7 +203,7 @@ __global__ __launch_bounds__(kThr) void three_term_sub(SubArgs A) {
     const double2 a = make_double2(p[0] / nj, p[1] / nj);
     double2 b = make_double2(0.0, 0.0);
     if (A.um1) b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (sm * nm), 0.0);
-    const double sj = step_scale(A.j, A.scale, nj, nm, sm);
+    const double sj = step_scale(A.j, nj, nm, sm);
     if (blockIdx.x == 0 && t == 0) A.N[A.j + 1].y = sj;
     double n2[1] = {0.0};
     const int64_t chunk = (A.D + gridDim.x - 1) / gridDim.x;
@@ -247,7 +245,6 @@ struct SmallArgs {
     int64_t D;
     double2 *N, *SP;
     int j0, nj;
-    double scale;
 };
 
 // Iterations j0 .. j0 + nj - 1 for a state of at most 2^12 amplitudes in one workgroup: u_j sits in
@@ -369,7 +366,7 @@ __global__ __launch_bounds__(kSmallThr) void three_term_small(SmallArgs A, const
         const double2 a = make_double2(p[0] / nj, p[1] / nj);
         double2 b = make_double2(0.0, 0.0);
         if (j > 0) b = A.both ? make_double2(p[2] / nm, p[3] / nm) : make_double2(nj / (sm * nm), 0.0);
-        sm = step_scale(j, A.scale, nj, nm, sm);
+        sm = step_scale(j, nj, nm, sm);
         double n2[1] = {0.0};
         double2* out = A.V + int64_t(j + 1) * A.D;
 #pragma unroll
@@ -492,17 +489,6 @@ unsigned sweep_blocks(int64_t D) {
 
 }  // namespace
 
-double three_term_scale(const ed_model* m) {
-    double b = 0.0;
-    for (const double2& v : m->site) b += std::hypot(v.x, v.y);
-    for (const double2& v : m->bond) b += std::hypot(v.x, v.y);
-    for (const double2& v : m->lrz) b += std::hypot(v.x, v.y);
-    if (!(b > 0.0) || !std::isfinite(b)) return 1.0;
-    int e = 0;
-    (void)std::frexp(b, &e);  // b < 2^e
-    return std::ldexp(1.0, -e);
-}
-
 ed_status three_term_beta(const double2* N, int j, double hmax, double* beta, bool* brk) {
     const double n1 = std::max(N[j + 1].x, 0.0);
     *beta = std::sqrt(n1) / std::sqrt(N[j].x) / N[j + 1].y;
@@ -511,10 +497,9 @@ ed_status three_term_beta(const double2* N, int j, double hmax, double* beta, bo
     return ED_OK;
 }
 
-ed_status three_term_init(const ed_model* m, const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s) {
+ed_status three_term_init(const Workspace& w, int mmax, ThreeTerm* T, hipStream_t s) {
     if (mmax > kThreeTermMax || kThreeTermFree + 3 * mmax + 2 > kObs) return fail(ED_ERR_UNSUPPORTED, "basis too large for device scalars");
     T->mmax = mmax;
-    T->scale = three_term_scale(m);
     T->N = w.scal + kObs - T->count();
     T->SP = T->N + mmax + 2;
     static_assert((kTickets + 1) * kTicketStride * sizeof(unsigned) <= kThreeTermFree * sizeof(double2), "scalar area");
@@ -574,7 +559,6 @@ ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace&
         a.SP = T.SP;
         a.j0 = j0;
         a.nj = nj;
-        a.scale = T.scale;
         ED_L(launch_small<0>(m->op_class, a, m->d_site, m->d_bond, s));
         return ED_OK;
     }
@@ -590,7 +574,6 @@ ed_status three_term_run(const ed_model* m, const ThreeTerm& T, const Workspace&
         a.SP = T.SP;
         a.j = j;
         a.both = both && j > 0 ? 1 : 0;
-        a.scale = T.scale;
         a.tiles = nullptr;
         a.ntiles = 0;
         // the product's projections per tile may fill the partial buffer (2^30 amplitudes do); the sweep's

@@ -464,3 +464,21 @@ def test_krylov_L30():
     for n in range(3):
         assert np.max(np.abs(obs["sz"][n] - np.cos(2 * g * n * dt))) < 1e-9, n
         assert abs(obs["norm"][n] - 1.0) < 1e-12
+
+
+@pytest.mark.parametrize("L", [12, 13])
+@pytest.mark.parametrize("penalty", [1e60, 1e180])
+def test_krylov_unvisited_penalty(L, penalty):
+    """A penalty on configurations that the state never visits (one site stays up) changes nothing,
+    whatever its size: the recurrence's scales come from the state, not from the operators."""
+    flip, pen = np.full(L, -0.7), np.zeros(L)
+    flip[3], pen[3] = 0.0, penalty
+    bonds = dict(bond_ops=[E.SZSZ], bond_coef=np.full((1, L - 1), -1.0))
+    out = []
+    for p in (0.0 * pen, pen):
+        psi = dev(E.product_state(L, 0))
+        m = P.Model(E.ModelDesc(L, site_ops=[E.SX, np.diag([0.0, 1.0])], site_coef=np.stack([flip, p]), **bonds))
+        _, obs, info = P.krylov_evolve(m, psi, 0.1, 3, m_max=40, tol=1e-12)
+        out.append((psi, info["total_m"]))
+    assert out[0][1] == out[1][1]
+    assert torch.linalg.vector_norm(out[0][0] - out[1][0]) < 1e-13
